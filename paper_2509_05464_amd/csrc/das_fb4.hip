@@ -1,0 +1,6 @@
+// Delay-and-sum kernels for blocks of 4 frames.
+#include "das_kernel.hpp"
+
+namespace fq {
+DasFn das_fn4(int at, int interp, bool wide) { return das_pick<4>(at, interp, wide); }
+}  // namespace fq

@@ -1,0 +1,6 @@
+// Delay-and-sum kernels for blocks of 7 frames.
+#include "das_kernel.hpp"
+
+namespace fq {
+DasFn das_fn7(int at, int interp, bool wide) { return das_pick<7>(at, interp, wide); }
+}  // namespace fq
