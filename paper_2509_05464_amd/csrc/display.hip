@@ -6,9 +6,9 @@
 //   displayed power p = PD (power) or |IQ|^2 (complex IQ; 20 log10 |IQ| = 10 log10 |IQ|^2)
 //   out = max(-dr, 10 log10(p / max p));  max p == 0 shows everything at -dr;
 //   or, as grey levels, 1 + out / dr in [0, 1].
-// The reference max p comes from a two-pass reduction (block maxima, then one block); a
-// maximum does not depend on the order of its operands, so the result is exact and
-// deterministic.  The logarithms use the hardware log2 (error far below 1e-4 dB).
+// The reference max p comes from block maxima that every block of the second pass reduces
+// again; a maximum does not depend on the order of its operands, so the result is exact
+// and deterministic.  The logarithms use the hardware log2 (error far below 1e-4 dB).
 #include "fq_common.hpp"
 
 namespace fq {
@@ -32,6 +32,8 @@ __device__ __forceinline__ float block_max(float m, float* s) {
     return fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
 }
 
+// displayed power of value i, and of the values of one 16-byte load (four powers, or two
+// IQ samples)
 template <bool IQ>
 __device__ __forceinline__ float power_at(const float* in, int64_t i) {
     if (IQ) {
@@ -42,53 +44,100 @@ __device__ __forceinline__ float power_at(const float* in, int64_t i) {
 }
 
 template <bool IQ>
+struct Quad {
+    static constexpr int N = IQ ? 2 : 4;
+    float p[N];
+    __device__ __forceinline__ Quad(const float* in, int64_t q) {
+        const float4 v = reinterpret_cast<const float4*>(in)[q];
+        if constexpr (IQ) {
+            p[0] = v.x * v.x + v.y * v.y;
+            p[1] = v.z * v.z + v.w * v.w;
+        } else {
+            p[0] = v.x;
+            p[1] = v.y;
+            p[2] = v.z;
+            p[3] = v.w;
+        }
+    }
+};
+
+template <bool IQ>
 __global__ void __launch_bounds__(DISP_THREADS) peak_partial_kernel(const float* in, int64_t n, float* part) {
+    constexpr int N = Quad<IQ>::N;
     __shared__ float s[4];
     float m = 0.0f;
-    for (int64_t i = (int64_t)blockIdx.x * DISP_THREADS + threadIdx.x; i < n; i += (int64_t)gridDim.x * DISP_THREADS)
-        m = fmaxf(m, power_at<IQ>(in, i));
+    const int64_t i0 = (int64_t)blockIdx.x * DISP_THREADS + threadIdx.x, step = (int64_t)gridDim.x * DISP_THREADS;
+    for (int64_t q = i0; q < n / N; q += step) {
+        const Quad<IQ> v(in, q);
+#pragma unroll
+        for (int k = 0; k < N; ++k) m = fmaxf(m, v.p[k]);
+    }
+    if (i0 < n % N) m = fmaxf(m, power_at<IQ>(in, n - 1 - i0));
     m = block_max(m, s);
     if (threadIdx.x == 0) part[blockIdx.x] = m;
 }
 
-__global__ void __launch_bounds__(DISP_THREADS) peak_final_kernel(const float* part, int nb, float* peak) {
-    __shared__ float s[4];
-    float m = 0.0f;
-    for (int i = threadIdx.x; i < nb; i += DISP_THREADS) m = fmaxf(m, part[i]);
-    m = block_max(m, s);
-    if (threadIdx.x == 0) *peak = m;
-}
-
+// Every block reduces the block maxima itself (at most DISP_MAX_BLOCKS words out of L2):
+// a launch of one block between the two passes cost 3 us and its gap.
 template <bool IQ>
-__global__ void __launch_bounds__(DISP_THREADS) db_kernel(const float* in, int64_t n, const float* peak, float neg_dr,
-                                                          int unit, float* out) {
-    const float pk = *peak;
+__global__ void __launch_bounds__(DISP_THREADS) db_kernel(const float* in, int64_t n, const float* part, int nb,
+                                                          float* peak, float neg_dr, int unit, float* out) {
+    constexpr int N = Quad<IQ>::N;
+    __shared__ float s[4];
+    float pk = 0.0f;
+    for (int i = threadIdx.x; i < nb; i += DISP_THREADS) pk = fmaxf(pk, part[i]);
+    pk = block_max(pk, s);
+    if (peak && blockIdx.x == 0 && threadIdx.x == 0) *peak = pk;
     const float lpk = __builtin_amdgcn_logf(pk);   // log2
-    for (int64_t i = (int64_t)blockIdx.x * DISP_THREADS + threadIdx.x; i < n; i += (int64_t)gridDim.x * DISP_THREADS) {
-        const float p = power_at<IQ>(in, i);
+    auto level = [&](float p) {
         float d = neg_dr;
         if (pk > 0.0f && p > 0.0f) d = fmaxf(neg_dr, TEN_LOG10_2 * (__builtin_amdgcn_logf(p) - lpk));
         // grey level (d + dr) / dr: exactly 0 at the floor and 1 at the peak
-        out[i] = unit ? (d - neg_dr) / -neg_dr : d;
+        return unit ? (d - neg_dr) / -neg_dr : d;
+    };
+    const int64_t i0 = (int64_t)blockIdx.x * DISP_THREADS + threadIdx.x, step = (int64_t)gridDim.x * DISP_THREADS;
+    for (int64_t q = i0; q < n / N; q += step) {
+        const Quad<IQ> v(in, q);
+        if constexpr (IQ)
+            reinterpret_cast<float2*>(out)[q] = make_float2(level(v.p[0]), level(v.p[1]));
+        else
+            reinterpret_cast<float4*>(out)[q] = make_float4(level(v.p[0]), level(v.p[1]), level(v.p[2]), level(v.p[3]));
+    }
+    if (i0 < n % N) {
+        const int64_t i = n - 1 - i0;
+        out[i] = level(power_at<IQ>(in, i));
     }
 }
 
-// MIP onto x-y (max over z) or x-z (max over y): one thread per output pixel, the
-// reduction runs along a strided axis while neighbouring threads read neighbouring x.
-__global__ void __launch_bounds__(DISP_THREADS) mip_strided_kernel(const float* vol, int nx, int ny, int nz,
-                                                                   int over_z, float* out) {
-    const int64_t idx = (int64_t)blockIdx.x * DISP_THREADS + threadIdx.x;
+// MIP onto x-y (max over z) or x-z (max over y): a workgroup takes 64 consecutive output
+// pixels, its 16 waves share the planes (or rows) of the reduction, so that a 64^3 volume
+// keeps 1024 waves of independent reads in flight where one thread per pixel kept 64
+// waves in a chain of 64 reads (13.6 us).
+constexpr int MIP_SEG = 16;
+
+__global__ void __launch_bounds__(64 * MIP_SEG) mip_strided_kernel(const float* vol, int nx, int ny, int nz,
+                                                                  int over_z, float* out) {
+    __shared__ float s[MIP_SEG][64];
+    const int l = threadIdx.x & 63, seg = threadIdx.x >> 6;
+    const int64_t idx = (int64_t)blockIdx.x * 64 + l;
     const int64_t n_out = over_z ? (int64_t)nx * ny : (int64_t)nx * nz;
-    if (idx >= n_out) return;
-    const int ix = (int)(idx % nx);
-    const int o = (int)(idx / nx);   // iy (over z) or iz (over y)
     float m = -INFINITY;
-    if (over_z) {
-        for (int iz = 0; iz < nz; ++iz) m = fmaxf(m, vol[((int64_t)iz * ny + o) * nx + ix]);
-    } else {
-        for (int iy = 0; iy < ny; ++iy) m = fmaxf(m, vol[((int64_t)o * ny + iy) * nx + ix]);
+    if (idx < n_out) {
+        // over z: pixel (ix, iy) is voxel idx of every plane; over y: pixel (ix, iz) starts at row iz * ny
+        const int64_t o = idx / nx, plane = (int64_t)nx * ny;
+        const float* src = vol + (over_z ? idx : idx + o * (plane - nx));
+        const int64_t stride = over_z ? plane : nx;
+        const int len = over_z ? nz : ny;
+#pragma unroll 4
+        for (int k = seg; k < len; k += MIP_SEG) m = fmaxf(m, src[k * stride]);
     }
-    out[idx] = m;
+    s[seg][l] = m;
+    __syncthreads();
+    if (seg == 0 && idx < n_out) {
+#pragma unroll
+        for (int k = 1; k < MIP_SEG; ++k) m = fmaxf(m, s[k][l]);
+        out[idx] = m;
+    }
 }
 
 // MIP onto y-z (max over x): one wave per row of x.
@@ -103,7 +152,23 @@ __global__ void __launch_bounds__(DISP_THREADS) mip_rows_kernel(const float* vol
     if (l == 0) out[row] = m;
 }
 
-int blocks_for(int64_t n) { return (int)std::max<int64_t>(1, std::min<int64_t>(DISP_MAX_BLOCKS, (n + DISP_THREADS - 1) / DISP_THREADS)); }
+// blocks of the two display passes: one 16-byte load per thread and pass until the block
+// maxima fill their workspace
+int blocks_for(int64_t n, int per_thread) {
+    const int64_t per = (int64_t)DISP_THREADS * per_thread;
+    return (int)std::max<int64_t>(1, std::min<int64_t>(DISP_MAX_BLOCKS, (n + per - 1) / per));
+}
+
+template <bool IQ>
+int launch_display(const float* in, int64_t n, float* part, float* peak, float neg_dr, int unit, float* out,
+                   hipStream_t s) {
+    const int nb = blocks_for(n, Quad<IQ>::N);
+    hipLaunchKernelGGL(peak_partial_kernel<IQ>, dim3(nb), dim3(DISP_THREADS), 0, s, in, n, part);
+    FQ_LAUNCH_CHECK();
+    hipLaunchKernelGGL(db_kernel<IQ>, dim3(nb), dim3(DISP_THREADS), 0, s, in, n, part, nb, peak, neg_dr, unit, out);
+    FQ_LAUNCH_CHECK();
+    return FQ_OK;
+}
 
 }  // namespace
 }  // namespace fq
@@ -129,21 +194,8 @@ extern "C" int display_db(const float* in, int64_t n, int32_t kind, float dr_db,
     }
     hipStream_t s = as_stream(stream);
     float* part = reinterpret_cast<float*>(ws);
-    float* pk = peak ? peak : part + DISP_MAX_BLOCKS;
-    const int nb = blocks_for(n);
-    if (kind == FQ_DISP_IQ)
-        hipLaunchKernelGGL(peak_partial_kernel<true>, dim3(nb), dim3(DISP_THREADS), 0, s, in, n, part);
-    else
-        hipLaunchKernelGGL(peak_partial_kernel<false>, dim3(nb), dim3(DISP_THREADS), 0, s, in, n, part);
-    FQ_LAUNCH_CHECK();
-    hipLaunchKernelGGL(peak_final_kernel, dim3(1), dim3(DISP_THREADS), 0, s, part, nb, pk);
-    FQ_LAUNCH_CHECK();
-    if (kind == FQ_DISP_IQ)
-        hipLaunchKernelGGL(db_kernel<true>, dim3(nb), dim3(DISP_THREADS), 0, s, in, n, pk, -dr_db, unit ? 1 : 0, out);
-    else
-        hipLaunchKernelGGL(db_kernel<false>, dim3(nb), dim3(DISP_THREADS), 0, s, in, n, pk, -dr_db, unit ? 1 : 0, out);
-    FQ_LAUNCH_CHECK();
-    return FQ_OK;
+    return kind == FQ_DISP_IQ ? launch_display<true>(in, n, part, peak, -dr_db, unit ? 1 : 0, out, s)
+                              : launch_display<false>(in, n, part, peak, -dr_db, unit ? 1 : 0, out, s);
 }
 
 extern "C" int mip(const float* vol, int32_t nx, int32_t ny, int32_t nz, int32_t plane, float* out, void* stream) {
@@ -158,8 +210,8 @@ extern "C" int mip(const float* vol, int32_t nx, int32_t ny, int32_t nz, int32_t
     } else {
         const int over_z = plane == FQ_MIP_XY ? 1 : 0;
         const int64_t n_out = over_z ? (int64_t)nx * ny : (int64_t)nx * nz;
-        const unsigned nb = (unsigned)((n_out + DISP_THREADS - 1) / DISP_THREADS);
-        hipLaunchKernelGGL(mip_strided_kernel, dim3(nb), dim3(DISP_THREADS), 0, s, vol, nx, ny, nz, over_z, out);
+        const unsigned nb = (unsigned)((n_out + 63) / 64);
+        hipLaunchKernelGGL(mip_strided_kernel, dim3(nb), dim3(64 * MIP_SEG), 0, s, vol, nx, ny, nz, over_z, out);
     }
     FQ_LAUNCH_CHECK();
     return FQ_OK;
