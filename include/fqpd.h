@@ -379,8 +379,8 @@ int lcf_forward(const float* w, const uint16_t* w_bf16, const float* x, int64_t 
 
 /*  After lcf_forward(..., act, ...) on the same x: gradient of
  *  loss = mean over (series, channel, t) of (y - [Re, Im](target)/r)^2.
- *  target complex64 [n_t][n_series]; act is consumed (the dz of each layer overwrites its
- *  pre-activation, and its tail holds per-wave gradient partials, reduced in a fixed
+ *  target complex64 [n_t][n_series]; act is consumed (layer 2's dz overwrites its
+ *  pre-activation, and its tail holds per-workgroup gradient partials, reduced in a fixed
  *  order so the gradient is deterministic); grad float32 [19170] (overwritten);
  *  loss float32 [1] (device, overwritten). */
 int lcf_backward(const float* w, const uint16_t* w_bf16, const float* x, const float* target,

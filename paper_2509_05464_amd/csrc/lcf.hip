@@ -15,7 +15,7 @@
 // Backward: dgrad is the same conv on dz with the transposed, time-flipped kernel
 // (A[i][k'*32+o] = W[o][i][8-k']); wgrad reduces over time,
 //   dW[o][i][k] = sum_t dz[t][o] h[t+k-4][i],
-// with K = time: its operands are gathered from the time-major images.
+// with K = time: its operands come from the time-major images by transposing LDS reads.
 // Rounding points (round to nearest even): weights (BF16 copy kept by Adam), the
 // network input, every stored activation (z and h of layers 1-3) and every dz; all
 // accumulation, biases, GELU and the output layer are FP32.
@@ -34,10 +34,8 @@ constexpr int OFF_W1 = 0, OFF_B1 = 576, OFF_W2 = 608, OFF_B2 = 9824, OFF_W3 = 98
               OFF_W4 = 19104, OFF_B4 = 19168, NPAR = 19170;
 constexpr int K1C = 2;    // layer-1 K chunks: 9 taps x 2 channels = 18 -> 32
 constexpr int K2C = 18;   // 32->32 K chunks: 9 taps x 32 channels = 288
-constexpr int NWB = 256;  // waves of the backward reduction kernels
-constexpr int PART = 9216 + 32;   // partial gradient of one 32->32 layer (W then b)
-constexpr int PART1 = 576 + 32;   // partial gradient of layer 1
-constexpr int PART4 = 64 + 2 + 1; // partial gradient of layer 4 + loss
+constexpr int NWB = 256;          // workgroups of the backward pass, at most
+constexpr int PART = NPAR + 1;    // partial gradient of a workgroup, then its loss sum
 
 __device__ __forceinline__ unsigned short f2bf(float x) {
     unsigned int u = __float_as_uint(x);
@@ -61,11 +59,12 @@ __device__ __forceinline__ unsigned int f2bf2(float lo, float hi) {
     const bf16x2 v = {(__bf16)lo, (__bf16)hi};
     return __builtin_bit_cast(unsigned int, v);
 }
-// d GELU / dz = s + 2 C z s (1 - s) (1 + 3 A z^2), s = (1 + tanh u)/2
+// d GELU / dz = s + 2 C z s (1 - s) (1 + 3 A z^2), s = (1 + tanh u)/2; the hardware
+// exponential and reciprocal (1 ulp each) are far below the BF16 rounding of the product
 __device__ __forceinline__ float gelu_grad(float z) {
     const float z2 = z * z;
-    const float s = 1.0f / (1.0f + exp2f(z * fmaf(GELU_K3, z2, GELU_K1)));
-    return s + 1.5957691216f * z * s * (1.0f - s) * fmaf(0.134145f, z2, 1.0f);
+    const float s = __builtin_amdgcn_rcpf(__builtin_amdgcn_exp2f(z * fmaf(GELU_K3, z2, GELU_K1)) + 1.0f);
+    return fmaf(1.5957691216f * z * s * (1.0f - s), fmaf(0.134145f, z2, 1.0f), s);
 }
 __device__ __forceinline__ float wave_sum(float v) {
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
@@ -82,47 +81,37 @@ struct Geo {
 };
 
 // per-series activation record (u16): h0 [T][2] hi terms, [T][2] lo terms (padded to 8) |
-// z1 h1 z2 h2 z3 h3 [T][32]; every slot starts on a 16-byte boundary
+// z1 h1 z2 h2 z3 h3, T*32 each; every slot starts on a 16-byte boundary.  A slot holds its
+// 32-frame tiles in the order the accumulators hold them, so that one 16-byte store or load
+// per lane and half tile moves contiguous memory: piece g of lane (frame j, half h) has
+// channels 8 (2g + e/4) + 4h + e%4, e = 0..7, at ((g nf + j) 2 + h) 8 of the tile, nf the
+// frames of the tile.
 __host__ __device__ inline int64_t h0_len(int T) { return ((int64_t)4 * T + 7) / 8 * 8; }
 __host__ __device__ inline int64_t act_stride(int T) { return h0_len(T) + (int64_t)6 * T * CH; }
 __host__ __device__ inline int64_t act_off(int which, int T) {   // 0:h0 1:z1 2:h1 3:z2 4:h2 5:z3 6:h3
     return which == 0 ? 0 : h0_len(T) + (int64_t)(which - 1) * T * CH;
 }
 
+__device__ __forceinline__ int64_t act_piece(int which, int T, int u, int g, int j, int h) {
+    return act_off(which, T) + u * 1024 + ((g * min(32, T - 32 * u) + j) * 2 + h) * 8;
+}
+
 // ---------------------------------------------------------------- fragment loads
+// A lane's 8 channels x 9 taps of a chunk pair are 72 consecutive weights (nine 16-byte
+// loads; OFF_W2, OFF_W3 and the row length are multiples of 8).
 __device__ void frag_fwd32(const uint16_t* wb, int base, int l, u16x8* fr) {
     const int o = l % 32, h = l / 32;
 #pragma unroll
-    for (int c = 0; c < K2C; ++c) {
-        const int k = c / 2, i0 = (c % 2) * 16 + 8 * h;
+    for (int b = 0; b < 2; ++b) {
+        const u16x8* src = reinterpret_cast<const u16x8*>(wb + base + o * 288 + (16 * b + 8 * h) * 9);
+        u16x8 row[KW];
 #pragma unroll
-        for (int q = 0; q < 8; ++q) fr[c][q] = wb[base + o * 288 + (i0 + q) * 9 + k];
+        for (int m = 0; m < KW; ++m) row[m] = src[m];
+#pragma unroll
+        for (int k = 0; k < KW; ++k)
+#pragma unroll
+            for (int q = 0; q < 8; ++q) fr[2 * k + b][q] = row[(q * 9 + k) / 8][(q * 9 + k) % 8];
     }
-}
-// dgrad: A[i][k'*32 + o] = W[o][i][8 - k']
-__device__ void frag_dgrad32(const uint16_t* wb, int base, int l, u16x8* fr) {
-    const int i = l % 32, h = l / 32;
-#pragma unroll
-    for (int c = 0; c < K2C; ++c) {
-        const int kp = c / 2, o0 = (c % 2) * 16 + 8 * h;
-#pragma unroll
-        for (int q = 0; q < 8; ++q) fr[c][q] = wb[base + (o0 + q) * 288 + i * 9 + (8 - kp)];
-    }
-}
-
-// one 32x32 output tile (channels x frames t0..t0+31) of a 32-channel image conv
-__device__ __forceinline__ floatx16 conv32(const unsigned short* img, int t0, const u16x8* fr, int l) {
-    const int j = l % 32, h = l / 32;
-    floatx16 acc;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
-#pragma unroll
-    for (int c = 0; c < K2C; ++c) {
-        const int k = c / 2, ch0 = (c % 2) * 16 + 8 * h;
-        const u16x8 b = *reinterpret_cast<const u16x8*>(img + (t0 + j + k) * CH + ch0);
-        acc = mfma(fr[c], b, acc);
-    }
-    return acc;
 }
 // 32x32 accumulator layout: lane l holds frame column l%32 and channel rows
 // 8*(r/4) + 4*(l/32) + r%4, r = 0..15 (four groups of four consecutive channels).
@@ -250,22 +239,28 @@ __device__ __forceinline__ floatx16 conv32b(const unsigned short* img, int t0, c
     return acc;
 }
 
-// GELU of one 32x32 output tile (this lane: frame t, channels 8q + 4h + p), rounded to
-// BF16 (zero for frames past the end: they are the next layer's padding).  With an
-// activation record, z and h of the layer are stored too.
+// GELU of one 32x32 output tile u (this lane: frame 32 u + j, channels 8q + 4h + p),
+// rounded to BF16 (zero for frames past the end: they are the next layer's padding).  With
+// an activation record, z and h of the layer are stored too.
 template <bool ACT>
-__device__ __forceinline__ void gelu_tile(const floatx16& acc, uint16_t* actv, int layer, int t, int T, int h,
+__device__ __forceinline__ void gelu_tile(const floatx16& acc, uint16_t* actv, int layer, int u, int T, int j, int h,
                                           uint2* hv) {
+    const bool live = 32 * u + j < T;
+    uint2 zv[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         const float z[4] = {acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
-        hv[q] = t < T ? make_uint2(f2bf2(gelu_fwd(z[0]), gelu_fwd(z[1])), f2bf2(gelu_fwd(z[2]), gelu_fwd(z[3])))
-                      : make_uint2(0u, 0u);
-        if (ACT && actv) {
-            const int o = 8 * q + 4 * h;
-            *reinterpret_cast<uint2*>(actv + act_off(2 * layer - 1, T) + t * CH + o) =
-                make_uint2(f2bf2(z[0], z[1]), f2bf2(z[2], z[3]));
-            *reinterpret_cast<uint2*>(actv + act_off(2 * layer, T) + t * CH + o) = hv[q];
+        hv[q] = live ? make_uint2(f2bf2(gelu_fwd(z[0]), gelu_fwd(z[1])), f2bf2(gelu_fwd(z[2]), gelu_fwd(z[3])))
+                     : make_uint2(0u, 0u);
+        if (ACT) zv[q] = make_uint2(f2bf2(z[0], z[1]), f2bf2(z[2], z[3]));
+    }
+    if (ACT && live) {
+#pragma unroll
+        for (int g = 0; g < 2; ++g) {
+            *reinterpret_cast<uint4*>(actv + act_piece(2 * layer - 1, T, u, g, j, h)) =
+                make_uint4(zv[2 * g].x, zv[2 * g].y, zv[2 * g + 1].x, zv[2 * g + 1].y);
+            *reinterpret_cast<uint4*>(actv + act_piece(2 * layer, T, u, g, j, h)) =
+                make_uint4(hv[2 * g].x, hv[2 * g].y, hv[2 * g + 1].x, hv[2 * g + 1].y);
         }
     }
 }
@@ -376,7 +371,7 @@ __global__ void __launch_bounds__(64, 2) lcf_fwd_kernel(const FwdArgs a) {
             const floatx16 acc = conv32b(img, 0, f3, fb3, l);
             const int t = 32 * u + j;
             uint2 hv[4];
-            gelu_tile<ACT>(acc, t < g.T ? actv : nullptr, 3, t, g.T, h, hv);
+            gelu_tile<ACT>(acc, actv, 3, u, g.T, j, h, hv);
             floatx16 yo;
 #pragma unroll
             for (int i = 0; i < 16; ++i) yo[i] = 0.0f;
@@ -395,9 +390,8 @@ __global__ void __launch_bounds__(64, 2) lcf_fwd_kernel(const FwdArgs a) {
             for (int s = 0; s < g.TT + 2; ++s) {
                 if (s < g.TT) {   // layer 1, tile s
                     const floatx16 acc = conv2(h0, hl, 32 * s, f1, l);
-                    const int t = 32 * s + j;
                     uint2 hv[4];
-                    gelu_tile<ACT>(acc, t < g.T ? actv : nullptr, 1, t, g.T, h, hv);
+                    gelu_tile<ACT>(acc, actv, 1, s, g.T, j, h, hv);
                     ring_store(ra, s, j, h, hv);
                 } else if (s == g.TT) {
                     ring_clear(ra, last * SLOT + 36, l);   // after the last tile
@@ -405,9 +399,8 @@ __global__ void __launch_bounds__(64, 2) lcf_fwd_kernel(const FwdArgs a) {
                 if (s >= 1 && s <= g.TT) {   // layer 2, tile s - 1
                     const int u = s - 1;
                     const floatx16 acc = conv32b(ra + (u % 3) * SLOT * RS, 0, f2, fb2, l);
-                    const int t = 32 * u + j;
                     uint2 hv[4];
-                    gelu_tile<ACT>(acc, t < g.T ? actv : nullptr, 2, t, g.T, h, hv);
+                    gelu_tile<ACT>(acc, actv, 2, u, g.T, j, h, hv);
                     ring_store(rb, u, j, h, hv);
                 } else if (s == g.TT + 1) {
                     ring_clear(rb, last * SLOT + 36, l);
@@ -423,7 +416,7 @@ __global__ void __launch_bounds__(64, 2) lcf_fwd_kernel(const FwdArgs a) {
                 const floatx16 acc = conv2(h0, hl, 32 * tt, f1, l);
                 const int t = 32 * tt + j;
                 uint2 hv[4];
-                gelu_tile<ACT>(acc, t < g.T ? actv : nullptr, 1, t, g.T, h, hv);
+                gelu_tile<ACT>(acc, actv, 1, tt, g.T, j, h, hv);
 #pragma unroll
                 for (int q = 0; q < 4; ++q) *reinterpret_cast<uint2*>(hb + (t + PADT) * RS + 8 * q + 4 * h) = hv[q];
             }
@@ -436,8 +429,7 @@ __global__ void __launch_bounds__(64, 2) lcf_fwd_kernel(const FwdArgs a) {
                     for (int q = 0; q < 4; ++q)
                         *reinterpret_cast<uint2*>(hb + (32 * tt - 32 + j + PADT) * RS + 8 * q + 4 * h) = pend[q];
                 }
-                const int t = 32 * tt + j;
-                gelu_tile<ACT>(acc, t < g.T ? actv : nullptr, 2, t, g.T, h, pend);
+                gelu_tile<ACT>(acc, actv, 2, tt, g.T, j, h, pend);
             }
 #pragma unroll
             for (int q = 0; q < 4; ++q)
@@ -451,283 +443,413 @@ __global__ void __launch_bounds__(64, 2) lcf_fwd_kernel(const FwdArgs a) {
     }
 }
 
-// ---------------------------------------------------------------- backward, per series
+// ---------------------------------------------------------------- backward
 struct BwdArgs {
     const float* w;
     const uint16_t* wb;
     const float2* x;      // [T][N]
     const float2* tgt;    // [T][N]
     uint16_t* act;
-    float* part4;         // [NWB][PART4]: dW4 (64), db4 (2), loss sum (1)
+    float* part;          // [workgroups][PART]: gradient in parameter order, loss sum
     int64_t N;
     int T;
     float eps;
     float inv_count;      // 1 / (N * 2 * T)
 };
 
-// Output-layer gradient, then dz of layers 3, 2, 1 through the transposed convs.
-// Each dz overwrites the pre-activation z of its layer in the activation record
-// (z is read for GELU' by the same lane immediately before).
-__global__ void __launch_bounds__(64) lcf_bwd_series_kernel(const BwdArgs a) {
-    extern __shared__ float4 smem4[];
-    const Geo g(a.T);
-    const int l = threadIdx.x, h = l / 32, j = l % 32;
-    float* par = reinterpret_cast<float*>(smem4);      // w4 (64) b4 (2) pad -> 68
-    float2* xs = reinterpret_cast<float2*>(par + 68);  // [T]
-    float2* ts = xs + g.T;                              // [T]
-    unsigned short* d3 = reinterpret_cast<unsigned short*>(ts + g.T);   // [TP][32]
-    unsigned short* d2 = d3 + g.TP * CH;                                 // [TP][32]
+// Two kernels, one per 32->32 layer L: dz_L comes in, dW_L and the dz of the layer below go
+// out.  L = 3 forms dz3 from the output layer and the target, adds dW4 and stores dz2 over z2;
+// L = 2 reads it back and adds dW1.  One wavefront takes a series through a kernel, streaming
+// 32-frame tiles: step s puts tile s of dz_L into a ring of three slots (as the forward pass
+// streams its layers) and works on tile s-1, whose neighbours are then there.
+//
+//  * The gradient of layer L takes 9 taps x 16 registers and stays in registers for all the
+//    series of a wavefront (one wavefront per SIMD; both layers at once would need more
+//    accumulators than the 256 there are); the dgrad weight fragments, the same for all
+//    four wavefronts, are read from LDS.
+//  * wgrad's K dimension is time.  dz is read from its time-major slot by transposing LDS
+//    reads, 16 frames per lane once; the 9 taps are 9 shifts of them in registers.
+//  * One more accumulator tile collects what is left, by column: 0..17 dW1 (tap 2k + i; the
+//    input rows overlap, so the read needs no copy per tap), 18..20 db1..db3 (ones), 21..26
+//    dW4 (rows = channels; dL/dy as three BF16 terms per output).
+//  * dL/dy enters the products exactly (three BF16 terms), like the biases of the forward pass.
+//
+// Bound by the VALU (GELU' of 96 values a frame) and the matrix products, with one wavefront
+// per SIMD to issue both.  4096 series x 200 frames: 235 us for the two kernels, where one
+// for the dz (256 wavefronts, weights in registers) and three for the weight gradients took
+// 1262 us.
+constexpr int BWD_WAVES = 4;
+constexpr int BSLOT = 48;                  // ring slot rows (40 used; 48 keeps the chunk rotation in phase)
+constexpr int BRING = 3 * BSLOT * 64;      // bytes
+constexpr int BTILE = 32 * 64;
+constexpr int BG = 6 * 64;                 // dL/dy terms [6][32]
+constexpr int BH0 = 192;                   // one copy of an input window (48 rows)
+constexpr int BWD_WAVE = BRING + 2 * BTILE + 4 * BH0;   // the terms of dL/dy share the second tile
+constexpr int BWD_FRAG = K2C * 64 * 16;
+constexpr int BWD_PART = OFF_W3;           // parameters of a kernel, at most
+constexpr size_t BWD_LDS = std::max<size_t>(BWD_FRAG + BWD_WAVES * BWD_WAVE, 2 * BWD_PART * sizeof(float));
+static_assert(BWD_LDS <= 160 * 1024 && PART - OFF_W3 <= BWD_PART && BG <= BTILE, "LDS of a compute unit");
 
-    u16x8 fd3[K2C], fd2[K2C];
-    frag_dgrad32(a.wb, OFF_W3, l, fd3);
-    frag_dgrad32(a.wb, OFF_W2, l, fd2);
-    for (int i = l; i < 68; i += 64) par[i] = i < 64 ? bf2f(a.wb[OFF_W4 + i]) : (i < 66 ? a.w[OFF_B4 + i - 64] : 0.f);
-    for (int i = l; i < 2 * g.TP * CH; i += 64) d3[i] = 0;
-    __builtin_amdgcn_wave_barrier();
+// byte of 16-byte chunk c (8 channels) of a row of 32 channels: chunks are rotated by the
+// row group so that 16 consecutive rows' chunks fall in distinct banks
+__device__ __forceinline__ int chunk_at(int row, int c) { return row * 64 + ((c ^ ((row >> 2) & 3)) << 4); }
 
-    float dw4[2 * CH];
-#pragma unroll
-    for (int i = 0; i < 2 * CH; ++i) dw4[i] = 0.0f;
-    float db40 = 0.0f, db41 = 0.0f, lossacc = 0.0f;
-
-    for (int64_t v = blockIdx.x; v < a.N; v += gridDim.x) {
-        for (int t = l; t < g.T; t += 64) {
-            xs[t] = a.x[(int64_t)t * a.N + v];
-            ts[t] = a.tgt[(int64_t)t * a.N + v];
-        }
-        __builtin_amdgcn_wave_barrier();
-        float ss = 0.0f;
-        for (int t = l; t < g.T; t += 64) ss += xs[t].x * xs[t].x + xs[t].y * xs[t].y;
-        const float ir = 1.0f / sqrtf(wave_sum(ss) / (float)g.T + a.eps);
-        uint16_t* av = a.act + v * act_stride(g.T);
-        // output layer and dz3: one frame per lane
-        for (int t = l; t < g.T; t += 64) {
-            unsigned short* h3 = av + act_off(6, g.T) + t * CH;
-            unsigned short* z3 = av + act_off(5, g.T) + t * CH;
-            float hv[CH];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const u16x8 hh = *reinterpret_cast<const u16x8*>(h3 + 8 * q);
-#pragma unroll
-                for (int p = 0; p < 8; ++p) hv[8 * q + p] = bf2f(hh[p]);
-            }
-            float y0 = par[64], y1 = par[65];
-#pragma unroll
-            for (int o = 0; o < CH; ++o) {
-                y0 = fmaf(par[o], hv[o], y0);
-                y1 = fmaf(par[32 + o], hv[o], y1);
-            }
-            const float e0 = y0 - ts[t].x * ir, e1 = y1 - ts[t].y * ir;
-            lossacc += e0 * e0 + e1 * e1;
-            const float g0 = 2.0f * e0 * a.inv_count, g1 = 2.0f * e1 * a.inv_count;
-            db40 += g0;
-            db41 += g1;
-#pragma unroll
-            for (int o = 0; o < CH; ++o) {
-                dw4[o] = fmaf(g0, hv[o], dw4[o]);
-                dw4[CH + o] = fmaf(g1, hv[o], dw4[CH + o]);
-            }
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const u16x8 zz = *reinterpret_cast<const u16x8*>(z3 + 8 * q);
-                u16x8 ob;
-#pragma unroll
-                for (int p = 0; p < 8; ++p) {
-                    const int o = 8 * q + p;
-                    const float dh = par[o] * g0 + par[32 + o] * g1;
-                    ob[p] = f2bf(dh * gelu_grad(bf2f(zz[p])));
-                }
-                *reinterpret_cast<u16x8*>(d3 + (t + PADT) * CH + 8 * q) = ob;
-                *reinterpret_cast<u16x8*>(z3 + 8 * q) = ob;          // dz3 replaces z3
-            }
-        }
-        __builtin_amdgcn_wave_barrier();
-        // dgrad through layer 3: dz2 = conv(dz3; W3 transposed, flipped) * GELU'(z2)
-        for (int tt = 0; tt < g.TT; ++tt) {
-            const floatx16 acc = conv32(d3, 32 * tt, fd3, l);
-            const int t = 32 * tt + j;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int i = 8 * q + 4 * h;
-                u16x4 ob = {0, 0, 0, 0};
-                if (t < g.T) {
-                    u16x4* zp = reinterpret_cast<u16x4*>(av + act_off(3, g.T) + t * CH + i);
-                    const u16x4 z = *zp;
-#pragma unroll
-                    for (int p = 0; p < 4; ++p) ob[p] = f2bf(acc[4 * q + p] * gelu_grad(bf2f(z[p])));
-                    *zp = ob;                                         // dz2 replaces z2
-                }
-                *reinterpret_cast<u16x4*>(d2 + (t + PADT) * CH + i) = ob;
-            }
-        }
-        __builtin_amdgcn_wave_barrier();
-        // dgrad through layer 2: dz1 = conv(dz2; W2 transposed, flipped) * GELU'(z1)
-        for (int tt = 0; tt < g.TT; ++tt) {
-            const floatx16 acc = conv32(d2, 32 * tt, fd2, l);
-            const int t = 32 * tt + j;
-            if (t < g.T) {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int i = 8 * q + 4 * h;
-                    u16x4* zp = reinterpret_cast<u16x4*>(av + act_off(1, g.T) + t * CH + i);
-                    const u16x4 z = *zp;
-                    u16x4 ob;
-#pragma unroll
-                    for (int p = 0; p < 4; ++p) ob[p] = f2bf(acc[4 * q + p] * gelu_grad(bf2f(z[p])));
-                    *zp = ob;                                         // dz1 replaces z1
-                }
-            }
-        }
-        __builtin_amdgcn_wave_barrier();
-    }
-    // wave reduction of the output-layer partials
-    float* out = a.part4 + (int64_t)blockIdx.x * PART4;
-#pragma unroll
-    for (int i = 0; i < 2 * CH; ++i) {
-        const float s = wave_sum(dw4[i]);
-        if (l == 0) out[i] = s;
-    }
-    db40 = wave_sum(db40);
-    db41 = wave_sum(db41);
-    lossacc = wave_sum(lossacc);
-    if (l == 0) {
-        out[64] = db40;
-        out[65] = db41;
-        out[66] = lossacc;
-    }
+// Transposing read: lane i of each 16 lanes supplies 4 columns of row i / 4 and receives the
+// 4 rows of column i.
+__device__ __forceinline__ uint2 tr_read(const char* p) {
+    typedef short s16x4 __attribute__((ext_vector_type(4)));
+    typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+    return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)p));
+}
+__device__ __forceinline__ u16x8 frag4(unsigned int a, unsigned int b, unsigned int c, unsigned int d) {
+    return __builtin_bit_cast(u16x8, make_uint4(a, b, c, d));
 }
 
-// ---------------------------------------------------------------- weight gradients
-struct WgArgs {
-    const uint16_t* act;
-    float* part;          // [NWB][PART] (layers 2, 3) or [NWB][PART1] (layer 1)
-    int64_t N;
-    int T;
-    int layer;            // 1, 2 or 3
-};
-
-// dW[o][i][k] = sum_series sum_t dz[t][o] h_prev[t + k - 4][i], db[o] = sum dz[t][o]:
-// a GEMM over K = time.  A[o][t] = dz (gathered from the time-major record), B[t][n] =
-// h_prev shifted by the tap k of column block n.  Each wave accumulates over its series.
-template <int LAYER>
-__global__ void __launch_bounds__(64) lcf_wgrad_kernel(const WgArgs a) {
+template <int LAYER, int XR>
+__global__ void __launch_bounds__(64 * BWD_WAVES, 1) lcf_bwd_kernel(const BwdArgs a) {
     extern __shared__ float4 smem4[];
-    const Geo g(a.T);
-    const int T16 = (a.T + 15) / 16 * 16;
-    constexpr int HC = LAYER == 1 ? 2 : CH;            // channels of h_prev
-    constexpr int NTILE = LAYER == 1 ? 1 : KW;
-    const int l = threadIdx.x, h = l / 32, n = l % 32;
-    unsigned short* dz = reinterpret_cast<unsigned short*>(smem4);   // [T16][32]
-    unsigned short* hp = dz + T16 * CH;                              // [TP][HC]
-    unsigned short* hq = hp + g.TP * HC;                             // layer 1: lo terms [TP][2]
-    for (int i = l; i < T16 * CH + g.TP * HC * (LAYER == 1 ? 2 : 1); i += 64) dz[i] = 0;
-    __builtin_amdgcn_wave_barrier();
-    const int zslot = 2 * LAYER - 1;                          // dz_L sits in z_L's slot
-    const int hslot = LAYER == 1 ? 0 : 2 * (LAYER - 1);       // h_{L-1}
+    char* sm = reinterpret_cast<char*>(smem4);
+    const int T = a.T, TT = (T + 31) / 32;
+    const int l = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int h = l / 32, j = l % 32;
 
-    floatx16 acc[NTILE];
+    // dgrad fragments: A[i][k'*32 + o] = W[o][i][8 - k']
+    constexpr int OFF_W = LAYER == 3 ? OFF_W3 : OFF_W2;
+    u16x8* frag = reinterpret_cast<u16x8*>(sm);
+    for (int it = threadIdx.x; it < K2C * 64; it += 64 * BWD_WAVES) {
+        const int c = it / 64, i = it % 32, o0 = (c % 2) * 16 + 8 * ((it / 32) % 2);
+        u16x8 f;
 #pragma unroll
-    for (int k = 0; k < NTILE; ++k)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[k][r] = 0.0f;
-    float dbacc = 0.0f;
-
-    for (int64_t v = blockIdx.x; v < a.N; v += gridDim.x) {
-        const uint16_t* av = a.act + v * act_stride(g.T);
-        for (int t = l; t < g.T; t += 64) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                *reinterpret_cast<u16x8*>(dz + t * CH + 8 * q) =
-                    *reinterpret_cast<const u16x8*>(av + act_off(zslot, g.T) + t * CH + 8 * q);
-            if (LAYER == 1) {
-                hp[(t + PADT) * 2] = av[act_off(0, g.T) + 2 * t];
-                hp[(t + PADT) * 2 + 1] = av[act_off(0, g.T) + 2 * t + 1];
-                hq[(t + PADT) * 2] = av[act_off(0, g.T) + 2 * g.T + 2 * t];
-                hq[(t + PADT) * 2 + 1] = av[act_off(0, g.T) + 2 * g.T + 2 * t + 1];
-            } else {
-#pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    *reinterpret_cast<u16x8*>(hp + (t + PADT) * CH + 8 * q) =
-                        *reinterpret_cast<const u16x8*>(av + act_off(hslot, g.T) + t * CH + 8 * q);
-            }
-        }
-        __builtin_amdgcn_wave_barrier();
-        for (int t0 = 0; t0 < T16; t0 += 16) {
-            u16x8 A;
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                A[q] = dz[(t0 + 8 * h + q) * CH + n];
-                dbacc += bf2f(A[q]);
-            }
-#pragma unroll
-            for (int k = 0; k < NTILE; ++k) {
-                u16x8 B;
-                if (LAYER == 1) {   // dz (hi + lo): the hi product here, the lo one below
-                    const int kk = min(n / 2, KW - 1), ii = n % 2;
-                    u16x8 Bl;
-#pragma unroll
-                    for (int q = 0; q < 8; ++q) {
-                        B[q] = n < 18 ? hp[(t0 + 8 * h + q + kk) * 2 + ii] : (unsigned short)0;
-                        Bl[q] = n < 18 ? hq[(t0 + 8 * h + q + kk) * 2 + ii] : (unsigned short)0;
-                    }
-                    acc[k] = mfma(A, Bl, acc[k]);
-                } else {
-#pragma unroll
-                    for (int q = 0; q < 8; ++q) B[q] = hp[(t0 + 8 * h + q + k) * CH + n];
-                }
-                acc[k] = mfma(A, B, acc[k]);
-            }
-        }
-        __builtin_amdgcn_wave_barrier();
+        for (int q = 0; q < 8; ++q) f[q] = a.wb[OFF_W + (o0 + q) * 288 + i * 9 + (8 - c / 2)];
+        frag[it] = f;
     }
-    const int stride = LAYER == 1 ? PART1 : PART;
-    float* out = a.part + (int64_t)blockIdx.x * stride;
+    __syncthreads();
+    const u16x8* fr = frag + l;
+    char* ring = sm + BWD_FRAG + wv * BWD_WAVE;   // dz of this layer
+    char* ht = ring + BRING;                      // h tile
+    char* d1 = ht + BTILE;                        // L = 2: dz1 tile
+    char* gst = d1;                               // L = 3: dL/dy terms
+    char* h0 = d1 + BTILE;                        // input window: hi, hi one row on, lo, lo one row on
+
+    // output layer: y = W4 h3 (rows 0, 1) and W4^T against the terms of dL/dy
+    u16x8 f4[2], f4t;
+    frag_out(a.wb, l, f4);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) f4t[e] = h == 0 && e < 6 ? a.wb[OFF_W4 + (e % 2) * CH + j] : (unsigned short)0;
+    const float b40 = a.w[OFF_B4], b41 = a.w[OFF_B4 + 1];
+
+    // lane offsets: conv rows j + k (chunk h; chunk 2 + h is 32 bytes off by xor), transposing
+    // reads of rows 8h + 4m + 0..3, the same of the input window
+    int co[KW], tro[4], tr0[2];
+#pragma unroll
+    for (int k = 0; k < KW; ++k) co[k] = chunk_at(j + k, h);
+    const int i16 = l % 16, g2 = (l / 16) % 2;
+#pragma unroll
+    for (int m = 0; m < 4; ++m) tro[m] = chunk_at(8 * h + 4 * m + i16 / 4, 2 * g2 + (i16 % 4) / 2) + 8 * (i16 % 2);
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+        const int t = 8 * h + 4 * m + i16 / 4;
+        tr0[m] = (t & 1) * BH0 + 4 * (t & ~1) + 8 * (i16 % 4 + 4 * g2);
+    }
+
+    floatx16 accw[KW], accm;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-        const int o = acc_row(r, l);
-        if (LAYER == 1) {
-            if (n < 18) out[o * 18 + (n % 2) * 9 + n / 2] = acc[0][r];
-        } else {
+        accm[r] = 0.0f;
 #pragma unroll
-            for (int k = 0; k < NTILE; ++k) out[o * 288 + n * 9 + k] = acc[k][r];
+        for (int k = 0; k < KW; ++k) accw[k][r] = 0.0f;
+    }
+    float db40 = 0.0f, db41 = 0.0f, lossacc = 0.0f;
+
+    auto conv = [&](const char* slot) {
+        floatx16 acc;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
+#pragma unroll
+        for (int c = 0; c < K2C; ++c)
+            acc = mfma(fr[c * 64], *reinterpret_cast<const u16x8*>(slot + (co[c / 2] ^ (32 * (c % 2)))), acc);
+        return acc;
+    };
+    // gradient of the 9 taps from a dz slot (rows 32u-4 .. 32u+35) and the h tile in ht; db in
+    // column `col` of accm
+    auto wgrad = [&](const char* slot, int col) {
+        const unsigned int one = j == col ? BF_ONE2 : 0u;
+#pragma unroll
+        for (int t0 = 0; t0 < 32; t0 += 16) {
+            unsigned int e[8], o[7];   // frames 2d, 2d + 1 and 2d + 1, 2d + 2 of this lane's 16
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                const uint2 v = tr_read(slot + t0 * 64 + tro[m]);
+                e[2 * m] = v.x;
+                e[2 * m + 1] = v.y;
+            }
+            const uint2 b0 = tr_read(ht + t0 * 64 + tro[0]), b1 = tr_read(ht + t0 * 64 + tro[1]);
+            const u16x8 B = frag4(b0.x, b0.y, b1.x, b1.y);
+#pragma unroll
+            for (int d = 0; d < 7; ++d) o[d] = __builtin_amdgcn_alignbit(e[d + 1], e[d], 16);
+#pragma unroll
+            for (int k = 0; k < KW; ++k) {   // dz[t' + 4 - k]: 8 - k frames into the window
+                const int m = (8 - k) / 2;
+                const u16x8 A = k % 2 ? frag4(o[m], o[m + 1], o[m + 2], o[m + 3]) : frag4(e[m], e[m + 1], e[m + 2], e[m + 3]);
+                accw[k] = mfma(A, B, accw[k]);
+            }
+            accm = mfma(frag4(e[2], e[3], e[4], e[5]), frag4(one, one, one, one), accm);
+        }
+    };
+    // dz = dh GELU'(z) of tile u, BF16, zero past the end
+    auto dz_tile = [&](const floatx16& dh, const uint4& za, const uint4& zb, bool live, uint2* out) {
+        const unsigned int z[8] = {za.x, za.y, za.z, za.w, zb.x, zb.y, zb.z, zb.w};
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            unsigned int v[2];
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+                const unsigned int zz = z[2 * q + p];
+                v[p] = f2bf2(dh[4 * q + 2 * p] * gelu_grad(__uint_as_float(zz << 16)),
+                             dh[4 * q + 2 * p + 1] * gelu_grad(__uint_as_float(zz & 0xffff0000u)));
+            }
+            out[q] = live ? make_uint2(v[0], v[1]) : make_uint2(0u, 0u);
+        }
+    };
+    auto row_store = [&](char* base, int row, const uint2* v) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) *reinterpret_cast<uint2*>(base + chunk_at(row, q) + 8 * h) = v[q];
+    };
+    auto dz_store = [&](int s, const uint2* v) {
+        row_store(ring + (s % 3) * BSLOT * 64, 4 + j, v);
+        if (j < 4) row_store(ring + ((s + 2) % 3) * BSLOT * 64, 36 + j, v);
+        else if (j >= 28) row_store(ring + ((s + 1) % 3) * BSLOT * 64, j - 28, v);
+    };
+    auto halo_clear = [&](char* rows) {   // 4 rows
+        *reinterpret_cast<unsigned int*>(rows + 4 * l) = 0u;
+    };
+    auto h_store = [&](const uint4& pa, const uint4& pb) {
+        const uint2 v[4] = {make_uint2(pa.x, pa.y), make_uint2(pa.z, pa.w), make_uint2(pb.x, pb.y), make_uint2(pb.z, pb.w)};
+        row_store(ht, j, v);
+    };
+
+    const int64_t stride = (int64_t)gridDim.x * BWD_WAVES;
+    for (int64_t v = (int64_t)blockIdx.x * BWD_WAVES + wv; v < a.N; v += stride) {
+        uint16_t* av = a.act + v * act_stride(T);
+        // record pieces, loaded one step before they are used
+        auto load = [&](int which, int u, uint4& pa, uint4& pb) {
+            pa = pb = make_uint4(0u, 0u, 0u, 0u);
+            if (u < TT && 32 * u + j < T) {
+                pa = *reinterpret_cast<const uint4*>(av + act_piece(which, T, u, 0, j, h));
+                pb = *reinterpret_cast<const uint4*>(av + act_piece(which, T, u, 1, j, h));
+            }
+        };
+        auto load_tgt = [&](int u) {
+            const int t = 32 * u + j;
+            return h == 0 && u < TT && t < T ? a.tgt[(int64_t)t * a.N + v] : make_float2(0.0f, 0.0f);
+        };
+        auto load_in = [&](int u, unsigned int& hi, unsigned int& lo) {
+            const int t = 32 * u - PADT + l;
+            hi = lo = 0u;
+            if (l < 40 && u < TT && t >= 0 && t < T) {
+                hi = *reinterpret_cast<const unsigned int*>(av + 2 * t);
+                lo = *reinterpret_cast<const unsigned int*>(av + 2 * T + 2 * t);
+            }
+        };
+        uint4 za, zb, ha, hb;        // z and h of the layer below
+        uint4 za3, zb3, ha3, hb3;    // L = 3: z3 and h3
+        uint4 da, db;                // L = 2: dz2
+        unsigned int xhi = 0u, xlo = 0u;
+        float2 tg = make_float2(0.0f, 0.0f);
+        float ir = 0.0f;
+        load(LAYER == 3 ? 3 : 1, 0, za, zb);
+        load(LAYER == 3 ? 4 : 2, 0, ha, hb);
+        if (LAYER == 3) {
+            tg = load_tgt(0);
+            load(5, 0, za3, zb3);
+            load(6, 0, ha3, hb3);
+            float ss = 0.0f;
+#pragma unroll
+            for (int q = 0; q < XR; ++q) {
+                const int t = l + 64 * q;
+                const float2 xv = t < T ? a.x[(int64_t)t * a.N + v] : make_float2(0.0f, 0.0f);
+                ss += xv.x * xv.x + xv.y * xv.y;
+            }
+            ir = 1.0f / sqrtf(wave_sum(ss) / (float)T + a.eps);
+        } else {
+            load(3, 0, da, db);
+            load_in(0, xhi, xlo);
+        }
+        halo_clear(ring);   // before tile 0
+        __builtin_amdgcn_wave_barrier();
+
+        for (int s = 0; s <= TT; ++s) {
+            if (s == TT) {
+                halo_clear(ring + ((TT - 1) % 3) * BSLOT * 64 + 36 * 64);   // after the last tile
+                __builtin_amdgcn_wave_barrier();
+            } else if (LAYER == 2) {   // dz2, tile s
+                const uint2 dz[4] = {make_uint2(da.x, da.y), make_uint2(da.z, da.w), make_uint2(db.x, db.y),
+                                     make_uint2(db.z, db.w)};
+                dz_store(s, dz);
+                load(3, s + 1, da, db);
+                __builtin_amdgcn_wave_barrier();
+            } else {   // output layer and dz3, tile s
+                const bool live = 32 * s + j < T;
+                floatx16 yo;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) yo[r] = 0.0f;
+                const floatx16 zero = yo;
+                yo = mfma(f4[0], __builtin_bit_cast(u16x8, ha3), yo);
+                yo = mfma(f4[1], __builtin_bit_cast(u16x8, hb3), yo);
+                h_store(ha3, hb3);
+                float g0 = 0.0f, g1 = 0.0f;
+                if (h == 0 && live) {   // rows 0 and 1 of column j
+                    const float e0 = yo[0] + b40 - tg.x * ir, e1 = yo[1] + b41 - tg.y * ir;
+                    lossacc += e0 * e0 + e1 * e1;
+                    g0 = 2.0f * e0 * a.inv_count;
+                    g1 = 2.0f * e1 * a.inv_count;
+                    db40 += g0;
+                    db41 += g1;
+                }
+                unsigned short t0[3], t1[3];
+                split3(g0, t0);
+                split3(g1, t1);
+                unsigned int gp[3];
+#pragma unroll
+                for (int m = 0; m < 3; ++m) {
+                    gp[m] = t0[m] | ((unsigned int)t1[m] << 16);
+                    if (h == 0) {
+                        reinterpret_cast<unsigned short*>(gst)[(2 * m) * 32 + j] = t0[m];
+                        reinterpret_cast<unsigned short*>(gst)[(2 * m + 1) * 32 + j] = t1[m];
+                    }
+                }
+                const floatx16 dh = mfma(f4t, frag4(gp[0], gp[1], gp[2], 0u), zero);
+                uint2 dz[4];
+                dz_tile(dh, za3, zb3, live, dz);
+                tg = load_tgt(s + 1);
+                load(5, s + 1, za3, zb3);
+                load(6, s + 1, ha3, hb3);
+                dz_store(s, dz);
+                __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                for (int k0 = 0; k0 < 32; k0 += 16) {   // dW4
+                    const uint2 a0 = tr_read(ht + k0 * 64 + tro[0]), a1 = tr_read(ht + k0 * 64 + tro[1]);
+                    const bool in = j >= 21 && j < 27;
+                    const uint4 b = *reinterpret_cast<const uint4*>(gst + (in ? (j - 21) * 64 : 0) + (k0 + 8 * h) * 2);
+                    accm = mfma(frag4(a0.x, a0.y, a1.x, a1.y),
+                                frag4(in ? b.x : 0u, in ? b.y : 0u, in ? b.z : 0u, in ? b.w : 0u), accm);
+                }
+                __builtin_amdgcn_wave_barrier();
+            }
+            if (s == 0) continue;
+            // dW of this layer and dz of the one below, tile u
+            const int u = s - 1;
+            const char* slot = ring + (u % 3) * BSLOT * 64;
+            h_store(ha, hb);
+            if (LAYER == 2 && l < 48) {
+                unsigned int* hw = reinterpret_cast<unsigned int*>(h0);
+                hw[l] = xhi;
+                hw[2 * BH0 / 4 + l] = xlo;
+                if (l > 0) {
+                    hw[BH0 / 4 + l - 1] = xhi;
+                    hw[3 * BH0 / 4 + l - 1] = xlo;
+                }
+            }
+            __builtin_amdgcn_wave_barrier();
+            const floatx16 dh = conv(slot);
+            wgrad(slot, LAYER == 3 ? 20 : 19);
+            uint2 dz[4];
+            const bool live = 32 * u + j < T;
+            dz_tile(dh, za, zb, live, dz);
+            load(LAYER == 3 ? 3 : 1, s, za, zb);
+            load(LAYER == 3 ? 4 : 2, s, ha, hb);
+            if (LAYER == 3) {   // dz2 replaces z2
+                if (live) {
+#pragma unroll
+                    for (int g = 0; g < 2; ++g)
+                        *reinterpret_cast<uint4*>(av + act_piece(3, T, u, g, j, h)) =
+                            make_uint4(dz[2 * g].x, dz[2 * g].y, dz[2 * g + 1].x, dz[2 * g + 1].y);
+                }
+                __builtin_amdgcn_wave_barrier();
+                continue;
+            }
+            load_in(s, xhi, xlo);
+            row_store(d1, j, dz);
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int k0 = 0; k0 < 32; k0 += 16) {
+                const uint2 a0 = tr_read(d1 + k0 * 64 + tro[0]), a1 = tr_read(d1 + k0 * 64 + tro[1]);
+                const u16x8 A = frag4(a0.x, a0.y, a1.x, a1.y);
+#pragma unroll
+                for (int p = 0; p < 2; ++p) {   // hi terms, with the ones of db1; lo terms
+                    const uint2 b0 = tr_read(h0 + 2 * p * BH0 + k0 * 4 + tr0[0]);
+                    const uint2 b1 = tr_read(h0 + 2 * p * BH0 + k0 * 4 + tr0[1]);
+                    const unsigned int one = p == 0 && j == 18 ? BF_ONE2 : 0u;
+                    const bool in = j < 18;
+                    accm = mfma(A, frag4(in ? b0.x : one, in ? b0.y : one, in ? b1.x : one, in ? b1.y : one), accm);
+                }
+            }
+            __builtin_amdgcn_wave_barrier();
         }
     }
-    dbacc += __shfl_xor(dbacc, 32);
-    if (h == 0) out[(LAYER == 1 ? 576 : 9216) + n] = dbacc;
+
+    // sum over the wavefronts in LDS, in a fixed order: waves 0, 1 store, 2, 3 add
+    constexpr int FIRST = LAYER == 3 ? OFF_W3 : 0, LAST = LAYER == 3 ? PART : OFF_W3;
+    __syncthreads();
+    float* reg = reinterpret_cast<float*>(smem4) + (wv & 1) * BWD_PART - FIRST;
+    if (LAYER == 3) {
+        db40 = wave_sum(db40);
+        db41 = wave_sum(db41);
+        lossacc = wave_sum(lossacc);
+    }
+    auto put = [&](bool add) {
+        auto one = [&](int idx, float x) { reg[idx] = add ? reg[idx] + x : x; };
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int o = acc_row(r, l);
+#pragma unroll
+            for (int k = 0; k < KW; ++k) one(OFF_W + o * 288 + j * 9 + k, accw[k][r]);
+            const float x = accm[r];
+            if (LAYER == 3) {
+                const float x3 = x + __shfl_down(x, 2) + __shfl_down(x, 4);   // the three terms of dW4
+                if (j == 20) one(OFF_B3 + o, x);
+                else if (j == 21 || j == 22) one(OFF_W4 + (j - 21) * CH + o, x3);
+            } else {
+                if (j < 18) one(OFF_W1 + o * 18 + (j % 2) * 9 + j / 2, x);
+                else if (j == 18) one(OFF_B1 + o, x);
+                else if (j == 19) one(OFF_B2 + o, x);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (LAYER == 3 && l == 0) {
+            one(OFF_B4, db40);
+            one(OFF_B4 + 1, db41);
+            one(NPAR, lossacc);
+        }
+    };
+    for (int turn = 0; turn < 2; ++turn) {
+        if (wv / 2 == turn) put(turn == 1);
+        __syncthreads();
+    }
+    const float* sum = reinterpret_cast<const float*>(smem4);
+    for (int p = threadIdx.x; p < LAST - FIRST; p += 64 * BWD_WAVES)
+        a.part[(int64_t)blockIdx.x * PART + FIRST + p] = sum[p] + sum[BWD_PART + p];
 }
 
-struct RedArgs {
-    const float* p1;   // [NWB][PART1]
-    const float* p2;   // [NWB][PART]
-    const float* p3;   // [NWB][PART]
-    const float* p4;   // [NWB][PART4]
-    float* grad;
-    float* loss;
-    float inv_count;
-};
-
-// deterministic sum of the per-wave partials into the parameter-vector layout
-__global__ void lcf_reduce_kernel(const RedArgs a) {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p > NPAR) return;
-    if (p == NPAR) {
-        float s = 0.0f;
-        for (int w = 0; w < NWB; ++w) s += a.p4[(int64_t)w * PART4 + 66];
-        *a.loss = s * a.inv_count;
-        return;
+// deterministic sum of the workgroups' partials: 16 waves share the partials of 64 parameters
+constexpr int RED_GROUPS = 16;
+__global__ void __launch_bounds__(64 * RED_GROUPS) lcf_reduce_kernel(const float* part, int nwg, float* grad, float* loss,
+                                                                    float inv_count) {
+    __shared__ float s[RED_GROUPS][64];
+    const int l = threadIdx.x & 63, g = threadIdx.x >> 6;
+    const int p = blockIdx.x * 64 + l;
+    float x = 0.0f;
+    if (p < PART) {
+#pragma unroll 8
+        for (int w = g; w < nwg; w += RED_GROUPS) x += part[(int64_t)w * PART + p];
     }
-    const float* src;
-    int stride, idx;
-    if (p < OFF_B1) { src = a.p1; stride = PART1; idx = p; }
-    else if (p < OFF_W2) { src = a.p1; stride = PART1; idx = 576 + (p - OFF_B1); }
-    else if (p < OFF_B2) { src = a.p2; stride = PART; idx = p - OFF_W2; }
-    else if (p < OFF_W3) { src = a.p2; stride = PART; idx = 9216 + (p - OFF_B2); }
-    else if (p < OFF_B3) { src = a.p3; stride = PART; idx = p - OFF_W3; }
-    else if (p < OFF_W4) { src = a.p3; stride = PART; idx = 9216 + (p - OFF_B3); }
-    else { src = a.p4; stride = PART4; idx = p - OFF_W4; }
-    float s = 0.0f;
-    for (int w = 0; w < NWB; ++w) s += src[(int64_t)w * stride + idx];
-    a.grad[p] = s;
+    s[g][l] = x;
+    __syncthreads();
+    if (g > 0 || p >= PART) return;
+#pragma unroll
+    for (int k = 1; k < RED_GROUPS; ++k) x += s[k][l];
+    if (p < NPAR) grad[p] = x;
+    else *loss = x * inv_count;
 }
 
 // ---------------------------------------------------------------- optimiser, batches, fallback
@@ -745,14 +867,20 @@ __global__ void adam_kernel(float* w, uint16_t* wb, float* m, float* v, const fl
     wb[i] = f2bf(wi);
 }
 
-__global__ void gather_kernel(const float2* src, int64_t nv, int T, const int64_t* idx, int64_t B, float2* dst) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= (int64_t)T * B) return;
-    const int t = (int)(i / B);
-    const int64_t b = i - (int64_t)t * B;
-    const int64_t gi = idx[b];
-    const int64_t vol = gi / nv, vv = gi - vol * nv;
-    dst[i] = src[(vol * T + t) * nv + vv];
+// A thread copies GATHER_RUN frames of one batch series (their reads are independent and the
+// index is looked up and split once).
+constexpr int GATHER_RUN = 8;
+__global__ void __launch_bounds__(256) gather_kernel(const float2* src, int64_t nv, int T, const int64_t* idx, int64_t B,
+                                                     float2* dst) {
+    const int64_t b = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (b >= B) return;
+    const int64_t gi = idx[b], vol = gi / nv;
+    const int t0 = blockIdx.y * GATHER_RUN;
+    src += (vol * T + t0) * nv + (gi - vol * nv);
+    dst += (int64_t)t0 * B + b;
+#pragma unroll
+    for (int q = 0; q < GATHER_RUN; ++q)
+        if (t0 + q < T) dst[q * B] = src[q * nv];
 }
 
 __global__ void fb_partial_kernel(const float* pl, const float* ps, int64_t n, double* part) {
@@ -820,16 +948,8 @@ size_t fwd_lds(int T) {   // the launch below takes the streamed kernel above 25
     const int TP = 32 * ((T + 31) / 32) + 8;
     return (T > 256 ? 2 * (size_t)RING_ELEMS * 2 : (size_t)TP * RS * 2) + (size_t)(TP + 8) * 4 * 2;
 }
-size_t bwd_lds(int T) {
-    const int TP = 32 * ((T + 31) / 32) + 8;
-    return 68 * 4 + 2 * (size_t)T * 8 + 2 * (size_t)TP * CH * 2;
-}
-size_t wg_lds(int T, int layer) {
-    const int TP = 32 * ((T + 31) / 32) + 8, T16 = (T + 15) / 16 * 16;
-    return (size_t)T16 * CH * 2 + (size_t)TP * (layer == 1 ? 4 : CH) * 2;
-}
 size_t act_bytes(int64_t n, int T) { return round_up((size_t)n * act_stride(T) * 2, 256); }
-size_t part_bytes() { return (size_t)NWB * (PART1 + 2 * PART + PART4) * 4; }
+size_t part_bytes() { return (size_t)NWB * PART * 4; }
 
 }  // namespace
 }  // namespace fq
@@ -865,29 +985,18 @@ extern "C" int lcf_backward(const float* w, const uint16_t* w_bf16, const float*
     FQ_REQUIRE(aligned16(w_bf16) && aligned16(x) && aligned16(target) && aligned16(act), "misaligned pointer");
     FQ_REQUIRE(n_series >= 1 && n_t >= 1 && n_t <= FQ_MAX_NT, "bad sizes");
     hipStream_t s = as_stream(stream);
-    char* base = reinterpret_cast<char*>(act) + act_bytes(n_series, n_t);
-    float* p1 = reinterpret_cast<float*>(base);
-    float* p2 = p1 + (size_t)NWB * PART1;
-    float* p3 = p2 + (size_t)NWB * PART;
-    float* p4 = p3 + (size_t)NWB * PART;
+    float* part = reinterpret_cast<float*>(reinterpret_cast<char*>(act) + act_bytes(n_series, n_t));
     const float inv_count = (float)(1.0 / ((double)n_series * 2.0 * n_t));
-    BwdArgs ba{w, w_bf16, reinterpret_cast<const float2*>(x), reinterpret_cast<const float2*>(target), act, p4,
+    const int nwg = (int)std::min<int64_t>(NWB, (n_series + BWD_WAVES - 1) / BWD_WAVES);
+    BwdArgs ba{w, w_bf16, reinterpret_cast<const float2*>(x), reinterpret_cast<const float2*>(target), act, part,
                n_series, n_t, eps, inv_count};
-    hipLaunchKernelGGL(lcf_bwd_series_kernel, dim3(NWB), dim3(64), bwd_lds(n_t), s, ba);
+    hipLaunchKernelGGL((n_t <= 256 ? lcf_bwd_kernel<3, 4> : lcf_bwd_kernel<3, 8>), dim3(nwg), dim3(64 * BWD_WAVES),
+                       BWD_LDS, s, ba);
     FQ_LAUNCH_CHECK();
-    WgArgs wa{act, p3, n_series, n_t, 3};
-    hipLaunchKernelGGL(lcf_wgrad_kernel<3>, dim3(NWB), dim3(64), wg_lds(n_t, 3), s, wa);
+    hipLaunchKernelGGL((lcf_bwd_kernel<2, 1>), dim3(nwg), dim3(64 * BWD_WAVES), BWD_LDS, s, ba);
     FQ_LAUNCH_CHECK();
-    wa.part = p2;
-    wa.layer = 2;
-    hipLaunchKernelGGL(lcf_wgrad_kernel<2>, dim3(NWB), dim3(64), wg_lds(n_t, 2), s, wa);
-    FQ_LAUNCH_CHECK();
-    wa.part = p1;
-    wa.layer = 1;
-    hipLaunchKernelGGL(lcf_wgrad_kernel<1>, dim3(NWB), dim3(64), wg_lds(n_t, 1), s, wa);
-    FQ_LAUNCH_CHECK();
-    RedArgs ra{p1, p2, p3, p4, grad, loss, inv_count};
-    hipLaunchKernelGGL(lcf_reduce_kernel, dim3((NPAR + 1 + 255) / 256), dim3(256), 0, s, ra);
+    hipLaunchKernelGGL(lcf_reduce_kernel, dim3((PART + 63) / 64), dim3(64 * RED_GROUPS), 0, s, part, nwg, grad, loss,
+                       inv_count);
     FQ_LAUNCH_CHECK();
     return FQ_OK;
 }
@@ -909,9 +1018,10 @@ extern "C" int lcf_gather(const float* src, int64_t n_vox, int32_t n_t, int64_t 
                           int64_t batch, float* dst, void* stream) {
     FQ_REQUIRE(src && idx && dst && aligned16(src) && aligned16(dst), "null or misaligned pointer");
     FQ_REQUIRE(n_vox >= 1 && n_t >= 1 && n_vol >= 1 && batch >= 1, "bad sizes");
-    const int64_t total = (int64_t)n_t * batch;
-    hipLaunchKernelGGL(gather_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, as_stream(stream),
-                       reinterpret_cast<const float2*>(src), n_vox, n_t, idx, batch, reinterpret_cast<float2*>(dst));
+    const dim3 grid((unsigned)((batch + 255) / 256), (unsigned)((n_t + GATHER_RUN - 1) / GATHER_RUN));
+    FQ_REQUIRE(batch <= ((int64_t)1 << 38) && grid.y <= 65535, "batch or n_t too large");
+    hipLaunchKernelGGL(gather_kernel, grid, dim3(256), 0, as_stream(stream), reinterpret_cast<const float2*>(src), n_vox,
+                       n_t, idx, batch, reinterpret_cast<float2*>(dst));
     FQ_LAUNCH_CHECK();
     return FQ_OK;
 }
