@@ -2,12 +2,13 @@
 //
 // With S = A + iB (voxels x frames), Re G = A^T A + B^T B and Im G = A^T B - B^T A.
 // G is Hermitian, so only the 32x32 frame tiles (I, J) with I <= J are formed.  A
-// workgroup owns a 2x2 group of tiles (64 frames of I-blocks by 64 frames of J-blocks)
-// and one voxel range (split over the contraction dimension): each 64-voxel stage of the
-// 128 frames involved (64 on the group's diagonal) is staged in LDS once, and each of
-// the four waves forms the four real products Re.Re, Im.Im, Re.Im and Im.Re of its own
-// tile with MFMA, so every staged value feeds two tiles' products.
-//   FP32 mode       : v_mfma_f32_32x32x2_f32.
+// workgroup owns a group of four tiles on at most four frame blocks and one voxel range
+// (split over the contraction dimension): each stage of the 128 frames is staged in LDS once,
+// and each of the four waves forms the four real products Re.Re, Im.Im, Re.Im and Im.Re of
+// its own tile with MFMA, so every staged value feeds two tiles' products.  Up to 32 frames
+// there is one tile: the four waves then take four quarters of the voxels.
+//   FP32 mode       : v_mfma_f32_32x32x2_f32.  A lane's operands of four products are one
+//                     16-byte read: a stage keeps the even voxels of each eight ahead of the odd.
 //   split-BF16 mode : x = hi + lo with hi = bf16(x), lo = bf16(x - hi) (round to nearest
 //                     even), split once when the stage is written to LDS; three
 //                     v_mfma_f32_32x32x16_bf16 products hi.hi + hi.lo + lo.hi.
@@ -16,6 +17,10 @@
 //                     Gram's trace that biases every eigenvalue below that level; the
 //                     fourth product removes it.
 //   BF16 mode       : hi.hi only (negative control).
+// What bounds it: FP32, the matrix cores (6.6M voxels x 400 frames: 42.4 ms, MFMA busy 0.77; 51.4 ms
+// while every load was waited for in a branch of its own); the split modes, LDS traffic beside
+// the products (2.1M x 200, four products: 1.9 ms, busy 0.50; 2.76 before).  20 frames x 65536
+// voxels: 11 us on 256 workgroups of four busy wavefronts, 192 us on 32 with one.
 // Accumulation is FP32 inside each 64-voxel stage and FP64 across stages (a long FP32
 // running sum of same-sign terms grows its rounding error with the sum; short blocks
 // keep the Gram exact to ~1e-8 of lambda_1, which the clutter subspace near the cutoff
@@ -40,8 +45,6 @@ constexpr int GT = 32;            // tile edge, frames
 constexpr int GR = 2 * GT;        // LDS stage: 4 frame blocks (2 GR rows)
 constexpr int GMAX = 34;          // tile groups at n_t = 512 (136 tiles, 4 per group)
 constexpr int KC = 64;            // voxels per LDS stage
-constexpr int LDW = KC + 4;       // FP32 LDS row stride (floats)
-constexpr int LDB = KC + 8;       // BF16 LDS row stride (bf16 values; 144-byte rows)
 constexpr int GRAM_THREADS = 256;
 constexpr int NXCD = 8;
 
@@ -62,21 +65,14 @@ struct GramArgs {
     GroupTab tab;
 };
 
-// hi/lo pair of 8 values packed as two 16-byte vectors of bf16 bit patterns, with the
-// hardware pair conversion (round to nearest even): hi = bf16(x), lo = bf16(x - hi)
-__device__ __forceinline__ void split8(const float* x, uint4& hi, uint4& lo) {
+// two BF16 terms of two values, packed, with the hardware pair conversion (round to nearest
+// even): hi = bf16(x), lo = bf16(x - hi)
+__device__ __forceinline__ void split2(float x, float y, unsigned int& hi, unsigned int& lo) {
     typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-    unsigned int h[4], l[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const bf16x2 hv = {(__bf16)x[2 * q], (__bf16)x[2 * q + 1]};
-        h[q] = __builtin_bit_cast(unsigned int, hv);
-        const bf16x2 lv = {(__bf16)(x[2 * q] - __uint_as_float(h[q] << 16)),
-                           (__bf16)(x[2 * q + 1] - __uint_as_float(h[q] & 0xffff0000u))};
-        l[q] = __builtin_bit_cast(unsigned int, lv);
-    }
-    hi = make_uint4(h[0], h[1], h[2], h[3]);
-    lo = make_uint4(l[0], l[1], l[2], l[3]);
+    const bf16x2 v = {(__bf16)x, (__bf16)y};
+    hi = __builtin_bit_cast(unsigned int, v);
+    const bf16x2 r = {(__bf16)(x - __uint_as_float(hi << 16)), (__bf16)(y - __uint_as_float(hi & 0xffff0000u))};
+    lo = __builtin_bit_cast(unsigned int, r);
 }
 
 // flip the sign bits of 8 packed bf16 values
@@ -85,30 +81,46 @@ __device__ __forceinline__ uint4 neg8(uint4 x) {
 }
 
 template <int MODE>
+struct GramShape {
+    static constexpr bool SPLIT = MODE != FQ_GRAM_FP32;
+    static constexpr int NP = SPLIT ? 2 : 1;                     // terms of a value
+    static constexpr int LD = SPLIT ? (KC + 8) * 2 : (KC + 4) * 4;   // LDS row, bytes: 16-byte reads of 8 rows on distinct banks
+    static constexpr int PLANE = 2 * GR * LD;                    // bytes: one term of Re or Im of the 128 rows
+    static constexpr int LDS = 2 * NP * PLANE;
+    // a lane loads 8 consecutive voxels of a frame: one or two 16-byte LDS writes per plane, and
+    // the loads of a wavefront stay within 8 rows at a time
+    static constexpr int VPT = 8;
+    static constexpr int LPR = KC / VPT;                         // lanes per row
+    static constexpr int RPP = 64 / LPR;                         // rows per pass
+    static constexpr int NPASS = GT / RPP;
+};
+
+template <int MODE, bool ONE, bool EVEN>
 __global__ void __launch_bounds__(GRAM_THREADS, 2) gram_kernel(const GramArgs a) {
-    constexpr bool SPLIT = MODE != FQ_GRAM_FP32;
-    // FP32: planes Re, Im of [2 GR][LDW] floats; BF16: planes Re.hi, Re.lo, Im.hi, Im.lo of [2 GR][LDB]
-    constexpr int PLANE = SPLIT ? 2 * GR * LDB * 2 : 2 * GR * LDW * 4;   // bytes
-    constexpr int NPLANE = SPLIT ? 4 : 2;
-    __shared__ __align__(16) unsigned char lds[NPLANE * PLANE];
+    using S = GramShape<MODE>;
+    constexpr int NP = S::NP, PLANE = S::PLANE, VPT = S::VPT;
+    __shared__ __align__(16) unsigned char lds[S::LDS];   // planes [Re, Im][term][128 rows][LD]
 
     // XCD-aware decode: workgroups id, id+8, ... run on one XCD; give them one voxel range.
     const int id = blockIdx.x;
     const int xcd = id % NXCD, loc = id / NXCD;
-    const int grp = loc % a.ngroups;
-    const int split = (loc / a.ngroups) * NXCD + xcd;
+    const int grp = ONE ? 0 : loc % a.ngroups;
+    const int split = (ONE ? loc : loc / a.ngroups) * NXCD + xcd;
     if (split >= a.nsplit) return;
     const int64_t v_begin = (int64_t)split * a.chunk;
     const int64_t v_end = min(a.nv, v_begin + a.chunk);
 
-    const int w = threadIdx.x / 64, l = threadIdx.x % 64;
-    const int I = a.tab.ij[grp][w][0], J = a.tab.ij[grp][w][1];
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), l = threadIdx.x % 64;
+    const int I = ONE ? 0 : a.tab.ij[grp][w][0], J = ONE ? 0 : a.tab.ij[grp][w][1];
     const bool active = I != 255;
-    int xrow = 0, yrow = 0;   // stage rows of blocks I and J
+    int xrow = w * GT, yrow = w * GT;   // stage rows of blocks I and J
+    if (!ONE) {
+        xrow = yrow = 0;
 #pragma unroll
-    for (int sl = 0; sl < 4; ++sl) {
-        if (a.tab.blk[grp][sl] == I) xrow = sl * GT;
-        if (a.tab.blk[grp][sl] == J) yrow = sl * GT;
+        for (int sl = 0; sl < 4; ++sl) {
+            if (a.tab.blk[grp][sl] == I) xrow = sl * GT;
+            if (a.tab.blk[grp][sl] == J) yrow = sl * GT;
+        }
     }
 
     // Re G = Re.Re + Im.Im and Im G = Re.Im - Im.Re accumulate directly (the second term of
@@ -121,107 +133,137 @@ __global__ void __launch_bounds__(GRAM_THREADS, 2) gram_kernel(const GramArgs a)
         sum_re[r] = sum_im[r] = 0.0;
     }
 
-    // loader mapping: up to 128 rows x 64 voxels; thread -> (row, 32-voxel half).  The next
-    // stage is loaded into registers while the current one is multiplied.
-    const int lrow = threadIdx.x >> 1, lh = threadIdx.x & 1;
-    const int lblk = a.tab.blk[grp][lrow / GT];
+    // Wavefront w loads block slot w (one tile: the w-th quarter of the stage's voxels); the
+    // next stage is in flight to registers while the current one is multiplied.  The loads of
+    // a full stage have no condition on them (frames past the end read the last one: their
+    // tile elements are not stored): where lanes or rows were tested, every load sat in a
+    // branch of its own that waited for it, and nothing was in flight during the products.
+    const int lr = l / S::LPR, lv = (l % S::LPR) * VPT;
+    const int lblk = ONE ? 0 : a.tab.blk[grp][w];
     const bool lact = lblk != 255;
-    const int frame = lblk * GT + lrow % GT;
-    const bool fvalid = lact && frame < a.nt;
-    const float2* srow = a.iq + (int64_t)(fvalid ? frame : 0) * a.nv;
-    float re[32], im[32];
-    auto load = [&](int64_t v0) {
-        const int64_t vb = v0 + lh * 32;
-        if (fvalid && vb + 32 <= v_end && (a.nv % 2) == 0) {
-            const float4* src = reinterpret_cast<const float4*>(srow + vb);
+    const float2* src[S::NPASS];
 #pragma unroll
-            for (int q = 0; q < 16; ++q) {
-                const float4 p = src[q];
-                re[2 * q] = p.x;
-                im[2 * q] = p.y;
-                re[2 * q + 1] = p.z;
-                im[2 * q + 1] = p.w;
-            }
-        } else {
+    for (int p = 0; p < S::NPASS; ++p)
+        src[p] = a.iq + (int64_t)min((lact ? lblk : 0) * GT + p * S::RPP + lr, a.nt - 1) * a.nv + v_begin +
+                 (ONE ? w * KC : 0) + lv;
+    float4 in[S::NPASS][VPT / 2];
+    auto load = [&] {
 #pragma unroll
-            for (int q = 0; q < 32; ++q) {
-                float2 p = make_float2(0.f, 0.f);
-                if (fvalid && vb + q < v_end) p = srow[vb + q];
-                re[q] = p.x;
-                im[q] = p.y;
+        for (int p = 0; p < S::NPASS; ++p) {
+#pragma unroll
+            for (int q = 0; q < VPT / 2; ++q) {
+                if (EVEN) {
+                    in[p][q] = reinterpret_cast<const float4*>(src[p])[q];
+                } else {   // rows start on 8-byte boundaries
+                    const float2 x = src[p][2 * q], y = src[p][2 * q + 1];
+                    in[p][q] = make_float4(x.x, x.y, y.x, y.y);
+                }
             }
+            src[p] += ONE ? 4 * KC : KC;
         }
     };
-    if (lact && v_begin < v_end) load(v_begin);
+    // the last, partial stage, of `left` voxels
+    auto load_tail = [&](int left) {
+        left -= (ONE ? w * KC : 0) + lv;
+#pragma unroll
+        for (int p = 0; p < S::NPASS; ++p)
+#pragma unroll
+            for (int q = 0; q < VPT / 2; ++q) {
+                float2 x = make_float2(0.f, 0.f), y = x;
+                if (2 * q < left) x = src[p][2 * q];
+                if (2 * q + 1 < left) y = src[p][2 * q + 1];
+                in[p][q] = make_float4(x.x, x.y, y.x, y.y);
+            }
+    };
 
     const int i = l % 32, h = l / 32;
-    for (int64_t v0 = v_begin; v0 < v_end; v0 += KC) {
+    constexpr int STEP = ONE ? 4 * KC : KC;
+    const int len = (int)max((int64_t)0, v_end - v_begin), nfull = len / STEP, left = len % STEP;
+    if (lact && nfull) load();
+    for (int stage = 0; stage < nfull + (left ? 1 : 0); ++stage) {
         __syncthreads();
         if (lact) {
-            if (!SPLIT) {
-                float* dr = reinterpret_cast<float*>(lds) + lrow * LDW + lh * 32;
-                float* di = reinterpret_cast<float*>(lds + PLANE) + lrow * LDW + lh * 32;
+            if (stage == nfull) load_tail(left);
 #pragma unroll
-                for (int q = 0; q < 32; q += 4) {
-                    *reinterpret_cast<float4*>(dr + q) = make_float4(re[q], re[q + 1], re[q + 2], re[q + 3]);
-                    *reinterpret_cast<float4*>(di + q) = make_float4(im[q], im[q + 1], im[q + 2], im[q + 3]);
-                }
-            } else {
-                const int off = (lrow * LDB + lh * 32) * 2;   // bytes
+            for (int p = 0; p < S::NPASS; ++p) {
+                unsigned char* d = lds + (w * GT + p * S::RPP + lr) * S::LD + lv * (S::SPLIT ? 2 : 4);
+                if constexpr (!S::SPLIT) {
+                    const float4* x = in[p];
+                    *reinterpret_cast<float4*>(d) = make_float4(x[0].x, x[1].x, x[2].x, x[3].x);
+                    *reinterpret_cast<float4*>(d + 16) = make_float4(x[0].z, x[1].z, x[2].z, x[3].z);
+                    *reinterpret_cast<float4*>(d + PLANE) = make_float4(x[0].y, x[1].y, x[2].y, x[3].y);
+                    *reinterpret_cast<float4*>(d + PLANE + 16) = make_float4(x[0].w, x[1].w, x[2].w, x[3].w);
+                } else {
+                    unsigned int re[2][4], im[2][4];
 #pragma unroll
-                for (int q = 0; q < 32; q += 8) {
-                    uint4 hi, lo;
-                    split8(re + q, hi, lo);
-                    *reinterpret_cast<uint4*>(lds + 0 * PLANE + off + q * 2) = hi;
-                    *reinterpret_cast<uint4*>(lds + 1 * PLANE + off + q * 2) = lo;
-                    split8(im + q, hi, lo);
-                    *reinterpret_cast<uint4*>(lds + 2 * PLANE + off + q * 2) = hi;
-                    *reinterpret_cast<uint4*>(lds + 3 * PLANE + off + q * 2) = lo;
+                    for (int q = 0; q < 4; ++q) {
+                        split2(in[p][q].x, in[p][q].z, re[0][q], re[1][q]);
+                        split2(in[p][q].y, in[p][q].w, im[0][q], im[1][q]);
+                    }
+#pragma unroll
+                    for (int t = 0; t < 2; ++t) {
+                        *reinterpret_cast<uint4*>(d + t * PLANE) = make_uint4(re[t][0], re[t][1], re[t][2], re[t][3]);
+                        *reinterpret_cast<uint4*>(d + (2 + t) * PLANE) = make_uint4(im[t][0], im[t][1], im[t][2], im[t][3]);
+                    }
                 }
             }
         }
         __syncthreads();
-        if (lact && v0 + KC < v_end) load(v0 + KC);
+        if (lact && stage + 1 < nfull) load();
         if (!active) continue;
-        if (!SPLIT) {
-            const float* Re = reinterpret_cast<const float*>(lds);
-            const float* Im = reinterpret_cast<const float*>(lds + PLANE);
-            const int xo = (xrow + i) * LDW + h, yo = (yrow + i) * LDW + h;
+        const unsigned char* X = lds + (xrow + i) * S::LD + h * 16;
+        const unsigned char* Y = lds + (yrow + i) * S::LD + h * 16;
+        if constexpr (!S::SPLIT) {
 #pragma unroll
-            for (int kk = 0; kk < KC; kk += 2) {
-                const float xr = Re[xo + kk], xi = Im[xo + kk], yr = Re[yo + kk], yi = Im[yo + kk];
-                acc_re = __builtin_amdgcn_mfma_f32_32x32x2f32(xr, yr, acc_re, 0, 0, 0);
-                acc_re = __builtin_amdgcn_mfma_f32_32x32x2f32(xi, yi, acc_re, 0, 0, 0);
-                acc_im = __builtin_amdgcn_mfma_f32_32x32x2f32(xr, yi, acc_im, 0, 0, 0);
-                acc_im = __builtin_amdgcn_mfma_f32_32x32x2f32(-xi, yr, acc_im, 0, 0, 0);
+            for (int kk = 0; kk < KC; kk += 8) {
+                const float4 xr = *reinterpret_cast<const float4*>(X + kk * 4);
+                const float4 xi = *reinterpret_cast<const float4*>(X + PLANE + kk * 4);
+                const float4 yr = *reinterpret_cast<const float4*>(Y + kk * 4);
+                const float4 yi = *reinterpret_cast<const float4*>(Y + PLANE + kk * 4);
+                auto step = [&](float ar, float ai, float br, float bi) {   // the accumulators take turns
+                    acc_re = __builtin_amdgcn_mfma_f32_32x32x2f32(ar, br, acc_re, 0, 0, 0);
+                    acc_im = __builtin_amdgcn_mfma_f32_32x32x2f32(ar, bi, acc_im, 0, 0, 0);
+                    acc_re = __builtin_amdgcn_mfma_f32_32x32x2f32(ai, bi, acc_re, 0, 0, 0);
+                    acc_im = __builtin_amdgcn_mfma_f32_32x32x2f32(-ai, br, acc_im, 0, 0, 0);
+                };
+                step(xr.x, xi.x, yr.x, yi.x);
+                step(xr.y, xi.y, yr.y, yi.y);
+                step(xr.z, xi.z, yr.z, yi.z);
+                step(xr.w, xi.w, yr.w, yi.w);
             }
         } else {
-            const int xo = ((xrow + i) * LDB + h * 8) * 2, yo = ((yrow + i) * LDB + h * 8) * 2;   // bytes
 #pragma unroll
             for (int kk = 0; kk < KC; kk += 16) {
-                const int k2 = kk * 2;
-                const uint4 xrh = *reinterpret_cast<const uint4*>(lds + 0 * PLANE + xo + k2);
-                const uint4 xrl = *reinterpret_cast<const uint4*>(lds + 1 * PLANE + xo + k2);
-                const uint4 xih = *reinterpret_cast<const uint4*>(lds + 2 * PLANE + xo + k2);
-                const uint4 xil = *reinterpret_cast<const uint4*>(lds + 3 * PLANE + xo + k2);
-                const uint4 yrh = *reinterpret_cast<const uint4*>(lds + 0 * PLANE + yo + k2);
-                const uint4 yrl = *reinterpret_cast<const uint4*>(lds + 1 * PLANE + yo + k2);
-                const uint4 yih = *reinterpret_cast<const uint4*>(lds + 2 * PLANE + yo + k2);
-                const uint4 yil = *reinterpret_cast<const uint4*>(lds + 3 * PLANE + yo + k2);
-                // (x, y) operand pairs: Re.Re and Im.Im into Re G; Re.Im and (-Im).Re into Im G
-                const uint4 XH[4] = {xrh, xih, xrh, neg8(xih)}, XL[4] = {xrl, xil, xrl, neg8(xil)};
-                const uint4 YH[4] = {yrh, yih, yih, yrh}, YL[4] = {yrl, yil, yil, yrl};
+                uint4 xr[2], xi[2], xn[2], yr[2], yi[2];
 #pragma unroll
-                for (int p = 0; p < 4; ++p) {
-                    floatx16& acc = p < 2 ? acc_re : acc_im;
-                    const bf16x8 xh = __builtin_bit_cast(bf16x8, XH[p]), yh = __builtin_bit_cast(bf16x8, YH[p]);
-                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xh, yh, acc, 0, 0, 0);
-                    if (MODE == FQ_GRAM_SPLIT_BF16 || MODE == FQ_GRAM_SPLIT4_BF16) {
-                        const bf16x8 xl = __builtin_bit_cast(bf16x8, XL[p]), yl = __builtin_bit_cast(bf16x8, YL[p]);
-                        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xh, yl, acc, 0, 0, 0);
-                        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xl, yh, acc, 0, 0, 0);
-                        if (MODE == FQ_GRAM_SPLIT4_BF16) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xl, yl, acc, 0, 0, 0);
+                for (int t = 0; t < 2; ++t) {
+                    xr[t] = *reinterpret_cast<const uint4*>(X + t * PLANE + kk * 2);
+                    xi[t] = *reinterpret_cast<const uint4*>(X + (2 + t) * PLANE + kk * 2);
+                    yr[t] = *reinterpret_cast<const uint4*>(Y + t * PLANE + kk * 2);
+                    yi[t] = *reinterpret_cast<const uint4*>(Y + (2 + t) * PLANE + kk * 2);
+                    xn[t] = neg8(xi[t]);
+                }
+                auto mul = [](const uint4& x, const uint4& y, floatx16& acc) {
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, x),
+                                                                  __builtin_bit_cast(bf16x8, y), acc, 0, 0, 0);
+                };
+                // Re.Re and Re.Im, then Im.Im and -Im.Re; the two accumulators take turns
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    const uint4* xa = c ? xi : xr;
+                    const uint4* xb = c ? xn : xr;
+                    const uint4* ya = c ? yi : yr;
+                    const uint4* yb = c ? yr : yi;
+                    auto product = [&](int p, int q) {
+                        mul(xa[p], ya[q], acc_re);
+                        mul(xb[p], yb[q], acc_im);
+                    };
+                    product(0, 0);
+                    if constexpr (MODE != FQ_GRAM_BF16) {
+                        product(0, 1);
+                        product(1, 0);
                     }
+                    if constexpr (MODE == FQ_GRAM_SPLIT4_BF16) product(1, 1);
                 }
             }
         }
@@ -231,6 +273,26 @@ __global__ void __launch_bounds__(GRAM_THREADS, 2) gram_kernel(const GramArgs a)
             sum_im[r] += (double)acc_im[r];
             acc_re[r] = acc_im[r] = 0.0f;
         }
+    }
+    if (ONE) {   // the four waves' sums, in a fixed order
+        double* part = reinterpret_cast<double*>(lds);   // [3][16][64], Re then Im
+        static_assert(3 * 16 * 64 * sizeof(double) <= S::LDS, "partial sums fit the stage");
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            double* sum = c ? sum_im : sum_re;
+            __syncthreads();
+            if (w > 0) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) part[((w - 1) * 16 + r) * 64 + l] = sum[r];
+            }
+            __syncthreads();
+            if (w == 0) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    sum[r] = (sum[r] + part[r * 64 + l]) + (part[(16 + r) * 64 + l] + part[(32 + r) * 64 + l]);
+            }
+        }
+        if (w > 0) return;
     }
     if (!active) return;
 
@@ -374,11 +436,19 @@ Plan plan(int64_t nv, int nt, size_t max_bytes = 0) {
         const int64_t cap = (int64_t)(max_bytes / per_split) / NXCD * NXCD;
         want = std::max<int64_t>(1, std::min<int64_t>(want, cap));
     }
-    int64_t chunk = (nv + want - 1) / want;
-    chunk = std::max<int64_t>(2048, round_up((size_t)chunk, 2048));
-    int64_t ns = (nv + chunk - 1) / chunk;
+    // Few workgroups: as many ranges as fill the 512 places on the chip (two workgroups a
+    // compute unit) a whole number of times, down to 256 voxels each.  262144 voxels x 200 frames
+    // are 73 ranges x 7 groups, one round, where 2048-voxel ranges made 1.75.
+    int64_t rounds = (nv * p.ngroups + 512 * 2048 - 1) / (512 * 2048);
+    if (rounds <= 4) {
+        const int64_t ranges = std::max<int64_t>(NXCD, 512 * rounds / p.ngroups / NXCD * NXCD);
+        want = std::min(ranges, max_bytes ? want : ranges);
+        p.chunk = std::max<int64_t>(256, round_up((size_t)((nv + want - 1) / want), 64));
+    } else {
+        p.chunk = std::max<int64_t>(2048, round_up((size_t)((nv + want - 1) / want), 2048));
+    }
+    const int64_t ns = (nv + p.chunk - 1) / p.chunk;
     p.nsplit = (int)round_up((size_t)ns, NXCD);
-    p.chunk = chunk;
     p.bytes = (size_t)p.nsplit * p.ntiles * 2 * GT * GT * sizeof(double);
     return p;
 }
@@ -412,6 +482,21 @@ int scratch_for_current_device(void** out) {
     return FQ_OK;
 }
 
+using GramFn = void (*)(const GramArgs);
+template <int MODE>
+GramFn gram_mode_fn(bool one, bool even) {
+    if (one) return even ? gram_kernel<MODE, true, true> : gram_kernel<MODE, true, false>;
+    return even ? gram_kernel<MODE, false, true> : gram_kernel<MODE, false, false>;
+}
+GramFn gram_fn(int mode, bool one, bool even) {
+    switch (mode) {
+        case FQ_GRAM_FP32: return gram_mode_fn<FQ_GRAM_FP32>(one, even);
+        case FQ_GRAM_SPLIT_BF16: return gram_mode_fn<FQ_GRAM_SPLIT_BF16>(one, even);
+        case FQ_GRAM_SPLIT4_BF16: return gram_mode_fn<FQ_GRAM_SPLIT4_BF16>(one, even);
+        default: return gram_mode_fn<FQ_GRAM_BF16>(one, even);
+    }
+}
+
 int launch_gram(const float* iq, int64_t n_vox, int32_t n_t, int32_t gram_mode, const Plan& p, void* ws,
                 double* gram, hipStream_t s) {
     GramArgs ga{};
@@ -426,20 +511,8 @@ int launch_gram(const float* iq, int64_t n_vox, int32_t n_t, int32_t gram_mode, 
     ga.ngroups = p.ngroups;
     ga.tab = p.tab;
     const unsigned nwg = (unsigned)(p.ngroups * p.nsplit);
-    switch (gram_mode) {
-        case FQ_GRAM_FP32:
-            hipLaunchKernelGGL(gram_kernel<FQ_GRAM_FP32>, dim3(nwg), dim3(GRAM_THREADS), 0, s, ga);
-            break;
-        case FQ_GRAM_SPLIT_BF16:
-            hipLaunchKernelGGL(gram_kernel<FQ_GRAM_SPLIT_BF16>, dim3(nwg), dim3(GRAM_THREADS), 0, s, ga);
-            break;
-        case FQ_GRAM_SPLIT4_BF16:
-            hipLaunchKernelGGL(gram_kernel<FQ_GRAM_SPLIT4_BF16>, dim3(nwg), dim3(GRAM_THREADS), 0, s, ga);
-            break;
-        default:
-            hipLaunchKernelGGL(gram_kernel<FQ_GRAM_BF16>, dim3(nwg), dim3(GRAM_THREADS), 0, s, ga);
-            break;
-    }
+    const GramFn fn = gram_fn(gram_mode, p.ntiles == 1, n_vox % 2 == 0);
+    hipLaunchKernelGGL(fn, dim3(nwg), dim3(GRAM_THREADS), 0, s, ga);
     FQ_LAUNCH_CHECK();
     ReduceArgs ra{reinterpret_cast<const double*>(ws), reinterpret_cast<double2*>(gram), n_t, p.nb, p.ntiles,
                   p.nsplit};
