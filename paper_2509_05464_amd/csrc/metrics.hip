@@ -46,10 +46,6 @@ __global__ void __launch_bounds__(IQM_THREADS) image_quality_kernel(const IqmArg
     const int tid = threadIdx.x;
     const int n = p.nx * p.ny;
     double m = 0.0;
-    for (int i = tid; i < n; i += IQM_THREADS) {
-        const double d = (double)p.a[i] - (double)p.b[i];
-        m = fma(d, d, m);
-    }
     const int ox = p.nx - IQM_WIN + 1, oy = p.ny - IQM_WIN + 1;
     // tiles of equal size
     const int tx = (ox + IQM_TX - 1) / IQM_TX, ty = (oy + IQM_TY - 1) / IQM_TY;
@@ -63,11 +59,17 @@ __global__ void __launch_bounds__(IQM_THREADS) image_quality_kernel(const IqmArg
                 const int r = i / quads, c0 = (i - r * quads) * IQM_QX;
                 const int64_t at = (int64_t)(y0 + r) * p.nx;
                 double acc[5][IQM_QX] = {};
+                // each pixel's squared error is counted once: in its own tile and group of
+                // four, the image's last rows and columns in the last ones
+                const bool own_row = r < h || y0 + h == oy, own_tail = x0 + w == ox && c0 + IQM_QX >= w;
 #pragma unroll
                 for (int k = 0; k < IQM_WIN + IQM_QX - 1; ++k) {
                     const int x = min(x0 + c0 + k, p.nx - 1);   // past the tile: not stored
                     const double va = p.a[at + x], vb = p.b[at + x];
                     const double v[5] = {va, vb, va * va, vb * vb, va * vb};
+                    const bool own = own_row && x0 + c0 + k < p.nx && (own_tail || (k < IQM_QX && c0 + k < w));
+                    const double d = own ? va - vb : 0.0;
+                    m = fma(d, d, m);
 #pragma unroll
                     for (int j = 0; j < IQM_QX; ++j) {
                         if (k - j < 0 || k - j >= IQM_WIN) continue;
