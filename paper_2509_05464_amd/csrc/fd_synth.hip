@@ -10,53 +10,69 @@
 //   P_a(m, f) = sum_s H_m(s, f) R_s T_a(s, f),
 // and the RF is  rf_a(m, t) = 2 Re sum_j w_j P_a(m, f_j) e^{-i 2 pi j t / N},
 // w_j = q_j S(f_j) df with S the Fourier transform of the Gaussian pulse (q = 1/2 at
-// j = 0 and j = N/2).  Three kernels per scatterer block and frame:
-//   fd_tx_kernel   lane = scatterer: T for a chunk of KC consecutive frequencies and up
-//                  to AG transmits; elements are visited in LDS blocks holding
-//                  W_e e^{i 2 pi f dtau_ae} for the chunk;
+// j = 0 and j = N/2).  Three kernels per scatterer block and batch of frames:
+//   fd_tx_kernel   lane = scatterer: T for a chunk of KC consecutive frequencies and the
+//                  transmits of a group; the four wavefronts of a workgroup take every fourth
+//                  block of elements, whose W_e e^{i 2 pi f dtau_ae} they hold in LDS, and add up
+//                  their sums at the end;
 //   fd_rx_kernel   lane = receive element: P for the chunk, scatterers staged in LDS
-//                  blocks with R_s T_a(s, f); scatterer ranges split over z for
-//                  occupancy, partial sums kept apart and added in a fixed order;
-//   fd_idft_kernel workgroup = (element, transmit): the weighted inverse transform of the
-//                  band, the complex exponential stepped in frequency and re-anchored
-//                  from an exact integer phase every 64 samples.
-// Within a chunk e^{i k r} is stepped from frequency to frequency by one complex
-// multiplication (the frequency-stepping propagation update of Algorithm 2); each chunk
-// starts from phases taken in FP64 (cycles = j df r / c) so the error does not grow with
-// j.  The directivity sines (a few cycles at most) come straight from the hardware sine.  Scatterer blocks bound the transmit-field buffer by the
-// workspace (the memory partition of Algorithm 2); their echoes add up in P.
+//                  blocks with R_s T_a(s, f); scatterer ranges split for occupancy, partial
+//                  sums kept apart and added in a fixed order;
+//   fd_idft_kernel workgroup = (elements, transmit): the weighted inverse transform of the
+//                  band, the complex exponential stepped in frequency, shared by the
+//                  elements and re-anchored from an exact integer phase every 64 samples.
+// Frames go through the kernels in batches as large as the workspace holds: one frame of a
+// small scene (500 scatterers, 405 frequencies) fills a quarter of the chip for 0.6 ms.
+//
+// Element response: within a chunk e^{i k r} is stepped from frequency to frequency by one
+// complex multiplication (the frequency-stepping propagation update of Algorithm 2),
+// outwards from the chunk's middle, whose phase is taken in FP64 (cycles = j df r / c), so the
+// error does not grow with j and is at most KC/2 steps.  The directivity sines (a few cycles
+// at most) come straight from the hardware sine.  The
+// kernels are bound by the VALU work of this response (FP64 path and reduction to a turn,
+// 16 transcendentals, ~110 FP32 multiply-adds per sub-element and chunk); the products with
+// the NA transmits add 4 NA KC.  Chunks of 8 cost 0.55 of chunks of 4 with a sine per
+// frequency and axis; kernels compiled for the group's number of transmits do not compute
+// 9 for 3.  (16 x 16 elements of 2 x 2, 3 transmits, 2000 static + 20 x 500 scatterers:
+// 9.8 ms against 23.6.)
+// Scatterer blocks bound the transmit-field buffer by the workspace (the memory partition
+// of Algorithm 2); their echoes add up in P.
 #include "fq_common.hpp"
 
 namespace fq {
 namespace {
 
 constexpr int FD_THREADS = 256;
-constexpr int KC = 4;         // frequencies per chunk
-constexpr int AG = 9;         // transmits per launch group
-constexpr int EB = 64;        // elements per LDS block (transmit field)
-constexpr int SB = 64;        // scatterers per LDS block (echo)
+constexpr int KC = 8;         // frequencies per chunk
+constexpr int AG = 9;         // transmits per launch group, at most
+constexpr int EB = 16;        // elements per LDS block (transmit field) and wavefront
+constexpr int SB = 32;        // scatterers per LDS block (echo)
 constexpr int FD_MAX_K = 4096;
 constexpr int FD_MIN_BLOCK = 256;
+constexpr int MC = 8;         // elements of an inverse-transform workgroup
+constexpr int MC_MAX_K = 1024;   // band that MC elements' spectra fit in LDS for; two beyond
 constexpr double TWO_PI = 6.283185307179586;
 
 struct FdArgs {
-    const float* pos;       // [S][3] of this frame
+    const float* pos;       // [S][3] of the batch's first frame
     const float* amp;       // [S]
     const float* apod;      // [E] or null
-    float2* T;              // [K][nsb][AG]
-    float2* P;              // [nsplit][K][E][AG]
+    float2* T;              // [frame][chunk][nsb][nq][NA], nq = frequencies of the chunk
+    float2* P;              // [frame][split][chunk][E][nq][NA]
     const float* w;         // [K] 2 w_j
     float* rf;              // output of the inverse transform
     int64_t s0, ns, nsb;    // scatterer block [s0, s0 + ns), T row stride nsb
-    int n_elem, nx_el, K, j_lo, N;
+    int64_t pos_stride;     // floats between frames of pos
+    int n_elem, nx_el, K, j_lo, N, chunks;
     int vx, vy;
     int na;                 // transmits in this group (<= AG)
     int nsplit, p_acc;      // echo splits; P accumulates over scatterer blocks
+    int dir;                // elements have a size
     double pitch_x, pitch_y, hx, hy;   // element pitch; (n-1)/2 pitch offsets
     double wx, wy;          // element size
     double df_c;            // df / c: cycles per metre per frequency step
+    double alpha2_df;       // attenuation, powers of two per metre per frequency step
     double bx_df_c, by_df_c;   // directivity cycles per step per unit direction cosine (b df / c)
-    double alpha_df;        // attenuation nepers per metre per frequency step
     double df;
     float r_ref;
     double ux[AG], uy[AG], t0[AG];   // transmit directions and first-firing offsets (s)
@@ -74,106 +90,147 @@ __device__ __forceinline__ void elem_xy(const FdArgs& a, int e, double& ex, doub
     ey = (e / a.nx_el) * a.pitch_y - a.hy;
 }
 
-// h[q] += (1/v) sum_mu (r_ref/r) e^{(i k - alpha) r} D for f = (j0 + q) df, q < KC.
-__device__ __forceinline__ void elem_resp(const FdArgs& a, double ex, double ey, double sx, double sy, double sz,
-                                          int j0, const float* invj, float2* h) {
+// h[q] = sum_mu (r_ref/r) e^{(i k - alpha) r} D for f = (j0 + q) df, q < KC, of an element whose
+// centre is (dxc, dyc) off the scatterer; D = sinc sinc of the sub-element's direction.
+__device__ __forceinline__ void elem_resp(const FdArgs& a, double dxc, double dyc, double sz2, int j0,
+                                          const float* invj2, float2* h) {
+    constexpr int M = KC / 2;
 #pragma unroll
     for (int q = 0; q < KC; ++q) h[q] = make_float2(0.f, 0.f);
+    float h0 = 0.0f;   // the response at f = 0
+    const float jm = (float)(j0 + M);
     for (int mx = 0; mx < a.vx; ++mx) {
-        const double px = ex + ((mx + 0.5) / a.vx - 0.5) * a.wx;
+        const double dx = dxc - ((mx + 0.5) / a.vx - 0.5) * a.wx;
+        const double dx2 = fma(dx, dx, sz2);
         for (int my = 0; my < a.vy; ++my) {
-            const double py = ey + ((my + 0.5) / a.vy - 0.5) * a.wy;
-            const double dx = sx - px, dy = sy - py;
-            const double r = sqrt_nr(dx * dx + dy * dy + sz * sz);
+            const double dy = dyc - ((my + 0.5) / a.vy - 0.5) * a.wy;
+            const double r = sqrt_nr(fma(dy, dy, dx2));
             const double cyc = a.df_c * r;                        // phase cycles per frequency step
-            float2 z = cis_cycles((double)j0 * cyc);
-            float2 st = cis_cycles(cyc);
-            float g = a.r_ref * __builtin_amdgcn_rcpf((float)r);
-            if (a.alpha_df > 0.0) {
-                const float ar = (float)(a.alpha_df * r);         // nepers per frequency step
-                g *= __expf(-ar * (float)j0);
-                const float ast = __expf(-ar);
-                st.x *= ast;
-                st.y *= ast;
-            }
-            z.x *= g;
-            z.y *= g;
-            // directivity sinc(2 pi j t) = sin(2 pi j t) / (2 pi j t), t = b df u / c cycles per
-            // frequency step: the sine straight from the hardware (argument reduced to a turn)
-            float dxq[KC], dyq[KC];
+            const float2 zm = cis_cycles((double)(j0 + M) * cyc);
+            const float2 st = cis_cycles(cyc);
+            const float rinv = __builtin_amdgcn_rcpf((float)r);
+            const float ar = (float)(a.alpha2_df * r);
+            const float at = __builtin_amdgcn_exp2f(-ar), ai = __builtin_amdgcn_exp2f(ar);
+            const float2 up = make_float2(st.x * at, st.y * at), dn = make_float2(st.x * ai, -st.y * ai);
+            float g = a.r_ref * rinv;
+            h0 += g;
+            g *= __builtin_amdgcn_exp2f(-ar * jm);
+            if (!a.dir) {
+                float2 z = make_float2(zm.x * g, zm.y * g);
+                const float2 z0 = z;
 #pragma unroll
-            for (int q = 0; q < KC; ++q) dxq[q] = dyq[q] = 1.0f;
-            const float rinv = (float)(1.0 / r);
-            if (a.wx > 0.0) {
-                const float tx = (float)(a.bx_df_c * dx) * rinv;   // directivity cycles per step
-                if (tx != 0.0f) {
-                    const float ix = __builtin_amdgcn_rcpf((float)TWO_PI * tx);
-#pragma unroll
-                    for (int q = 0; q < KC; ++q) {
-                        const float c = tx * (float)(j0 + q);
-                        dxq[q] = invj[q] > 0.0f ? __builtin_amdgcn_sinf(c - floorf(c)) * ix * invj[q] : 1.0f;
-                    }
+                for (int q = M; q < KC; ++q) {
+                    h[q].x += z.x;
+                    h[q].y += z.y;
+                    z = cmul(z, up);
                 }
-            }
-            if (a.wy > 0.0) {
-                const float ty = (float)(a.by_df_c * dy) * rinv;
-                if (ty != 0.0f) {
-                    const float iy = __builtin_amdgcn_rcpf((float)TWO_PI * ty);
+                z = z0;
 #pragma unroll
-                    for (int q = 0; q < KC; ++q) {
-                        const float c = ty * (float)(j0 + q);
-                        dyq[q] = invj[q] > 0.0f ? __builtin_amdgcn_sinf(c - floorf(c)) * iy * invj[q] : 1.0f;
-                    }
+                for (int q = M - 1; q >= 0; --q) {
+                    z = cmul(z, dn);
+                    h[q].x += z.x;
+                    h[q].y += z.y;
                 }
+                continue;
             }
+            // sinc(2 pi j t) = sin(2 pi j t) / (2 pi j t), t = b df u / c turns per frequency step, the
+            // sine straight from the hardware (argument reduced to a turn); 1 / j^2 of both axes
+            // comes last.  In a direction of exactly zero j stands for the sine.
+            const float tx = (float)(a.bx_df_c * dx) * rinv, ty = (float)(a.by_df_c * dy) * rinv;
+            float d[KC];
+            {
+                float s[KC];
 #pragma unroll
-            for (int q = 0; q < KC; ++q) {
-                const float d = dxq[q] * dyq[q];
-                h[q].x = fmaf(z.x, d, h[q].x);
-                h[q].y = fmaf(z.y, d, h[q].y);
-                z = cmul(z, st);
+                for (int q = 0; q < KC; ++q) {
+                    const float c = tx * (float)(j0 + q);
+                    d[q] = __builtin_amdgcn_sinf(c - floorf(c));
+                }
+#pragma unroll
+                for (int q = 0; q < KC; ++q) {
+                    const float c = ty * (float)(j0 + q);
+                    s[q] = __builtin_amdgcn_sinf(c - floorf(c));
+                }
+                if (tx == 0.0f) {
+#pragma unroll
+                    for (int q = 0; q < KC; ++q) d[q] = (float)(j0 + q);
+                }
+                if (ty == 0.0f) {
+#pragma unroll
+                    for (int q = 0; q < KC; ++q) s[q] = (float)(j0 + q);
+                }
+#pragma unroll
+                for (int q = 0; q < KC; ++q) d[q] *= s[q];
+            }
+            g *= __builtin_amdgcn_rcpf((tx != 0.0f ? (float)TWO_PI * tx : 1.0f) * (ty != 0.0f ? (float)TWO_PI * ty : 1.0f));
+            float2 z = make_float2(zm.x * g, zm.y * g);
+            const float2 z0 = z;
+#pragma unroll
+            for (int q = M; q < KC; ++q) {
+                h[q].x = fmaf(z.x, d[q], h[q].x);
+                h[q].y = fmaf(z.y, d[q], h[q].y);
+                z = cmul(z, up);
+            }
+            z = z0;
+#pragma unroll
+            for (int q = M - 1; q >= 0; --q) {
+                z = cmul(z, dn);
+                h[q].x = fmaf(z.x, d[q], h[q].x);
+                h[q].y = fmaf(z.y, d[q], h[q].y);
             }
         }
     }
+    if (a.dir) {
+#pragma unroll
+        for (int q = 0; q < KC; ++q) {
+            h[q].x *= invj2[q];
+            h[q].y *= invj2[q];
+        }
+    }
+    if (j0 == 0) h[0] = make_float2(h0, 0.0f);
 }
 
-__device__ __forceinline__ void chunk_invj(const FdArgs& a, int j0, float* invj) {
+__device__ __forceinline__ void chunk_invj2(int j0, float* invj2) {
 #pragma unroll
-    for (int q = 0; q < KC; ++q) invj[q] = (j0 + q) > 0 ? 1.0f / (float)(j0 + q) : 0.0f;
+    for (int q = 0; q < KC; ++q) invj2[q] = 1.0f / ((float)max(1, j0 + q) * (float)max(1, j0 + q));
 }
 
 // Transmit field T_a(s, f) of one chunk of frequencies; lane = scatterer.
+template <int NA>
 __global__ void __launch_bounds__(FD_THREADS) fd_tx_kernel(const FdArgs a) {
-    __shared__ float2 etab[EB][AG][KC];
-    const int kc0 = blockIdx.y * KC;
-    const int j0 = a.j_lo + kc0;
-    const int nq = min(KC, a.K - kc0);
-    const int64_t sl = (int64_t)blockIdx.x * FD_THREADS + threadIdx.x;
+    constexpr int W = FD_THREADS / 64;
+    constexpr int TAB = EB * KC * NA, SUM = 64 * KC * NA;   // float2
+    __shared__ float2 lds[W * TAB > SUM ? W * TAB : SUM];
+    const int chunk = blockIdx.y, fr = blockIdx.z;
+    const int j0 = a.j_lo + chunk * KC;
+    const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t sl = (int64_t)blockIdx.x * 64 + l;
     const bool valid = sl < a.ns;
     double sx = 0.0, sy = 0.0, sz = 1.0;
     if (valid) {
-        const float* p = a.pos + 3 * (a.s0 + sl);
+        const float* p = a.pos + fr * a.pos_stride + 3 * (a.s0 + sl);
         sx = p[0];
         sy = p[1];
         sz = p[2];
     }
     const bool live = valid && sz > 0.0;
     if (!live) sz = 1.0;
-    float invj[KC];
-    chunk_invj(a, j0, invj);
-    float2 acc[KC][AG];
+    const double sz2 = sz * sz;
+    float invj2[KC];
+    chunk_invj2(j0, invj2);
+    float2 acc[KC][NA];
 #pragma unroll
     for (int q = 0; q < KC; ++q)
 #pragma unroll
-        for (int g = 0; g < AG; ++g) acc[q][g] = make_float2(0.f, 0.f);
+        for (int g = 0; g < NA; ++g) acc[q][g] = make_float2(0.f, 0.f);
 
-    for (int e0 = 0; e0 < a.n_elem; e0 += EB) {
-        __syncthreads();
-        for (int i = threadIdx.x; i < EB * AG * KC; i += FD_THREADS) {
-            const int el = i / (AG * KC), g = (i / KC) % AG, q = i % KC;
+    float2* tab = lds + w * TAB;   // [EB][KC][NA] of this wavefront
+    for (int e0 = w * EB; e0 < a.n_elem; e0 += W * EB) {
+        __builtin_amdgcn_wave_barrier();
+        for (int i = l; i < TAB; i += 64) {
+            const int el = i / (KC * NA), q = (i / NA) % KC, g = i % NA;
             const int e = e0 + el;
             float2 v = make_float2(0.f, 0.f);
-            if (e < a.n_elem && g < a.na && q < nq) {
+            if (e < a.n_elem) {
                 double ex, ey;
                 elem_xy(a, e, ex, ey);
                 const double dtau = (a.ux[g] * ex + a.uy[g] * ey) * a.inv_c - a.t0[g];
@@ -182,92 +239,96 @@ __global__ void __launch_bounds__(FD_THREADS) fd_tx_kernel(const FdArgs a) {
                 v.x *= wgt;
                 v.y *= wgt;
             }
-            etab[el][g][q] = v;
+            tab[i] = v;
         }
-        __syncthreads();
+        __builtin_amdgcn_wave_barrier();
         const int ne = min(EB, a.n_elem - e0);
         for (int el = 0; el < ne; ++el) {
             double ex, ey;
             elem_xy(a, e0 + el, ex, ey);
             float2 h[KC];
-            elem_resp(a, ex, ey, sx, sy, sz, j0, invj, h);
+            elem_resp(a, sx - ex, sy - ey, sz2, j0, invj2, h);
 #pragma unroll
             for (int q = 0; q < KC; ++q)
 #pragma unroll
-                for (int g = 0; g < AG; ++g) {
-                    const float2 E = etab[el][g][q];
+                for (int g = 0; g < NA; ++g) {
+                    const float2 E = tab[(el * KC + q) * NA + g];
                     acc[q][g].x = fmaf(h[q].x, E.x, fmaf(-h[q].y, E.y, acc[q][g].x));
                     acc[q][g].y = fmaf(h[q].x, E.y, fmaf(h[q].y, E.x, acc[q][g].y));
                 }
         }
     }
-    if (!valid) return;
+    // the wavefronts' sums, in order; lane-minor, so that a wavefront's accesses are contiguous
+    for (int turn = 0; turn < W; ++turn) {
+        __syncthreads();
+        if (w == turn) {
 #pragma unroll
-    for (int q = 0; q < KC; ++q) {
-        if (q < nq) {
-            float2* dst = a.T + ((int64_t)(kc0 + q) * a.nsb + sl) * AG;
+            for (int q = 0; q < KC; ++q)
 #pragma unroll
-            for (int g = 0; g < AG; ++g) dst[g] = live ? acc[q][g] : make_float2(0.f, 0.f);
+                for (int g = 0; g < NA; ++g) {
+                    float2& s = lds[(q * NA + g) * 64 + l];
+                    s = turn ? make_float2(s.x + acc[q][g].x, s.y + acc[q][g].y) : acc[q][g];
+                }
         }
     }
+    __syncthreads();
+    const int row = min(KC, a.K - chunk * KC) * NA;
+    float2* dst = a.T + ((int64_t)fr * a.K + chunk * KC) * a.nsb * NA + (int64_t)blockIdx.x * 64 * row;
+    const int n = (int)min((int64_t)64, a.ns - (int64_t)blockIdx.x * 64);
+    // (dead scatterers' fields are not used: their echo is skipped)
+    for (int i = threadIdx.x; i < n * row; i += FD_THREADS) dst[i] = lds[(i % row) * 64 + i / row];
 }
 
 // Echo P_a(m, f) of one chunk of frequencies and one scatterer split; lane = element.
+template <int NA>
 __global__ void __launch_bounds__(FD_THREADS) fd_rx_kernel(const FdArgs a) {
     __shared__ float4 spos[SB];
-    __shared__ float2 xs[SB][KC][AG];
-    const int kc0 = blockIdx.y * KC;
-    const int j0 = a.j_lo + kc0;
-    const int nq = min(KC, a.K - kc0);
-    const int m = blockIdx.x * FD_THREADS + threadIdx.x;
-    const int split = blockIdx.z;
+    __shared__ float2 xs[SB * KC * NA];
+    const int chunk = blockIdx.y, fr = blockIdx.z / a.nsplit, split = blockIdx.z % a.nsplit;
+    const int j0 = a.j_lo + chunk * KC;
+    const int m = blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t per = (a.ns + a.nsplit - 1) / a.nsplit;
     const int64_t sb0 = split * per;
     const int64_t sb1 = a.ns < sb0 + per ? a.ns : sb0 + per;
+    const float* pos = a.pos + fr * a.pos_stride + 3 * a.s0;
+    const float* amp = a.amp + a.s0;
+    const int row = min(KC, a.K - chunk * KC) * NA;
+    const float2* T = a.T + ((int64_t)fr * a.K + chunk * KC) * a.nsb * NA;
     double ex = 0.0, ey = 0.0;
     if (m < a.n_elem) elem_xy(a, m, ex, ey);
-    float invj[KC];
-    chunk_invj(a, j0, invj);
-    float2 acc[KC][AG];
+    float invj2[KC];
+    chunk_invj2(j0, invj2);
+    float2 acc[KC][NA];
 #pragma unroll
     for (int q = 0; q < KC; ++q)
 #pragma unroll
-        for (int g = 0; g < AG; ++g) acc[q][g] = make_float2(0.f, 0.f);
+        for (int g = 0; g < NA; ++g) acc[q][g] = make_float2(0.f, 0.f);
 
     for (int64_t b = sb0; b < sb1; b += SB) {
         const int nb = sb1 - b < SB ? (int)(sb1 - b) : SB;
         __syncthreads();
-        for (int i = threadIdx.x; i < SB; i += FD_THREADS) {
-            float4 v = make_float4(0.f, 0.f, -1.f, 0.f);
-            if (i < nb) {
-                const float* p = a.pos + 3 * (a.s0 + b + i);
-                v = make_float4(p[0], p[1], p[2], a.amp[a.s0 + b + i]);
-            }
-            spos[i] = v;
+        for (int i = threadIdx.x; i < nb; i += blockDim.x) {
+            const float* p = pos + 3 * (b + i);
+            spos[i] = make_float4(p[0], p[1], p[2], 0.f);
         }
-        for (int i = threadIdx.x; i < SB * KC * AG; i += FD_THREADS) {
-            const int sl = i / (KC * AG), q = (i / AG) % KC, g = i % AG;
-            float2 v = make_float2(0.f, 0.f);
-            if (sl < nb && q < nq) {
-                v = a.T[((int64_t)(kc0 + q) * a.nsb + b + sl) * AG + g];
-                const float r = a.amp[a.s0 + b + sl];
-                v.x *= r;
-                v.y *= r;
-            }
-            xs[sl][q][g] = v;
+        for (int i = threadIdx.x; i < nb * row; i += blockDim.x) {
+            const float2 v = T[b * row + i];
+            const float r = amp[b + i / row];
+            xs[i] = make_float2(v.x * r, v.y * r);
         }
         __syncthreads();
         if (m < a.n_elem) {
             for (int sl = 0; sl < nb; ++sl) {
                 const float4 p = spos[sl];
                 if (!(p.z > 0.0f)) continue;
+                const double sz = p.z;
                 float2 h[KC];
-                elem_resp(a, ex, ey, p.x, p.y, p.z, j0, invj, h);
+                elem_resp(a, (double)p.x - ex, (double)p.y - ey, sz * sz, j0, invj2, h);
 #pragma unroll
                 for (int q = 0; q < KC; ++q)
 #pragma unroll
-                    for (int g = 0; g < AG; ++g) {
-                        const float2 X = xs[sl][q][g];
+                    for (int g = 0; g < NA; ++g) {
+                        const float2 X = xs[sl * row + q * NA + g];   // (past the chunk: not stored)
                         acc[q][g].x = fmaf(h[q].x, X.x, fmaf(-h[q].y, X.y, acc[q][g].x));
                         acc[q][g].y = fmaf(h[q].x, X.y, fmaf(h[q].y, X.x, acc[q][g].y));
                     }
@@ -275,58 +336,80 @@ __global__ void __launch_bounds__(FD_THREADS) fd_rx_kernel(const FdArgs a) {
         }
     }
     if (m >= a.n_elem) return;
+    float2* dst = a.P + (((int64_t)fr * a.nsplit + split) * a.K + chunk * KC) * a.n_elem * NA + (int64_t)m * row;
 #pragma unroll
-    for (int q = 0; q < KC; ++q) {
-        if (q < nq) {
-            float2* dst = a.P + (((int64_t)split * a.K + kc0 + q) * a.n_elem + m) * AG;
+    for (int q = 0; q < KC; ++q)
 #pragma unroll
-            for (int g = 0; g < AG; ++g) {
-                float2 v = acc[q][g];
-                if (a.p_acc) {
-                    v.x += dst[g].x;
-                    v.y += dst[g].y;
+        for (int g = 0; g < NA; ++g) {
+            if (q * NA >= row) break;
+            float2 v = acc[q][g];
+            if (a.p_acc) {
+                v.x += dst[q * NA + g].x;
+                v.y += dst[q * NA + g].y;
+            }
+            dst[q * NA + g] = v;
+        }
+}
+
+// Inverse transform of NM elements of one transmit: rf(t) = sum_j Re(Q_j e^{-i 2 pi j t / N}),
+// Q_j = 2 w_j sum_split P; written to n_frames_out consecutive frames from frame0.
+template <int NM>
+__global__ void __launch_bounds__(FD_THREADS) fd_idft_kernel(const FdArgs a) {
+    extern __shared__ float2 Q[];   // [K][NM]
+    const int m0 = blockIdx.x * NM, g = blockIdx.y, fr = blockIdx.z;
+    for (int i = threadIdx.x; i < a.K * NM; i += FD_THREADS) {
+        const int kk = i / NM, m = min(m0 + i % NM, a.n_elem - 1);
+        const int c0 = kk / KC * KC, row = min(KC, a.K - c0) * a.na;
+        float2 s = make_float2(0.f, 0.f);
+        for (int sp = 0; sp < a.nsplit; ++sp) {
+            const float2 v = a.P[(((int64_t)fr * a.nsplit + sp) * a.K + c0) * a.n_elem * a.na + (int64_t)m * row +
+                                 (kk - c0) * a.na + g];
+            s.x += v.x;
+            s.y += v.y;
+        }
+        const float wk = a.w[kk];
+        Q[i] = make_float2(s.x * wk, s.y * wk);
+    }
+    __syncthreads();
+    const int an = a.a0 + g, nm = min(NM, a.n_elem - m0);
+    for (int t = threadIdx.x; t < a.T_len; t += FD_THREADS) {
+        // e^{-i 2 pi j t / N}, stepped in j; exact integer phase every 64 samples
+        const float2 st = cis_cycles(-(double)t / a.N);
+        float acc[NM];
+#pragma unroll
+        for (int c = 0; c < NM; ++c) acc[c] = 0.0f;
+        for (int k0 = 0; k0 < a.K; k0 += 64) {
+            const int64_t ph = ((int64_t)(a.j_lo + k0) * t) % a.N;
+            float2 z = cis_cycles(-(double)ph / a.N);
+            const int k1 = min(a.K, k0 + 64);
+            for (int kk = k0; kk < k1; ++kk) {
+#pragma unroll
+                for (int c = 0; c < NM; ++c) {
+                    const float2 q = Q[kk * NM + c];
+                    acc[c] = fmaf(q.x, z.x, fmaf(-q.y, z.y, acc[c]));
                 }
-                dst[g] = v;
+                z = cmul(z, st);
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < NM; ++c) {
+            if (c >= nm) break;
+            for (int f = 0; f < a.n_frames_out; ++f) {
+                float* dst = a.rf + (((int64_t)(a.frame0 + fr + f) * a.n_angles_total + an) * a.n_elem + m0 + c) * a.T_len + t;
+                *dst = a.accumulate ? *dst + acc[c] : acc[c];
             }
         }
     }
 }
 
-// Inverse transform of one (element, transmit): rf(t) = sum_j Re(Q_j e^{-i 2 pi j t / N}),
-// Q_j = 2 w_j sum_split P; written to n_frames_out consecutive frames from frame0.
-__global__ void __launch_bounds__(FD_THREADS) fd_idft_kernel(const FdArgs a) {
-    __shared__ float2 Q[FD_MAX_K];
-    const int m = blockIdx.x, g = blockIdx.y;
-    for (int kk = threadIdx.x; kk < a.K; kk += FD_THREADS) {
-        float2 s = make_float2(0.f, 0.f);
-        for (int sp = 0; sp < a.nsplit; ++sp) {
-            const float2 v = a.P[(((int64_t)sp * a.K + kk) * a.n_elem + m) * AG + g];
-            s.x += v.x;
-            s.y += v.y;
-        }
-        const float wk = a.w[kk];
-        Q[kk] = make_float2(s.x * wk, s.y * wk);
-    }
-    __syncthreads();
-    const int an = a.a0 + g;
-    for (int t = threadIdx.x; t < a.T_len; t += FD_THREADS) {
-        // e^{-i 2 pi j t / N}, stepped in j; exact integer phase every 64 samples
-        const float2 st = cis_cycles(-(double)t / a.N);
-        float acc = 0.0f;
-        float2 z = make_float2(1.f, 0.f);
-        for (int kk = 0; kk < a.K; ++kk) {
-            if ((kk & 63) == 0) {
-                const int64_t ph = ((int64_t)(a.j_lo + kk) * t) % a.N;
-                z = cis_cycles(-(double)ph / a.N);
-            }
-            const float2 q = Q[kk];
-            acc = fmaf(q.x, z.x, fmaf(-q.y, z.y, acc));
-            z = cmul(z, st);
-        }
-        for (int f = 0; f < a.n_frames_out; ++f) {
-            float* dst = a.rf + (((int64_t)(a.frame0 + f) * a.n_angles_total + an) * a.n_elem + m) * a.T_len + t;
-            *dst = a.accumulate ? *dst + acc : acc;
-        }
+using FdFn = void (*)(const FdArgs);
+template <int NA>
+FdFn fd_fn(bool tx, int na) {
+    if constexpr (NA > AG) {
+        return nullptr;
+    } else {
+        if (na == NA) return tx ? fd_tx_kernel<NA> : fd_rx_kernel<NA>;
+        return fd_fn<NA + 1>(tx, na);
     }
 }
 
@@ -342,15 +425,17 @@ __global__ void fd_weights_kernel(float* w, int K, int j_lo, int N, double df, d
 }
 
 struct FdPlan {
-    int N, j_lo, K, nsplit;
-    int64_t nsb;
-    size_t off_w, off_T, off_P, bytes;
+    int N, j_lo, K, chunks;
+    size_t off_T;      // the weights come first
+    size_t bytes;      // what the size query asks for
 };
 
 double spectrum(double f, double fc, double sig) {
     const double aa = 2.0 * M_PI * M_PI * sig * sig;
     return sig * std::sqrt(2.0 * M_PI) / 2.0 * (std::exp(-aa * (f - fc) * (f - fc)) + std::exp(-aa * (f + fc) * (f + fc)));
 }
+
+size_t field_bytes(int K, int64_t nsb, int na) { return round_up(sizeof(float2) * (size_t)K * nsb * na, 256); }
 
 FdPlan plan(const fq_probe& p, const fq_pulse& pl, const fq_fd_params& fd, int n_samples, int64_t nsb) {
     FdPlan r{};
@@ -368,20 +453,13 @@ FdPlan plan(const fq_probe& p, const fq_pulse& pl, const fq_fd_params& fd, int n
     }
     r.j_lo = lo;
     r.K = hi - lo + 1;
+    r.chunks = (r.K + KC - 1) / KC;
     const int E = p.nx_el * p.ny_el;
-    r.nsb = nsb;
-    const int wg0 = ((E + FD_THREADS - 1) / FD_THREADS) * ((r.K + KC - 1) / KC);
-    r.nsplit = (int)std::max<int64_t>(1, std::min<int64_t>({(int64_t)8, (1024 + wg0 - 1) / wg0, (nsb + SB - 1) / SB}));
-    size_t o = 0;
-    auto take = [&](size_t b) {
-        const size_t at = o;
-        o += round_up(b, 256);
-        return at;
-    };
-    r.off_w = take(sizeof(float) * r.K);
-    r.off_T = take(sizeof(float2) * (size_t)r.K * nsb * AG);
-    r.off_P = take(sizeof(float2) * (size_t)r.nsplit * r.K * E * AG);
-    r.bytes = o;
+    // one frame's buffers for AG transmits and up to 8 echo splits
+    const int wg0 = ((E + FD_THREADS - 1) / FD_THREADS) * ((r.K + 3) / 4);
+    const int nsplit = (int)std::max<int64_t>(1, std::min<int64_t>({(int64_t)8, (1024 + wg0 - 1) / wg0, (nsb + 63) / 64}));
+    r.off_T = round_up(sizeof(float) * r.K, 256);
+    r.bytes = r.off_T + field_bytes(r.K, nsb, AG) + round_up(sizeof(float2) * (size_t)nsplit * r.K * E * AG, 256);
     return r;
 }
 
@@ -440,7 +518,7 @@ extern "C" int fd_synth(const fq_probe* probe, const fq_tx* tx, const fq_pulse* 
             if (plan(*probe, *pulse, *fd, n_samples, mid).bytes <= ws_bytes) lo = mid; else hi = mid;
         }
     }
-    pl = plan(*probe, *pulse, *fd, n_samples, lo);
+    const int64_t nsb = lo;
     FQ_REQUIRE(pl.K >= 1 && pl.K <= FD_MAX_K, "frequency band of %d samples (limit %d)", pl.K, FD_MAX_K);
     char* w = reinterpret_cast<char*>(ws);
     const TxHost th = make_tx(*probe, *tx);
@@ -450,10 +528,10 @@ extern "C" int fd_synth(const fq_probe* probe, const fq_tx* tx, const fq_pulse* 
     FdArgs a{};
     a.apod = apod;
     a.T = reinterpret_cast<float2*>(w + pl.off_T);
-    a.P = reinterpret_cast<float2*>(w + pl.off_P);
-    a.w = reinterpret_cast<const float*>(w + pl.off_w);
+    a.w = reinterpret_cast<const float*>(w);
     a.rf = rf;
-    a.nsb = pl.nsb;
+    a.amp = amp;
+    a.nsb = nsb;
     a.n_elem = E;
     a.nx_el = probe->nx_el;
     a.K = pl.K;
@@ -461,7 +539,9 @@ extern "C" int fd_synth(const fq_probe* probe, const fq_tx* tx, const fq_pulse* 
     a.N = pl.N;
     a.vx = fd->n_sub_x;
     a.vy = fd->n_sub_y;
-    a.nsplit = pl.nsplit;
+    a.chunks = pl.chunks;
+    a.dir = fd->elem_width_x > 0 || fd->elem_width_y > 0;
+    a.pos_stride = pos_static ? 0 : 3 * n_scat;
     a.pitch_x = probe->pitch_x;
     a.pitch_y = probe->pitch_y;
     a.hx = 0.5 * (probe->nx_el - 1) * probe->pitch_x;
@@ -472,7 +552,7 @@ extern "C" int fd_synth(const fq_probe* probe, const fq_tx* tx, const fq_pulse* 
     a.df_c = df / probe->c_mps;
     a.bx_df_c = 0.5 * fd->elem_width_x / fd->n_sub_x * df / probe->c_mps;
     a.by_df_c = 0.5 * fd->elem_width_y / fd->n_sub_y * df / probe->c_mps;
-    a.alpha_df = fd->atten_db_cm_mhz / (20.0 * std::log10(std::exp(1.0))) * 100.0 * df / 1e6;
+    a.alpha2_df = fd->atten_db_cm_mhz / (20.0 * std::log10(2.0)) * 100.0 * df / 1e6;
     a.r_ref = (float)pulse->r_ref_m;
     a.inv_c = 1.0 / probe->c_mps;
     a.T_len = n_samples;
@@ -480,36 +560,50 @@ extern "C" int fd_synth(const fq_probe* probe, const fq_tx* tx, const fq_pulse* 
     a.accumulate = accumulate ? 1 : 0;
 
     hipLaunchKernelGGL(fd_weights_kernel, dim3((pl.K + 255) / 256), dim3(256), 0, s,
-                       reinterpret_cast<float*>(w + pl.off_w), pl.K, pl.j_lo, pl.N, df, probe->fc_hz, sig);
+                       reinterpret_cast<float*>(w), pl.K, pl.j_lo, pl.N, df, probe->fc_hz, sig);
     FQ_LAUNCH_CHECK();
     const int nfr = pos_static ? 1 : n_frames;
-    const int kchunks = (pl.K + KC - 1) / KC;
-    for (int f = 0; f < nfr; ++f) {
-        a.pos = pos + (pos_static ? 0 : (int64_t)f * n_scat * 3);
-        a.amp = amp;
-        for (int a0 = 0; a0 < A; a0 += AG) {
-            a.a0 = a0;
-            a.na = std::min(AG, A - a0);
-            for (int g = 0; g < AG; ++g) {
-                const int an = std::min(a0 + g, A - 1);
-                a.ux[g] = th.ux[an];
-                a.uy[g] = th.uy[an];
-                a.t0[g] = th.t0[an];
-            }
-            for (int64_t s0 = 0; s0 < n_scat; s0 += pl.nsb) {
+    const int rx_threads = std::min(FD_THREADS, (E + 63) / 64 * 64), rx_blocks = (E + rx_threads - 1) / rx_threads;
+    const int groups = (A + AG - 1) / AG;
+    for (int a0 = 0; a0 < A; a0 += a.na) {
+        a.a0 = a0;
+        a.na = (A + groups - 1) / groups;   // groups of equal size
+        if (a0 + a.na > A) a.na = A - a0;
+        for (int g = 0; g < a.na; ++g) {
+            a.ux[g] = th.ux[a0 + g];
+            a.uy[g] = th.uy[a0 + g];
+            a.t0[g] = th.t0[a0 + g];
+        }
+        // Frames per batch: what the workspace holds (one if the scatterers come in blocks).
+        // Echo splits: enough for about 16 wavefronts a compute unit, again if there is room.
+        const size_t t_bytes = field_bytes(pl.K, nsb, a.na), p_bytes = sizeof(float2) * (size_t)pl.K * E * a.na;
+        const size_t room = ws_bytes - pl.off_T;
+        int64_t batch = nsb >= n_scat ? std::min<int64_t>(nfr, room / (t_bytes + p_bytes)) : 1;
+        batch = std::max<int64_t>(1, std::min<int64_t>(batch, 2048));
+        batch = (nfr + (nfr + batch - 1) / batch - 1) / ((nfr + batch - 1) / batch);
+        const int64_t waves = (int64_t)rx_blocks * (rx_threads / 64) * pl.chunks * batch;
+        a.nsplit = (int)std::max<int64_t>(1, std::min<int64_t>({(int64_t)16, (4096 + waves - 1) / waves, (nsb + SB - 1) / SB,
+                                                                (int64_t)((room / batch - t_bytes) / p_bytes)}));
+        a.P = reinterpret_cast<float2*>(w + pl.off_T + batch * t_bytes);
+        for (int f = 0; f < nfr; f += (int)batch) {
+            const unsigned nb = (unsigned)std::min<int64_t>(batch, nfr - f);
+            a.pos = pos + (int64_t)f * a.pos_stride;
+            for (int64_t s0 = 0; s0 < n_scat; s0 += nsb) {
                 a.s0 = s0;
-                a.ns = std::min<int64_t>(pl.nsb, n_scat - s0);
+                a.ns = std::min<int64_t>(nsb, n_scat - s0);
                 a.p_acc = s0 > 0 ? 1 : 0;
-                hipLaunchKernelGGL(fd_tx_kernel, dim3((unsigned)((a.ns + FD_THREADS - 1) / FD_THREADS), kchunks),
+                hipLaunchKernelGGL(fd_fn<1>(true, a.na), dim3((unsigned)((a.ns + 63) / 64), pl.chunks, nb),
                                    dim3(FD_THREADS), 0, s, a);
                 FQ_LAUNCH_CHECK();
-                hipLaunchKernelGGL(fd_rx_kernel, dim3((E + FD_THREADS - 1) / FD_THREADS, kchunks, pl.nsplit),
-                                   dim3(FD_THREADS), 0, s, a);
+                hipLaunchKernelGGL(fd_fn<1>(false, a.na), dim3(rx_blocks, pl.chunks, nb * a.nsplit), dim3(rx_threads), 0,
+                                   s, a);
                 FQ_LAUNCH_CHECK();
             }
-            a.frame0 = pos_static ? 0 : f;
+            a.frame0 = f;
             a.n_frames_out = pos_static ? n_frames : 1;
-            hipLaunchKernelGGL(fd_idft_kernel, dim3(E, a.na), dim3(FD_THREADS), 0, s, a);
+            const int nm = pl.K <= MC_MAX_K ? MC : 2;
+            hipLaunchKernelGGL(nm == MC ? fd_idft_kernel<MC> : fd_idft_kernel<2>, dim3((E + nm - 1) / nm, a.na, nb),
+                               dim3(FD_THREADS), sizeof(float2) * (size_t)pl.K * nm, s, a);
             FQ_LAUNCH_CHECK();
         }
     }
