@@ -302,25 +302,9 @@ __device__ __forceinline__ double quantize(double x, double scale, double inv_sc
     return rint(x * scale) * inv_scale;
 }
 
-// step 3 on one block (rows i0 .. i0+3 of column j in this lane); a diagonal block holds
-// both triangles and adds its row sums only
-template <bool DIAG>
-__device__ __forceinline__ void rt_matvec(const double2 (&x)[4], int i0, int j, int n, int c, int lane,
-                                          const double2* v, double2* p, double scale, double inv_scale) {
-    const double2 vj = v[j];
-    double d[8];
-    double2 cs = make_double2(0.0, 0.0);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const double2 r = zmul(x[q], vj);
-        d[2 * q] = r.x;
-        d[2 * q + 1] = r.y;
-        if (!DIAG) {
-            const double2 t = zmul(zconj(x[q]), v[i0 + q]);
-            cs.x += t.x;
-            cs.y += t.y;
-        }
-    }
+// row sums d[2 q + part] and column sums cs of a block, added into p
+__device__ __forceinline__ void rt_reduce(const double (&d)[8], double2 cs, int i0, int j, int n, int c, int lane, bool diag,
+                                          double2* p, double scale, double inv_scale) {
     // row sums over the 16 lanes of this row group: halving butterfly on c, partners c ^ 8,
     // c ^ 4, c ^ 2, c ^ 1 (the row's lanes, exchanged by DPP: c ^ 8 is a rotation by 8, c ^ 4
     // a rotation by 4 for the lanes with bit 2 set and by 12 for the others)
@@ -340,7 +324,7 @@ __device__ __forceinline__ void rt_matvec(const double2 (&x)[4], int i0, int j, 
         const int idx = (b3 ? 4 : 0) + (b2 ? 2 : 0) + (b1 ? 1 : 0);
         atomicAdd(reinterpret_cast<double*>(p + i0 + (idx >> 1)) + (idx & 1), quantize(e1, scale, inv_scale));
     }
-    if (DIAG) return;
+    if (diag) return;
     // column sums over the block's 4 row groups
     cs.x = swap_sum<true>(swap_sum<false>(cs.x));
     cs.y = swap_sum<true>(swap_sum<false>(cs.y));
@@ -348,6 +332,28 @@ __device__ __forceinline__ void rt_matvec(const double2 (&x)[4], int i0, int j, 
         atomicAdd(&p[j].x, quantize(cs.x, scale, inv_scale));
         atomicAdd(&p[j].y, quantize(cs.y, scale, inv_scale));
     }
+}
+
+// step 3 on one block (rows i0 .. i0+3 of column j in this lane); a diagonal block holds
+// both triangles and adds its row sums only
+template <bool DIAG>
+__device__ __forceinline__ void rt_matvec(const double2 (&x)[4], int i0, int j, int n, int c, int lane,
+                                          const double2* v, double2* p, double scale, double inv_scale) {
+    const double2 vj = v[j];
+    double d[8];
+    double2 cs = make_double2(0.0, 0.0);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const double2 r = zmul(x[q], vj);
+        d[2 * q] = r.x;
+        d[2 * q + 1] = r.y;
+        if (!DIAG) {
+            const double2 t = zmul(zconj(x[q]), v[i0 + q]);
+            cs.x += t.x;
+            cs.y += t.y;
+        }
+    }
+    rt_reduce(d, cs, i0, j, n, c, lane, DIAG, p, scale, inv_scale);
 }
 
 // step 5 on one block: A -= v w^H + w v^H, w = tau p - hw v, for this lane's stored elements
@@ -516,6 +522,226 @@ __global__ void __launch_bounds__(RT_THREADS) tridiag_reg_kernel(const TriArgs a
                 }
             }
         }
+    }
+}
+
+// The same for n <= 128, where a wavefront has registers to spare, with one barrier a step:
+//   1. every wavefront forms w = tau p - |tau|^2 (v^H p) v / 2 of step k-1, takes its rank-2
+//      update off column k (held in LDS as step k-2 left it), and forms the reflector v, tau of
+//      column k, all redundantly: the vectors are one or two values a lane, and the chain (two
+//      wavefront sums, a square root, a division) would otherwise need a barrier at each end
+//      for the one wavefront that computes it;
+//   2. the update of step k-1 and p = A22 v in one pass over the blocks; the owners of column
+//      k+1 put it in LDS;
+//   3. the barrier: p and column k+1 are complete.
+// v and w are zero on the rows already reduced and on rows past n, which so stay as they are.
+// All wavefronts write the same v and w to the same words (each reads back its own or an equal
+// value); v and the column alternate between two buffers, p between three, so that a wavefront
+// one step ahead writes nothing that another still reads.
+// 20 frames: 33 us, 64: 134, 128: 436 (54, 180, 521 with three barriers a step).  Beyond 128
+// frames its registers would spill: 1199 us at 129 frames, 621 in the form above.
+// step 2 on one block (rows i0 .. i0+3 of column j in this lane): A -= v1 w^H + w v1^H, then its
+// part of A v; a diagonal block holds both triangles and adds its row sums only.  get and put
+// move the lane's element of row q.
+template <class Get, class Put>
+__device__ __forceinline__ void rt_block_step(Get get, Put put, int i0, int j, int n, int c, int lane, bool diag,
+                                              const double2* v1, const double2* w, const double2* v, double2* p,
+                                              double scale, double inv_scale) {
+    const double2 v1j = v1[j], wj = w[j], vj = v[j];
+    double d[8];
+    double2 cs = make_double2(0.0, 0.0);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        double2 x = get(q);
+        const double2 u1 = zmulc(v1[i0 + q], wj), u2 = zmulc(w[i0 + q], v1j);
+        x.x -= u1.x + u2.x;
+        x.y -= u1.y + u2.y;
+        put(q, x);
+        const double2 r = zmul(x, vj);
+        d[2 * q] = r.x;
+        d[2 * q + 1] = r.y;
+        const double2 t = zmul(zconj(x), v[i0 + q]);
+        cs.x += t.x;
+        cs.y += t.y;
+    }
+    rt_reduce(d, cs, i0, j, n, c, lane, diag, p, scale, inv_scale);
+}
+
+template <int RN, int W>
+__global__ void __launch_bounds__(64 * W) tridiag_step_kernel(const TriArgs a) {
+    constexpr int NBLK = (RN / 16) * (RN / 16 + 1) / 2;
+    constexpr int BPW = (NBLK + W - 1) / W;   // blocks per wavefront
+    __shared__ double2 scol[2][RN], sv[2][RN], sw[RN], sp[3][RN];
+    __shared__ double fro2_w[W];
+    const int n = a.n, tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: block bookkeeping in scalars
+    const int nbr = (n + 15) / 16;
+    const int c = lane & 15, rb = (lane >> 4) * 4;
+    for (int i = tid; i < RN; i += (64 * W)) {
+        scol[0][i] = scol[1][i] = sv[0][i] = sv[1][i] = sw[i] = sp[0][i] = sp[1][i] = sp[2][i] = make_double2(0.0, 0.0);
+    }
+    int bI[BPW], bJ[BPW];
+    double2 A[BPW][4];
+    double fro2 = 0.0;   // this lane's part of ||A||_F^2
+#pragma unroll
+    for (int s = 0; s < BPW; ++s) {
+        rt_block(wv + W * s, nbr, bI[s], bJ[s]);
+        const int j = 16 * bJ[s] + c;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int i = 16 * bI[s] + rb + q;
+            double2 x = make_double2(0.0, 0.0);
+            if (bI[s] >= 0 && i < n && j < n) {
+                // Hermitian part of the input (the Gram is Hermitian up to its own rounding)
+                const double2 g = a.G[(size_t)i * n + j], gt = a.G[(size_t)j * n + i];
+                x = i == j ? make_double2(g.x, 0.0) : make_double2(0.5 * (g.x + gt.x), 0.5 * (g.y - gt.y));
+                fro2 += (bI[s] == bJ[s] ? 1.0 : 2.0) * (x.x * x.x + x.y * x.y);
+            }
+            A[s][q] = x;
+        }
+    }
+    fro2 = wave_total(fro2);
+    if (lane == 0) fro2_w[wv] = fro2;
+    __syncthreads();
+    // element (i, j) of the blocks into LDS if it belongs to column k, rows k .. n-1
+    auto put_col = [&](int i, int j, int k, double2 x) {
+        if (j == k && i >= k && i < n) scol[k & 1][i] = x;
+    };
+#pragma unroll
+    for (int s = 0; s < BPW; ++s)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (bJ[s] == 0) put_col(16 * bI[s] + rb + q, c, 0, A[s][q]);
+    // scale 2^(51 - e) with ||A||_F < 2^(e+1): partial sums of p_i below sqrt(2) 2^(e+1) + 13 delta
+    // < 2^52.6 delta
+    double fro = 0.0;
+#pragma unroll
+    for (int w = 0; w < W; ++w) fro += fro2_w[w];
+    fro = sqrt(fro);
+    const int fe = __builtin_amdgcn_readfirstlane(fro > 0.0 ? max(ilogb(fro), -900) : 0);
+    const double scale = ldexp(1.0, 51 - fe), inv_scale = ldexp(1.0, fe - 51);
+    __syncthreads();
+    constexpr int VL = (RN + 63) / 64;   // values of a vector per lane: i = lane + 64 t
+    double2 tau = make_double2(0.0, 0.0);   // of the step before
+    auto at = [&](const double2 (&x)[VL], int i) {   // element i, i uniform
+        double2 r = make_double2(0.0, 0.0);
+#pragma unroll
+        for (int t = 0; t < VL; ++t)
+            if ((i >> 6) == t) r = make_double2(lane_f64(x[t].x, i & 63), lane_f64(x[t].y, i & 63));
+        return r;
+    };
+    int pk = 0;   // k mod 3
+    for (int k = 0; k < n; ++k) {
+        const int pn = pk == 2 ? 0 : pk + 1;
+        const double2* p1 = sp[pn == 2 ? 0 : pn + 1];   // of step k - 1
+        double2* p = sp[pk];
+        // 1. w of step k-1, column k, its reflector
+        const double2* v1 = sv[(k & 1) ^ 1];
+        double2* v = sv[k & 1];
+        double2 vl[VL], wl[VL], col[VL];
+        double pr = 0.0;
+#pragma unroll
+        for (int t = 0; t < VL; ++t) {
+            const int i = lane + 64 * t;
+            vl[t] = wl[t] = make_double2(0.0, 0.0);
+            if (64 * t < n && i < RN) {
+                vl[t] = v1[i];
+                wl[t] = p1[i];
+            }
+            pr += vl[t].x * wl[t].x + vl[t].y * wl[t].y;
+        }
+        pr = wave_total(pr);
+        const double hw = 0.5 * (tau.x * tau.x + tau.y * tau.y) * pr;
+#pragma unroll
+        for (int t = 0; t < VL; ++t) {
+            const double2 tp = zmul(tau, wl[t]);
+            const bool live = lane + 64 * t >= k;   // (p_i of a reduced row holds partial sums)
+            wl[t] = make_double2(live ? tp.x - hw * vl[t].x : 0.0, live ? tp.y - hw * vl[t].y : 0.0);
+        }
+        const double2 wk = at(wl, k), vk = at(vl, k);
+        double ps = 0.0;
+#pragma unroll
+        for (int t = 0; t < VL; ++t) {
+            const int i = lane + 64 * t;
+            col[t] = make_double2(0.0, 0.0);
+            if (64 * t < n && i < RN) {
+                col[t] = scol[k & 1][i];
+                sw[i] = wl[t];
+            }
+            const double2 u1 = zmulc(vl[t], wk), u2 = zmulc(wl[t], vk);
+            col[t].x -= u1.x + u2.x;
+            col[t].y -= u1.y + u2.y;
+            if (lane + 64 * t >= k + 2) ps += col[t].x * col[t].x + col[t].y * col[t].y;
+        }
+        const double dk = at(col, k).x;
+        if (k == n - 1) {
+            if (tid == 0) {
+                a.d[k] = dk;
+                a.e[k] = 0.0;
+            }
+            break;
+        }
+        const double sigma = wave_total(ps);
+        const double2 alpha = at(col, k + 1);
+        double2 scl = make_double2(0.0, 0.0);
+        double beta = alpha.x;
+        tau = make_double2(0.0, 0.0);
+        if (sigma > 0.0 || alpha.y != 0.0) {
+            // square root and its reciprocal from one estimate, two Newton steps each (correct to
+            // the last place or two); the other reciprocal likewise
+            const double s2 = alpha.x * alpha.x + alpha.y * alpha.y + sigma;
+            double y = __builtin_amdgcn_rsq(s2);
+            y = fma(0.5 * y, fma(-s2 * y, y, 1.0), y);
+            y = fma(0.5 * y, fma(-s2 * y, y, 1.0), y);
+            double nrm = s2 * y;
+            nrm = fma(fma(-nrm, nrm, s2), 0.5 * y, nrm);
+            beta = alpha.x >= 0.0 ? -nrm : nrm;
+            const double ib = alpha.x >= 0.0 ? -y : y;
+            tau = make_double2((beta - alpha.x) * ib, -alpha.y * ib);
+            const double2 den = make_double2(alpha.x - beta, alpha.y);   // 1 / (alpha - beta)
+            const double d2 = den.x * den.x + den.y * den.y;
+            double idd = __builtin_amdgcn_rcp(d2);
+            idd = fma(idd, fma(-d2, idd, 1.0), idd);
+            idd = fma(idd, fma(-d2, idd, 1.0), idd);
+            scl = make_double2(den.x * idd, -den.y * idd);
+        }
+        if (tid == 0) {
+            a.tau[k] = tau;
+            a.e[k] = beta;
+            a.d[k] = dk;
+        }
+#pragma unroll
+        for (int t = 0; t < VL; ++t) {
+            const int i = lane + 64 * t;
+            double2 vi = make_double2(0.0, 0.0);
+            if (i == k + 1) vi = make_double2(1.0, 0.0);
+            else if (i > k + 1) vi = zmul(col[t], scl);
+            if (64 * t < n && i < RN) {
+                v[i] = vi;
+                if (wv == t && i > k && i < n) a.vh[(size_t)k * n + i] = vi;
+            }
+        }
+        for (int i = tid; i < n; i += (64 * W)) sp[pn][i] = make_double2(0.0, 0.0);
+        __builtin_amdgcn_wave_barrier();
+        // 2. the update of step k-1 and p = A22 v (blocks with a column beyond k)
+#pragma unroll
+        for (int s = 0; s < BPW; ++s) {
+            // (opaque: addresses kept for all blocks through the whole reduction would not leave
+            // the registers for the blocks)
+            int I = bI[s], J = bJ[s];
+            asm volatile("" : "+s"(I), "+s"(J));
+            if (I < 0 || 16 * J + 15 <= k) continue;
+            const int j = 16 * J + c, i0 = 16 * I + rb;
+            rt_block_step(
+                [&](int q) { return A[s][q]; },
+                [&](int q, double2 x) {
+                    A[s][q] = x;
+                    put_col(i0 + q, j, k + 1, x);
+                },
+                i0, j, n, c, lane, I == J, v1, sw, v, p, scale, inv_scale);
+        }
+        pk = pn;
+        __syncthreads();
     }
 }
 
@@ -1403,8 +1629,10 @@ __global__ void __launch_bounds__(256) pd_kernel(const float2* iq, int64_t nv, i
 }
 
 using TriFn = void (*)(const TriArgs);
-int tri_threads(int n) { return n <= RT_N ? RT_THREADS : TRI_THREADS; }
+int tri_threads(int n) { return n <= 64 ? 256 : n <= RT_N ? RT_THREADS : TRI_THREADS; }
 TriFn tri_fn(int n) {
+    if (n <= 64) return tridiag_step_kernel<64, 4>;
+    if (n <= 128) return tridiag_step_kernel<128, 8>;
     if (n <= RT_N) return tridiag_reg_kernel;
     if (n <= 256) return tridiag_kernel<4>;
     return tridiag_kernel<FQ_MAX_NT / 64>;
