@@ -229,6 +229,7 @@ __device__ __forceinline__ floatx16 conv32b(const unsigned short* img, int t0, c
     floatx16 acc;
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
+    __builtin_amdgcn_s_setprio(1);
     acc = mfma(fb, one, acc);
 #pragma unroll
     for (int c = 0; c < K2C; ++c) {
@@ -236,6 +237,7 @@ __device__ __forceinline__ floatx16 conv32b(const unsigned short* img, int t0, c
         const u16x8 b = *reinterpret_cast<const u16x8*>(img + (t0 + j + k) * RS + ch0);
         acc = mfma(fr[c], b, acc);
     }
+    __builtin_amdgcn_s_setprio(0);
     return acc;
 }
 
@@ -485,7 +487,7 @@ constexpr int BTILE = 32 * 64;
 constexpr int BG = 6 * 64;                 // dL/dy terms [6][32]
 constexpr int BH0 = 192;                   // one copy of an input window (48 rows)
 constexpr int BWD_WAVE = BRING + 2 * BTILE + 4 * BH0;   // the terms of dL/dy share the second tile
-constexpr int BWD_FRAG = K2C * 64 * 16;
+constexpr int BWD_FRAG = K2C * 64 * 16 + 2 * CH * 4;   // dgrad fragments, W4 in FP32
 constexpr int BWD_PART = OFF_W3;           // parameters of a kernel, at most
 constexpr size_t BWD_LDS = std::max<size_t>(BWD_FRAG + BWD_WAVES * BWD_WAVE, 2 * BWD_PART * sizeof(float));
 static_assert(BWD_LDS <= 160 * 1024 && PART - OFF_W3 <= BWD_PART && BG <= BTILE, "LDS of a compute unit");
@@ -523,6 +525,8 @@ __global__ void __launch_bounds__(64 * BWD_WAVES, 1) lcf_bwd_kernel(const BwdArg
         for (int q = 0; q < 8; ++q) f[q] = a.wb[OFF_W + (o0 + q) * 288 + i * 9 + (8 - c / 2)];
         frag[it] = f;
     }
+    float* w4 = reinterpret_cast<float*>(sm + K2C * 64 * 16);   // [2][32]
+    if (threadIdx.x < 2 * CH) w4[threadIdx.x] = bf2f(a.wb[OFF_W4 + threadIdx.x]);
     __syncthreads();
     const u16x8* fr = frag + l;
     char* ring = sm + BWD_FRAG + wv * BWD_WAVE;   // dz of this layer
@@ -531,9 +535,8 @@ __global__ void __launch_bounds__(64 * BWD_WAVES, 1) lcf_bwd_kernel(const BwdArg
     char* gst = d1;                               // L = 3: dL/dy terms
     char* h0 = d1 + BTILE;                        // input window: hi, hi one row on, lo, lo one row on
 
-    // output layer: y = W4 h3 (rows 0, 1) and W4^T against the terms of dL/dy
-    u16x8 f4[2], f4t;
-    frag_out(a.wb, l, f4);
+    // output layer: W4^T against the terms of dL/dy
+    u16x8 f4t;
 #pragma unroll
     for (int e = 0; e < 8; ++e) f4t[e] = h == 0 && e < 6 ? a.wb[OFF_W4 + (e % 2) * CH + j] : (unsigned short)0;
     const float b40 = a.w[OFF_B4], b41 = a.w[OFF_B4 + 1];
@@ -690,16 +693,30 @@ __global__ void __launch_bounds__(64 * BWD_WAVES, 1) lcf_bwd_kernel(const BwdArg
                 __builtin_amdgcn_wave_barrier();
             } else {   // output layer and dz3, tile s
                 const bool live = 32 * s + j < T;
-                floatx16 yo;
+                floatx16 zero;
 #pragma unroll
-                for (int r = 0; r < 16; ++r) yo[r] = 0.0f;
-                const floatx16 zero = yo;
-                yo = mfma(f4[0], __builtin_bit_cast(u16x8, ha3), yo);
-                yo = mfma(f4[1], __builtin_bit_cast(u16x8, hb3), yo);
+                for (int r = 0; r < 16; ++r) zero[r] = 0.0f;
+                // y = W4 h3 + b4 by FMAs: its terms cancel to a hundredth of their size, and the
+                // matrix cores' truncated sums put a bias of 1e-6 on the loss
+                float y0 = 0.0f, y1 = 0.0f;
+                {
+                    const unsigned int hw[8] = {ha3.x, ha3.y, ha3.z, ha3.w, hb3.x, hb3.y, hb3.z, hb3.w};
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const float4 wa = *reinterpret_cast<const float4*>(w4 + 8 * q + 4 * h);
+                        const float4 wc = *reinterpret_cast<const float4*>(w4 + CH + 8 * q + 4 * h);
+                        const float v0 = __uint_as_float(hw[2 * q] << 16), v1 = __uint_as_float(hw[2 * q] & 0xffff0000u);
+                        const float v2 = __uint_as_float(hw[2 * q + 1] << 16), v3 = __uint_as_float(hw[2 * q + 1] & 0xffff0000u);
+                        y0 = fmaf(wa.w, v3, fmaf(wa.z, v2, fmaf(wa.y, v1, fmaf(wa.x, v0, y0))));
+                        y1 = fmaf(wc.w, v3, fmaf(wc.z, v2, fmaf(wc.y, v1, fmaf(wc.x, v0, y1))));
+                    }
+                    y0 += __shfl_xor(y0, 32);
+                    y1 += __shfl_xor(y1, 32);
+                }
                 h_store(ha3, hb3);
                 float g0 = 0.0f, g1 = 0.0f;
-                if (h == 0 && live) {   // rows 0 and 1 of column j
-                    const float e0 = yo[0] + b40 - tg.x * ir, e1 = yo[1] + b41 - tg.y * ir;
+                if (h == 0 && live) {
+                    const float e0 = y0 + b40 - tg.x * ir, e1 = y1 + b41 - tg.y * ir;
                     lossacc += e0 * e0 + e1 * e1;
                     g0 = 2.0f * e0 * a.inv_count;
                     g1 = 2.0f * e1 * a.inv_count;
