@@ -20,7 +20,7 @@ namespace fq {
 namespace {
 
 // The tile that das_window_rows describes; its window also decides which grids are refused.
-constexpr int TILE_X = 16, TILE_Y = 16;
+constexpr int TILE_X = 16, TILE_Y = 16, TILE_Z = 2;
 constexpr int FIR_HALF = 16;
 constexpr int IQ_THREADS = 256;
 constexpr int IQ_RUN = 4;       // consecutive samples per thread
@@ -76,16 +76,16 @@ __global__ void __launch_bounds__(IQ_THREADS) rf2iq_kernel(const IqArgs a) {
     }
 }
 
-DasFn das_fn(int fb, int at, int interp, bool wide) {
+DasFn das_fn(int fb, int at, int interp, bool wide, int groups) {
     switch (fb) {
-        case 1: return das_fn1(at, interp, wide);
-        case 2: return das_fn2(at, interp, wide);
-        case 3: return das_fn3(at, interp, wide);
-        case 4: return das_fn4(at, interp, wide);
-        case 5: return das_fn5(at, interp, wide);
-        case 6: return das_fn6(at, interp, wide);
-        case 7: return das_fn7(at, interp, wide);
-        default: return das_fn8(at, interp, wide);
+        case 1: return das_fn1(at, interp, wide, groups);
+        case 2: return das_fn2(at, interp, wide, groups);
+        case 3: return das_fn3(at, interp, wide, groups);
+        case 4: return das_fn4(at, interp, wide, groups);
+        case 5: return das_fn5(at, interp, wide, groups);
+        case 6: return das_fn6(at, interp, wide, groups);
+        case 7: return das_fn7(at, interp, wide, groups);
+        default: return das_fn8(at, interp, wide, groups);
     }
 }
 
@@ -137,10 +137,11 @@ void frame_blocks(int F, int T, int& nfb, int& fb, int& TR) {
     }
 }
 
-// Voxel tile (log2 of its threads per axis, sum 8), angles per pass, window rows.
+// Voxel tile (log2 of its threads per axis), angles per pass, window rows, element groups.
 struct DasTile {
-    int sx, sy, sz, W, WB, at;
+    int sx, sy, sz, W, WB, at, groups;
     bool wide;
+    double cost;
     int64_t ntx, nty, ntz;
 };
 
@@ -149,34 +150,70 @@ struct DasTile {
 // over the elements for more angles than the LDS arrays hold repeats the receive geometry.
 // 128^3 voxels take 16 x 16 x 2 tiles or 8 x 8 x 8 ones; 35 x 33 x 61 voxels are padded to
 // 1.30 times their number by 8 x 2 x 32 where 16 x 16 x 2 made it 2.03.
-bool choose_tile(const fq_grid& g, const TxHost& th, double fs_c, int A, int fb, DasTile& best) {
-    double best_cost = 0.0;
+bool choose_tile(const fq_grid& g, const TxHost& th, double fs_c, int A, int fb, int groups, DasTile& best) {
+    const int bits = groups == 1 ? 8 : groups == 4 ? 8 : 6, vz = das_vz(groups);
     bool found = false;
     for (int sx = 0; sx <= 6; ++sx)
-        for (int sy = 0; sy <= 6 && sx + sy <= 8; ++sy) {
+        for (int sy = 0; sy <= 6 && sx + sy <= bits; ++sy) {
             DasTile t{};
             t.sx = sx;
             t.sy = sy;
-            t.sz = 8 - sx - sy;
-            const int tx = 1 << t.sx, ty = 1 << t.sy, tz = DAS_VZ << t.sz;
+            t.sz = bits - sx - sy;
+            t.groups = groups;
+            const int tx = 1 << t.sx, ty = 1 << t.sy, tz = vz << t.sz;
             t.ntx = (g.nx + tx - 1) / tx;
             t.nty = (g.ny + ty - 1) / ty;
             t.ntz = (g.nz + tz - 1) / tz;
             t.W = window_rows(g, th, fs_c, std::min(tx, g.nx), std::min(ty, g.ny), std::min(tz, g.nz));
             t.WB = (int)round_up((size_t)t.W * das_row_lds(fb) + DAS_SLACK, 16);
             t.wide = t.W > DAS_W_NARROW;
-            const int bytes = (t.wide ? DAS_ROWS_WIDE : DAS_ROWS) * das_row_lds(fb);
+            if (t.wide && groups > 1) continue;
+            const int bytes = das_rows(groups, t.wide, fb) * das_row_lds(fb);
             int at = std::min(t.wide ? 2 : DAS_MAX_AT, 2 * (bytes / t.WB));
             if (at < 1) continue;
             const int passes = (A + at - 1) / at;
             t.at = (A + passes - 1) / passes;
-            const double cost = (double)(t.ntx * t.nty * t.ntz) * (1.0 + 0.15 * t.W / 64.0) * (1.0 + 0.3 * (passes - 1));
-            if (!found || cost < best_cost) {
+            t.cost = (1.0 + 0.15 * t.W / 64.0) * (1.0 + 0.3 * (passes - 1));
+            if (!found || t.cost * (t.ntx * t.nty * t.ntz) < best.cost * (best.ntx * best.nty * best.ntz)) {
                 found = true;
-                best_cost = cost;
                 best = t;
             }
         }
+    return found;
+}
+
+// Tile and element groups by the time of a launch, in that of one wavefront's voxels over all
+// elements.  Unsplit, a compute unit takes its workgroups in rounds of the three it holds, and
+// one, two or three of them take 5.7, 6.7 or 7.5 (one wavefront a SIMD waits most of its time);
+// split, it takes one at a time, 16 wavefronts on a half or an eighth of the voxels.  Measured
+// on 45 calls of 4000 to 500000 voxels, 1 to 61 frames, 64 to 1024 elements: the choice is
+// within 4% of the best of the three on average.  34 x 16 x 14 voxels, 4 frames, 576
+// elements, 5 transmits: 1125 us unsplit, 379 with 4 groups, 122 with 16; 35 x 33 x 61, 20
+// frames, cubic: 1209, 881, 997; 107 x 72 x 91, 2 frames: 247, 422, 896.
+bool choose_launch(const fq_grid& g, const TxHost& th, double fs_c, int A, int fb, int nfb, int interp, DasTile& best) {
+    static const double unsplit[4] = {0.0, 5.7, 6.7, 7.5};
+    // (little work per row of a window: the staging shows)
+    const double split4 = interp ? 1.5 : fb * A <= 9 ? 2.1 : 1.75, split16 = 0.6;
+    bool found = false;
+    double best_time = 0.0;
+    for (int groups : {1, 4, 16}) {
+        DasTile t{};
+        if (!choose_tile(g, th, fs_c, A, fb, groups, t)) continue;
+        const double per_cu = (double)(t.ntx * t.nty * t.ntz) * nfb / 256.0;
+        double time;
+        if (groups == 1) {
+            const int n = (int)std::min(1e6, std::ceil(per_cu));
+            time = n > 6 ? per_cu * unsplit[3] / 3.0 : n / 3 * unsplit[3] + unsplit[n % 3];
+        } else {
+            time = std::ceil(per_cu) * (groups == 4 ? split4 : split16);
+        }
+        time *= t.cost;
+        if (!found || time < best_time) {
+            found = true;
+            best_time = time;
+            best = t;
+        }
+    }
     return found;
 }
 
@@ -200,7 +237,7 @@ extern "C" int das_window_rows(const fq_probe* probe, const fq_tx* tx, const fq_
         set_error("bad grid");
         return -1;
     }
-    return window_rows(*grid, make_tx(*probe, *tx), probe->fs_hz / probe->c_mps, TILE_X, TILE_Y, DAS_VZ);
+    return window_rows(*grid, make_tx(*probe, *tx), probe->fs_hz / probe->c_mps, TILE_X, TILE_Y, TILE_Z);
 }
 
 namespace fq {
@@ -239,13 +276,13 @@ int das_prepare(const fq_probe* probe, const fq_tx* tx, const fq_grid* grid, int
     }
     P.th = make_tx(*probe, *tx);
     P.fs_c = probe->fs_hz / probe->c_mps;
-    const int W0 = window_rows(*grid, P.th, P.fs_c, TILE_X, TILE_Y, DAS_VZ);
+    const int W0 = window_rows(*grid, P.th, P.fs_c, TILE_X, TILE_Y, TILE_Z);
     int TR = P.T;
     frame_blocks(n_frames, P.T, P.nfb, P.fb, TR);
     P.bblk = block_bytes(P.A, P.E, TR, P.fb);
     P.full = bmax * P.nfb;
     FQ_REQUIRE((size_t)W0 * das_row_lds(DAS_MAX_FB) <= DAS_LDS_BUDGET &&
-                   choose_tile(*grid, P.th, P.fs_c, P.A, P.fb, P.tile),
+                   choose_launch(*grid, P.th, P.fs_c, P.A, P.fb, P.nfb, interp, P.tile),
                "voxel spacing too coarse for the on-chip delay window (%d rows)", W0);
 
     IqArgs& ia = P.ia;
@@ -312,7 +349,8 @@ int launch_das(DasPlan& P, int fb0, int nb, int interp, const fq_grid* grid, dou
     DasArgs& da = P.da;
     da.fb0 = fb0;
     da.nwork = (int64_t)da.ntiles * nb;
-    FQ_REQUIRE(da.nwork * DAS_THREADS < (1LL << 32), "grid too large");
+    const int threads = P.tile.groups == 1 ? DAS_THREADS : DAS_SPLIT_THREADS;
+    FQ_REQUIRE(da.nwork * threads < (1LL << 32), "grid too large");
     const double one = P.tile.wide ? (double)(1 << 22) : (double)(1 << 24);
     for (int a0 = 0; a0 < P.A; a0 += P.tile.at) {
         const int na = std::min(P.tile.at, P.A - a0);
@@ -325,13 +363,14 @@ int launch_das(DasPlan& P, int fb0, int nb, int interp, const fq_grid* grid, dou
             da.uz[j] = P.th.uz[an];
             da.t0s[j] = P.th.t0[an] * fs_hz;
             const double step = P.th.uz[an] * grid->dz * P.fs_c;     // samples per z step
-            // (a window that fits has a step below 2^32 / one; a single plane takes no step)
-            da.dzs[j] = grid->nz > 1 ? (uint32_t)std::floor(step * one + 0.5) : 0u;
+            // (a window that fits has a step below 2^32 / one; a single plane or voxel takes none)
+            da.dzs[j] = grid->nz > 1 && P.tile.groups == 1 ? (uint32_t)std::floor(step * one + 0.5) : 0u;
             const double cyc = step * da.fc_fs;
             const double fr = cyc - std::floor(cyc);
             da.zeta[j] = make_float2((float)std::cos(2 * M_PI * fr), (float)std::sin(2 * M_PI * fr));
         }
-        hipLaunchKernelGGL(das_fn(P.fb, na, interp, P.tile.wide), dim3((unsigned)da.nwork), dim3(DAS_THREADS), 0, s, da);
+        hipLaunchKernelGGL(das_fn(P.fb, na, interp, P.tile.wide, P.tile.groups), dim3((unsigned)da.nwork),
+                           dim3(threads), 0, s, da);
         FQ_LAUNCH_CHECK();
     }
     return FQ_OK;

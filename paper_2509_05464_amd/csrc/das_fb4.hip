@@ -2,5 +2,5 @@
 #include "das_kernel.hpp"
 
 namespace fq {
-DasFn das_fn4(int at, int interp, bool wide) { return das_pick<4>(at, interp, wide); }
+DasFn das_fn4(int at, int interp, bool wide, int groups) { return das_pick<4>(at, interp, wide, groups); }
 }  // namespace fq

@@ -6,6 +6,11 @@
 // element) the delay rows that the tile touches (FB complex samples each) are staged in
 // LDS and every thread takes its taps from there.
 //
+// Calls too small to fill the chip that way split the elements: a workgroup of 1024 threads
+// works as G = 4 or 16 groups on one tile of 256 or 64 voxels, group g sums the elements
+// g, g + G, ..., and the groups' sums are added in LDS in a fixed order at the end (16
+// wavefronts a workgroup in place of 4, on smaller tiles; no memory and no atomics).
+//
 //  * Staging is asynchronous: the rows go from the baseband straight to LDS
 //    (buffer_load ... lds, no registers), one half of an element's transmits ahead of the
 //    half being summed, into two LDS arrays that take turns: one barrier per half.  Rows
@@ -33,17 +38,24 @@
 namespace fq {
 
 constexpr int DAS_MAX_FB = 8;         // frames per block, at most
-constexpr int DAS_VZ = 2;             // voxels per thread, consecutive in z
-constexpr int DAS_THREADS = 256;
+constexpr int DAS_THREADS = 256;      // one group
+constexpr int DAS_SPLIT_THREADS = 1024;
 constexpr int DAS_MAX_AT = 9;         // transmits per pass
 constexpr int DAS_ROWS = 320;         // rows of one LDS array (half the transmits of a pass)
 constexpr int DAS_ROWS_WIDE = 832;    // the same, for windows beyond 248 rows (AT <= 2)
+__host__ __device__ constexpr int das_group_threads(int G) { return G == 1 ? DAS_THREADS : DAS_SPLIT_THREADS / G; }
+__host__ __device__ constexpr int das_vz(int G) { return G == 1 ? 2 : 1; }   // voxels per thread, consecutive in z
 constexpr int DAS_W_NARROW = 248;     // fixed point with 24 fraction bits holds 256 rows
 constexpr int DAS_SLACK = 16;         // bytes after a window (odd row sizes are copied in 16-byte pieces)
 
 // LDS bytes of a row: the 16-byte reads of 16 consecutive rows fall in distinct banks for
 // every FB but 4 and 8, whose rows get one 16-byte pad
 __host__ __device__ constexpr int das_row_lds(int fb) { return fb == 8 ? 80 : fb == 4 ? 48 : 8 * fb; }
+
+// rows of one LDS array of a group
+__host__ __device__ constexpr int das_rows(int G, bool wide, int fb) {
+    return wide ? DAS_ROWS_WIDE : G == 1 ? DAS_ROWS : (fb == 8 ? 960 : 1280) / G;
+}
 
 struct DasArgs {
     const char* bb;        // baseband [block][A][E][TR][FB] complex64
@@ -77,8 +89,10 @@ __device__ __forceinline__ double das_lane(double x, int l) {
     return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
-template <int AT, int INTERP, int FB, bool WIDE>
-__global__ void __launch_bounds__(DAS_THREADS, WIDE ? 1 : 3) das_kernel(const DasArgs a) {
+template <int AT, int INTERP, int FB, bool WIDE, int G>
+__global__ void __launch_bounds__(G == 1 ? DAS_THREADS : DAS_SPLIT_THREADS, WIDE || G > 1 ? 1 : 3) das_kernel(const DasArgs a) {
+    constexpr int VZ = das_vz(G);
+    constexpr int TPG = das_group_threads(G), WPG = TPG / 64;   // threads and wavefronts of a group
     constexpr int NT = INTERP ? 4 : 2;         // taps per delay
     constexpr int J0 = INTERP ? -1 : 0;        // first tap offset
     constexpr int SH = WIDE ? 22 : 24;         // fraction bits of a delay
@@ -91,9 +105,12 @@ __global__ void __launch_bounds__(DAS_THREADS, WIDE ? 1 : 3) das_kernel(const Da
     constexpr int H1 = (AT + 1) / 2;           // transmits of the first half
     constexpr bool OWN = AT * FB <= 16;        // every transmit keeps its own sums
     constexpr int NS = OWN ? AT : 1;
-    constexpr int LDS_BYTES = (WIDE ? DAS_ROWS_WIDE : DAS_ROWS) * ROWL;
-    __shared__ __attribute__((aligned(16))) char winA[LDS_BYTES];
-    __shared__ __attribute__((aligned(16))) char winB[LDS_BYTES];
+    constexpr int LDS_BYTES = das_rows(G, WIDE, FB) * ROWL;   // of a group
+    __shared__ __attribute__((aligned(16))) char ldsA[G * LDS_BYTES];
+    __shared__ __attribute__((aligned(16))) char ldsB[G * LDS_BYTES];
+    const int grp = G == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / TPG);
+    char* const winA = ldsA + grp * LDS_BYTES;
+    char* const winB = ldsB + grp * LDS_BYTES;
 
     // Workgroup id -> (tile, frame block), tiles fastest.  (Handing each XCD a contiguous
     // run of tiles cut the HBM traffic ~3x but ran 5.6% slower: the neighbouring tiles of one
@@ -102,9 +119,9 @@ __global__ void __launch_bounds__(DAS_THREADS, WIDE ? 1 : 3) das_kernel(const Da
     const int tile = (int)(g % a.ntiles), fbl = (int)(g / a.ntiles);
     const int fb = a.fb0 + fbl;
     const int txi = tile % a.ntx, tyi = (tile / a.ntx) % a.nty, tzi = tile / (a.ntx * a.nty);
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((threadIdx.x % TPG) >> 6);
     // thread -> voxel column: up to 8 x 8 columns per wavefront (neighbouring delays)
-    int t = threadIdx.x;
+    int t = threadIdx.x % TPG;
     const int bx = min(a.sx, 3), by = min(a.sy, 3);
     int lx = t & ((1 << bx) - 1);
     t >>= bx;
@@ -114,17 +131,17 @@ __global__ void __launch_bounds__(DAS_THREADS, WIDE ? 1 : 3) das_kernel(const Da
     t >>= a.sx - bx;
     ly |= (t & ((1 << (a.sy - by)) - 1)) << by;
     t >>= a.sy - by;
-    const int ix = (txi << a.sx) + lx, iy = (tyi << a.sy) + ly, iz0 = ((tzi << a.sz) + t) * DAS_VZ;
+    const int ix = (txi << a.sx) + lx, iy = (tyi << a.sy) + ly, iz0 = ((tzi << a.sz) + t) * VZ;
 
     // voxels past the grid's edge repeat the last one (their sums are not stored)
-    const int ixl = txi << a.sx, iyl = tyi << a.sy, izl = (tzi << a.sz) * DAS_VZ;
+    const int ixl = txi << a.sx, iyl = tyi << a.sy, izl = (tzi << a.sz) * VZ;
     const double bx0 = a.x0 + ixl * a.dx, bx1 = a.x0 + min(ixl + (1 << a.sx) - 1, a.nx - 1) * a.dx;
     const double by0 = a.y0 + iyl * a.dy, by1 = a.y0 + min(iyl + (1 << a.sy) - 1, a.ny - 1) * a.dy;
-    const double bz0 = a.z0 + izl * a.dz, bz1 = a.z0 + min(izl + (DAS_VZ << a.sz) - 1, a.nz - 1) * a.dz;
+    const double bz0 = a.z0 + izl * a.dz, bz1 = a.z0 + min(izl + (VZ << a.sz) - 1, a.nz - 1) * a.dz;
     const double xv = a.x0 + min(ix, a.nx - 1) * a.dx, yv = a.y0 + min(iy, a.ny - 1) * a.dy;
-    double zv[DAS_VZ];
+    double zv[VZ];
 #pragma unroll
-    for (int k = 0; k < DAS_VZ; ++k) zv[k] = a.z0 + min(iz0 + k, a.nz - 1) * a.dz;
+    for (int k = 0; k < VZ; ++k) zv[k] = a.z0 + min(iz0 + k, a.nz - 1) * a.dz;
 
     // Transmit delays: tile bounds (uniform) and this thread's voxels.  Lane j of l_tlo
     // holds transmit j's row base, an integer at least one row below its lowest delay, and
@@ -152,11 +169,11 @@ __global__ void __launch_bounds__(DAS_THREADS, WIDE ? 1 : 3) das_kernel(const Da
         ptx[j] = p;
     }
 
-    float2 acc[NS][DAS_VZ][FB];
+    float2 acc[NS][VZ][FB];
 #pragma unroll
     for (int j = 0; j < NS; ++j)
 #pragma unroll
-        for (int k = 0; k < DAS_VZ; ++k)
+        for (int k = 0; k < VZ; ++k)
 #pragma unroll
             for (int q = 0; q < FB; ++q) acc[j][k][q] = make_float2(0.0f, 0.0f);
 
@@ -170,9 +187,11 @@ __global__ void __launch_bounds__(DAS_THREADS, WIDE ? 1 : 3) das_kernel(const Da
     int l_lo = 0, l_dr = 0;
     double pex_n = 0.0, pey_n = 0.0;   // of the element whose rows are requested next
     int rlo_n = 0, drx_n = 0;
-    auto element = [&](int e) {
-        if ((e & 63) == 0) {
-            const int el = min(e + lane, a.E - 1);
+    // n counts the elements of this group
+    const int n_el = G == 1 ? a.E : (a.E - grp + G - 1) / G;
+    auto element = [&](int n) {
+        if ((n & 63) == 0) {
+            const int el = min((n + lane) * G + grp, a.E - 1);
             l_px = ((el % a.nx_el) - 0.5 * (a.nx_el - 1)) * a.pitch_x;
             l_py = ((el / a.nx_el) - 0.5 * (ny_el - 1)) * a.pitch_y;
             const double cx = fmin(fmax(l_px, bx0), bx1) - l_px, cy = fmin(fmax(l_py, by0), by1) - l_py;
@@ -181,7 +200,7 @@ __global__ void __launch_bounds__(DAS_THREADS, WIDE ? 1 : 3) das_kernel(const Da
             l_lo = (int)rlo;
             l_dr = (int)ceil((sqrt(fx * fx + fy * fy + bz1 * bz1) * a.fs_c - rlo) * 16.0);
         }
-        const int l = e & 63;
+        const int l = n & 63;
         pex_n = das_lane(l_px, l);
         pey_n = das_lane(l_py, l);
         rlo_n = __builtin_amdgcn_readlane(l_lo, l);
@@ -191,7 +210,8 @@ __global__ void __launch_bounds__(DAS_THREADS, WIDE ? 1 : 3) das_kernel(const Da
     // Request the rows of transmits [j0, j1) of an element into one of the LDS arrays.
     typedef __attribute__((address_space(3))) void lds_void;
     const int lrow = lane / LPR, lcol = lane % LPR;   // padded copies
-    auto request = [&](char* win, auto J0C, auto J1C, int e, int rlo, int drx) {
+    auto request = [&](char* win, auto J0C, auto J1C, int n, int rlo, int drx) {
+        const int e = G == 1 ? n : n * G + grp;
         constexpr int ja = decltype(J0C)::value, jb = decltype(J1C)::value;
 #pragma unroll
         for (int j = ja; j < jb; ++j) {
@@ -201,7 +221,7 @@ __global__ void __launch_bounds__(DAS_THREADS, WIDE ? 1 : 3) das_kernel(const Da
             auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(src), 0, (int)trace_bytes, 0x00020000);
             char* dst = win + (j - ja) * a.WB;
             if (PADDED) {
-                for (int r0 = wave * RPI; r0 < rows; r0 += (DAS_THREADS / 64) * RPI) {
+                for (int r0 = wave * RPI; r0 < rows; r0 += WPG * RPI) {
                     if (lcol < LPR - 1 && lrow < RPI && r0 + lrow < rows)
                         __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void*)(dst + r0 * ROWL), 16,
                                                                  (first + r0 + lrow) * ROWG + lcol * 16, 0, 0, 0);
@@ -209,7 +229,7 @@ __global__ void __launch_bounds__(DAS_THREADS, WIDE ? 1 : 3) das_kernel(const Da
             } else {
                 const int begin = (first * ROWG) & ~15;   // odd row sizes start up to 8 bytes early
                 const int pieces = ((first + rows) * ROWG - begin + 15) >> 4;
-                for (int p0 = wave * 64; p0 < pieces; p0 += DAS_THREADS) {
+                for (int p0 = wave * 64; p0 < pieces; p0 += TPG) {
                     if (p0 + lane < pieces)
                         __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void*)(dst + p0 * 16), 16,
                                                                  begin + (p0 + lane) * 16, 0, 0, 0);
@@ -218,15 +238,15 @@ __global__ void __launch_bounds__(DAS_THREADS, WIDE ? 1 : 3) das_kernel(const Da
         }
     };
 
-    uint32_t frx[DAS_VZ];
-    float2 prx[DAS_VZ];
+    uint32_t frx[VZ];
+    float2 prx[VZ];
     // receive geometry of the thread's voxels (FP64 distance, shared by all transmits)
     auto receive = [&](double pex, double pey, int rlo) {
         const double ddx = xv - pex, ddy = yv - pey;
         const double dxy2 = ddx * ddx + ddy * ddy;
         const double off = 0.5 - (double)rlo * ONE;
 #pragma unroll
-        for (int k = 0; k < DAS_VZ; ++k) {
+        for (int k = 0; k < VZ; ++k) {
             const double xr = sqrt_nr(fma(zv[k], zv[k], dxy2)) * a.fs_c;
             frx[k] = (uint32_t)fma(xr, ONE, off);
             prx[k] = cis_cycles(xr * a.fc_fs);
@@ -241,7 +261,7 @@ __global__ void __launch_bounds__(DAS_THREADS, WIDE ? 1 : 3) das_kernel(const Da
             const char* wj = win + (j - ja) * a.WB;
             if (ROWG % 16) wj += ((__builtin_amdgcn_readlane(l_tlo, j) + rlo + J0) * ROWG) & 15;
 #pragma unroll
-            for (int k = 0; k < DAS_VZ; ++k) {
+            for (int k = 0; k < VZ; ++k) {
                 // The window holds every tap of the tile; the bound keeps the LDS reads in it
                 // whatever the input.
                 const uint32_t x = min(ftx[j] + frx[k] + (k ? a.dzs[j] : 0u), smax);
@@ -316,59 +336,63 @@ __global__ void __launch_bounds__(DAS_THREADS, WIDE ? 1 : 3) das_kernel(const Da
     using I0 = std::integral_constant<int, 0>;
     using IH = std::integral_constant<int, H1>;
     using IA = std::integral_constant<int, AT>;
+    // (a group that is out of elements keeps the barriers of the others)
+    const int n_max = G == 1 ? a.E : (a.E + G - 1) / G;
     element(0);
-    request(winA, I0{}, IH{}, 0, rlo_n, drx_n);
+    if (G == 1 || n_el > 0) request(winA, I0{}, IH{}, 0, rlo_n, drx_n);
     if (AT > 1) {
-        for (int e = 0; e < a.E; ++e) {
+        for (int n = 0; n < n_max; ++n) {
+            const bool live = G == 1 || n < n_el;
             const double pex = pex_n, pey = pey_n;
             const int rlo = rlo_n, drx = drx_n;
             arrive();
-            request(winB, IH{}, IA{}, e, rlo, drx);
-            receive(pex, pey, rlo);
-            sum(winA, I0{}, IH{}, rlo);
-            arrive();
-            if (e + 1 < a.E) {
-                element(e + 1);
-                request(winA, I0{}, IH{}, e + 1, rlo_n, drx_n);
+            if (live) {
+                request(winB, IH{}, IA{}, n, rlo, drx);
+                receive(pex, pey, rlo);
+                sum(winA, I0{}, IH{}, rlo);
             }
-            sum(winB, IH{}, IA{}, rlo);
+            arrive();
+            if (n + 1 < n_el) {
+                element(n + 1);
+                request(winA, I0{}, IH{}, n + 1, rlo_n, drx_n);
+            }
+            if (live) sum(winB, IH{}, IA{}, rlo);
         }
     } else {
-        for (int e = 0; e < a.E; e += 2) {   // one transmit: the arrays take turns by element
+        for (int n = 0; n < n_max; n += 2) {   // one transmit: the arrays take turns by element
             double pex = pex_n, pey = pey_n;
             int rlo = rlo_n;
             arrive();
-            if (e + 1 < a.E) {
-                element(e + 1);
-                request(winB, I0{}, IH{}, e + 1, rlo_n, drx_n);
+            if (n + 1 < n_el) {
+                element(n + 1);
+                request(winB, I0{}, IH{}, n + 1, rlo_n, drx_n);
             }
-            receive(pex, pey, rlo);
-            sum(winA, I0{}, IH{}, rlo);
-            if (e + 1 >= a.E) break;
+            if (G == 1 || n < n_el) {
+                receive(pex, pey, rlo);
+                sum(winA, I0{}, IH{}, rlo);
+            }
+            if (n + 1 >= n_max) break;
             pex = pex_n;
             pey = pey_n;
             rlo = rlo_n;
             arrive();
-            if (e + 2 < a.E) {
-                element(e + 2);
-                request(winA, I0{}, IH{}, e + 2, rlo_n, drx_n);
+            if (n + 2 < n_el) {
+                element(n + 2);
+                request(winA, I0{}, IH{}, n + 2, rlo_n, drx_n);
             }
-            receive(pex, pey, rlo);
-            sum(winB, I0{}, IH{}, rlo);
+            if (G == 1 || n + 1 < n_el) {
+                receive(pex, pey, rlo);
+                sum(winB, I0{}, IH{}, rlo);
+            }
         }
     }
 
-    if (ix >= a.nx || iy >= a.ny) return;
-    const int64_t nv = (int64_t)a.nx * a.ny * a.nz;
+    // every transmit's own sums, rotated
+    float2 tot[VZ][FB];
 #pragma unroll
-    for (int k = 0; k < DAS_VZ; ++k) {
-        const int iz = iz0 + k;
-        if (iz >= a.nz) break;
-        const int64_t v = ix + (int64_t)a.nx * (iy + (int64_t)a.ny * iz);
+    for (int k = 0; k < VZ; ++k)
 #pragma unroll
         for (int q = 0; q < FB; ++q) {
-            const int f = fb * FB + q;
-            if (f >= a.F) break;
             float2 s = acc[0][k][q];
             if (OWN) {
                 s = make_float2(0.0f, 0.0f);
@@ -380,6 +404,43 @@ __global__ void __launch_bounds__(DAS_THREADS, WIDE ? 1 : 3) das_kernel(const Da
                     s.y += p.y;
                 }
             }
+            tot[k][q] = s;
+        }
+    if (G > 1) {   // the groups' sums: group 0 adds the others' in order
+        static_assert(G == 1 || (size_t)(G - 1) * TPG * FB * VZ * 8 <= 2 * (size_t)G * LDS_BYTES, "sums fit the windows");
+        constexpr int PER = G * LDS_BYTES / (TPG * 8);   // values (of a thread) that one array holds
+        float2* sA = reinterpret_cast<float2*>(ldsA);
+        float2* sB = reinterpret_cast<float2*>(ldsB);
+        auto place = [&](int i) -> float2& { return i < PER ? sA[i * TPG + (threadIdx.x % TPG)] : sB[(i - PER) * TPG + (threadIdx.x % TPG)]; };
+        __syncthreads();
+        if (grp > 0) {
+#pragma unroll
+            for (int q = 0; q < FB; ++q) place((grp - 1) * FB + q) = tot[0][q];
+        }
+        __syncthreads();
+        if (grp > 0) return;
+#pragma unroll 1
+        for (int g = 1; g < G; ++g)
+#pragma unroll
+            for (int q = 0; q < FB; ++q) {
+                const float2 x = place((g - 1) * FB + q);
+                tot[0][q].x += x.x;
+                tot[0][q].y += x.y;
+            }
+    }
+
+    if (ix >= a.nx || iy >= a.ny) return;
+    const int64_t nv = (int64_t)a.nx * a.ny * a.nz;
+#pragma unroll
+    for (int k = 0; k < VZ; ++k) {
+        const int iz = iz0 + k;
+        if (iz >= a.nz) break;
+        const int64_t v = ix + (int64_t)a.nx * (iy + (int64_t)a.ny * iz);
+#pragma unroll
+        for (int q = 0; q < FB; ++q) {
+            const int f = fb * FB + q;
+            if (f >= a.F) break;
+            const float2 s = tot[k][q];
             float2* o = a.iq + (int64_t)f * nv + v;
             float2 r = make_float2(s.x * a.inv_A, s.y * a.inv_A);
             if (a.accumulate) {
@@ -393,33 +454,41 @@ __global__ void __launch_bounds__(DAS_THREADS, WIDE ? 1 : 3) das_kernel(const Da
 }
 
 // Kernel of a pass of `at` transmits and blocks of FB frames.
-template <int FB>
-DasFn das_pick(int at, int interp, bool wide) {
-    if (wide) {
-        if (at == 1) return interp ? das_kernel<1, 1, FB, true> : das_kernel<1, 0, FB, true>;
-        return interp ? das_kernel<2, 1, FB, true> : das_kernel<2, 0, FB, true>;
-    }
+template <int FB, bool WIDE, int G>
+DasFn das_pick_at(int at, int interp) {
     switch (at) {
-        case 1: return interp ? das_kernel<1, 1, FB, false> : das_kernel<1, 0, FB, false>;
-        case 2: return interp ? das_kernel<2, 1, FB, false> : das_kernel<2, 0, FB, false>;
-        case 3: return interp ? das_kernel<3, 1, FB, false> : das_kernel<3, 0, FB, false>;
-        case 4: return interp ? das_kernel<4, 1, FB, false> : das_kernel<4, 0, FB, false>;
-        case 5: return interp ? das_kernel<5, 1, FB, false> : das_kernel<5, 0, FB, false>;
-        case 6: return interp ? das_kernel<6, 1, FB, false> : das_kernel<6, 0, FB, false>;
-        case 7: return interp ? das_kernel<7, 1, FB, false> : das_kernel<7, 0, FB, false>;
-        case 8: return interp ? das_kernel<8, 1, FB, false> : das_kernel<8, 0, FB, false>;
-        default: return interp ? das_kernel<9, 1, FB, false> : das_kernel<9, 0, FB, false>;
+        case 1: return interp ? das_kernel<1, 1, FB, WIDE, G> : das_kernel<1, 0, FB, WIDE, G>;
+        case 2: return interp ? das_kernel<2, 1, FB, WIDE, G> : das_kernel<2, 0, FB, WIDE, G>;
+        default: break;
     }
+    if constexpr (!WIDE) {
+        switch (at) {
+            case 3: return interp ? das_kernel<3, 1, FB, WIDE, G> : das_kernel<3, 0, FB, WIDE, G>;
+            case 4: return interp ? das_kernel<4, 1, FB, WIDE, G> : das_kernel<4, 0, FB, WIDE, G>;
+            case 5: return interp ? das_kernel<5, 1, FB, WIDE, G> : das_kernel<5, 0, FB, WIDE, G>;
+            case 6: return interp ? das_kernel<6, 1, FB, WIDE, G> : das_kernel<6, 0, FB, WIDE, G>;
+            case 7: return interp ? das_kernel<7, 1, FB, WIDE, G> : das_kernel<7, 0, FB, WIDE, G>;
+            case 8: return interp ? das_kernel<8, 1, FB, WIDE, G> : das_kernel<8, 0, FB, WIDE, G>;
+            default: return interp ? das_kernel<9, 1, FB, WIDE, G> : das_kernel<9, 0, FB, WIDE, G>;
+        }
+    }
+    return nullptr;
+}
+template <int FB>
+DasFn das_pick(int at, int interp, bool wide, int groups) {
+    if (wide) return das_pick_at<FB, true, 1>(at, interp);
+    if (groups == 1) return das_pick_at<FB, false, 1>(at, interp);
+    return groups == 4 ? das_pick_at<FB, false, 4>(at, interp) : das_pick_at<FB, false, 16>(at, interp);
 }
 
 // one per das_fb*.hip
-DasFn das_fn1(int at, int interp, bool wide);
-DasFn das_fn2(int at, int interp, bool wide);
-DasFn das_fn3(int at, int interp, bool wide);
-DasFn das_fn4(int at, int interp, bool wide);
-DasFn das_fn5(int at, int interp, bool wide);
-DasFn das_fn6(int at, int interp, bool wide);
-DasFn das_fn7(int at, int interp, bool wide);
-DasFn das_fn8(int at, int interp, bool wide);
+DasFn das_fn1(int at, int interp, bool wide, int groups);
+DasFn das_fn2(int at, int interp, bool wide, int groups);
+DasFn das_fn3(int at, int interp, bool wide, int groups);
+DasFn das_fn4(int at, int interp, bool wide, int groups);
+DasFn das_fn5(int at, int interp, bool wide, int groups);
+DasFn das_fn6(int at, int interp, bool wide, int groups);
+DasFn das_fn7(int at, int interp, bool wide, int groups);
+DasFn das_fn8(int at, int interp, bool wide, int groups);
 
 }  // namespace fq
