@@ -36,3 +36,18 @@ def test_short_bands_in_the_smallest_workspace(gpu, floor):
     small = gpu_fd(4, 4, tilts, pos, amp, 300, elem_w=(0.2e-3, 0.2e-3), floor=floor, block=256)
     large = gpu_fd(4, 4, tilts, pos, amp, 300, elem_w=(0.2e-3, 0.2e-3), floor=floor, block=5000)
     assert rel_l2(small, large) < 1e-6
+
+
+@pytest.mark.parametrize('elems', [(1, 1), (8, 8), (13, 5), (16, 20), (23, 22), (23, 23)])   # one leg pair up to 512
+@pytest.mark.parametrize('n_tx', [1, 2, 3])
+def test_both_legs_in_one_workgroup(gpu, elems, n_tx):
+    """Element counts around the wavefront and the largest workgroup, 9 scatterers (one past a
+    group of four twice) with one behind the array of infinite amplitude."""
+    rng = np.random.default_rng(elems[0] + n_tx)
+    tilts = [(math.radians(a), math.radians(b)) for a, b in rng.uniform(-8, 8, (n_tx, 2))]
+    pos, amp = scatterers(9, rng, F=2)
+    behind = np.concatenate([pos, np.full((2, 1, 3), -2e-3)], axis=1)
+    got = gpu_fd(elems[0], elems[1], tilts, behind, np.concatenate([amp, [np.inf]]), 420, elem_w=(0.2e-3, 0.27e-3))
+    for f in range(2):
+        want = oracle_fd(elems[0], elems[1], tilts, pos[f], amp, 420, elem_w=(0.2e-3, 0.27e-3))
+        assert rel_l2(got[f], want) < TOL
