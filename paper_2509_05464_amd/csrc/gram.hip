@@ -453,6 +453,16 @@ Plan plan(int64_t nv, int nt, size_t max_bytes = 0) {
     return p;
 }
 
+// The least workspace that casorati_gram takes: ranges of whole multiples of 2048 voxels.  It
+// grows with n_vox up to 16384 workgroups (plan()'s ranges can shrink by a few where its chunk
+// rounds up), so that a workspace of the largest call also serves the smaller ones; with less
+// than plan() asks for, the call runs on as many ranges as fit.
+size_t least_bytes(int64_t nv, const Plan& p) {
+    const int64_t want = std::max<int64_t>(1, 16384 / p.ngroups);
+    const int64_t chunk = round_up((size_t)((nv + want - 1) / want), 2048);
+    return round_up((size_t)((nv + chunk - 1) / chunk), NXCD) * p.ntiles * 2 * GT * GT * sizeof(double);
+}
+
 }  // namespace
 }  // namespace fq
 
@@ -554,7 +564,8 @@ extern "C" int casorati_gram_noalloc(const float* iq, int64_t n_vox, int32_t n_t
 extern "C" size_t gram_workspace_size(int64_t n_vox, int32_t n_t, int32_t gram_mode) {
     (void)gram_mode;
     if (n_vox < 1 || n_t < 1) return 0;
-    return plan(n_vox, n_t).bytes;
+    const Plan p = plan(n_vox, n_t);
+    return std::max(p.bytes, least_bytes(n_vox, p));
 }
 
 extern "C" int casorati_gram(const float* iq, int64_t n_vox, int32_t n_t, int32_t gram_mode, void* ws, size_t ws_bytes,
@@ -562,10 +573,12 @@ extern "C" int casorati_gram(const float* iq, int64_t n_vox, int32_t n_t, int32_
     int st = check_gram_args(iq, n_vox, n_t, gram_mode, gram);
     if (st != FQ_OK) return st;
     FQ_REQUIRE(ws && aligned16(ws), "null or misaligned workspace");
-    const Plan p = plan(n_vox, n_t);
-    if (ws_bytes < p.bytes) {
-        set_error("workspace too small: %zu < %zu bytes", ws_bytes, p.bytes);
+    Plan p = plan(n_vox, n_t);
+    const size_t least = least_bytes(n_vox, p);
+    if (ws_bytes < least) {
+        set_error("workspace too small: %zu < %zu bytes", ws_bytes, least);
         return FQ_E_WORKSPACE;
     }
+    if (ws_bytes < p.bytes) p = plan(n_vox, n_t, ws_bytes);
     return launch_gram(iq, n_vox, n_t, gram_mode, p, ws, gram, as_stream(stream));
 }
