@@ -3,7 +3,8 @@
 // The clutter filter needs every eigenvalue of the N_t x N_t Hermitian Gram G = S^H S
 // (the singular-value curve, the knee) but only the K <= 64 leading eigenvectors (the
 // tissue subspace).  Its FP64 eigensolver therefore runs:
-//  1. tridiagonalisation (one workgroup): for k = 0 .. n-2 a Householder reflector
+//  1. tridiagonalisation (one workgroup up to 128 frames, one launch a step beyond): for
+//     k = 0 .. n-2 a Householder reflector
 //     H_k = I - tau_k v_k v_k^H (v_k[k+1] = 1) maps column k below the diagonal to
 //     beta_k e_1 with beta_k real, and the trailing block is updated two-sided,
 //     A22 <- H^H A22 H = A22 - (v w^H + w v^H),  w = tau A22 v - |tau|^2 (v^H A22 v) v / 2.
@@ -33,7 +34,6 @@
 namespace fq {
 namespace {
 
-constexpr int TRI_THREADS = 1024;
 constexpr int KMAX = 64;
 constexpr int QL_MAX_ITER = 60;       // QL iterations per eigenvalue
 constexpr int ROT_PER_N2 = 8;         // rotation log capacity, in units of n^2 (typical use ~1.2)
@@ -56,20 +56,6 @@ __device__ __forceinline__ double2 zmulc(double2 a, double2 b) {
     return make_double2(a.x * b.x + a.y * b.y, a.y * b.x - a.x * b.y);
 }
 
-// sum over the workgroup; every thread gets the total (red holds one slot per wave)
-template <int NT>
-__device__ __forceinline__ double block_sum(double v, double* red) {
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    const int w = threadIdx.x >> 6;
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) red[w] = v;
-    __syncthreads();
-    double t = 0.0;
-#pragma unroll
-    for (int i = 0; i < NT / 64; ++i) t += red[i];
-    return t;
-}
-
 // ------------------------------------------------------------------ 1. tridiagonalisation
 struct TriArgs {
     const double2* G;   // [n][n]
@@ -78,163 +64,9 @@ struct TriArgs {
     double2* tau;       // [n]
     double* d;          // [n]
     double* e;          // [n]
+    double2* p;         // [2][n] (tridiag_row_kernel)
     int n;
 };
-
-// The two-sided update of step k is applied lazily: step k+1 reads column k+1 through
-// it (for its reflector) and then makes one pass over its trailing block that applies
-// the update, stores the block and forms y = A22 v for its own reflector, so every step
-// reads and writes the trailing block once.  Each wavefront owns every 16th row of the
-// block (coalesced across columns, CT chunks of 64 columns per row) and loads its next
-// row before storing the current one.
-template <int CT>
-__global__ void __launch_bounds__(TRI_THREADS) tridiag_kernel(const TriArgs a) {
-    __shared__ double2 pv[FQ_MAX_NT], pw[FQ_MAX_NT];   // v, w of the previous step (pending update)
-    __shared__ double2 sv[FQ_MAX_NT], sy[FQ_MAX_NT];   // v of this step; y = A22 v, then w
-    __shared__ double2 col[FQ_MAX_NT];                 // column k with the pending update applied
-    __shared__ double red[TRI_THREADS / 64];
-    __shared__ double2 s_tau, s_scale;
-    const int n = a.n, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    constexpr int NW = TRI_THREADS / 64;
-    // Hermitian part of the input (the Gram is Hermitian up to its own rounding)
-    for (int idx = tid; idx < n * n; idx += TRI_THREADS) {
-        const int i = idx / n, j = idx - i * n;
-        const double2 g = a.G[idx], gt = a.G[j * n + i];
-        a.A[idx] = i == j ? make_double2(g.x, 0.0) : make_double2(0.5 * (g.x + gt.x), 0.5 * (g.y - gt.y));
-    }
-    for (int i = tid; i < n; i += TRI_THREADS) {
-        pv[i] = make_double2(0.0, 0.0);
-        pw[i] = make_double2(0.0, 0.0);
-    }
-    __syncthreads();
-    for (int k = 0; k < n - 1; ++k) {
-        // column k (rows k .. n-1) with the previous step's update, read as the conjugate
-        // of row k (contiguous; A is kept Hermitian)
-        double ps = 0.0;
-        for (int i = k + tid; i < n; i += TRI_THREADS) {
-            const double2 x0 = zconj(a.A[(size_t)k * n + i]);
-            const double2 p = zmulc(pv[i], pw[k]), q = zmulc(pw[i], pv[k]);
-            const double2 x = make_double2(x0.x - p.x - q.x, x0.y - p.y - q.y);
-            col[i] = x;
-            if (i >= k + 2) ps += x.x * x.x + x.y * x.y;
-        }
-        const double sigma = block_sum<TRI_THREADS>(ps, red);
-        if (tid == 0) {
-            const double2 alpha = col[k + 1];
-            double2 tau = make_double2(0.0, 0.0), scale = make_double2(0.0, 0.0);
-            double beta = alpha.x;
-            if (sigma > 0.0 || alpha.y != 0.0) {
-                const double nrm = sqrt(alpha.x * alpha.x + alpha.y * alpha.y + sigma);
-                beta = alpha.x >= 0.0 ? -nrm : nrm;
-                const double ib = 1.0 / beta;
-                tau = make_double2((beta - alpha.x) * ib, -alpha.y * ib);
-                const double2 den = make_double2(alpha.x - beta, alpha.y);   // 1 / (alpha - beta)
-                const double idd = 1.0 / (den.x * den.x + den.y * den.y);
-                scale = make_double2(den.x * idd, -den.y * idd);
-            }
-            a.tau[k] = tau;
-            a.e[k] = beta;
-            a.d[k] = col[k].x;
-            s_tau = tau;
-            s_scale = scale;
-        }
-        __syncthreads();
-        const double2 tau = s_tau, scale = s_scale;
-        for (int i = k + 1 + tid; i < n; i += TRI_THREADS) {
-            const double2 v = i == k + 1 ? make_double2(1.0, 0.0) : zmul(col[i], scale);
-            sv[i] = v;
-            a.vh[(size_t)k * n + i] = v;
-        }
-        __syncthreads();
-        // trailing block: apply the pending update, store, and y = A22 v; the wave's next
-        // row is loaded before the current one is stored (no store-to-load wait in the chain)
-        {
-            double2 cur[CT], nxt[CT];
-            int i = k + 1 + wv;
-#pragma unroll
-            for (int t = 0; t < CT; ++t) {
-                const int j = k + 1 + lane + 64 * t;
-                cur[t] = i < n && j < n ? a.A[(size_t)i * n + j] : make_double2(0.0, 0.0);
-            }
-            for (; i < n; i += NW) {
-                const int in = i + NW;
-#pragma unroll
-                for (int t = 0; t < CT; ++t) {
-                    const int j = k + 1 + lane + 64 * t;
-                    nxt[t] = in < n && j < n ? a.A[(size_t)in * n + j] : make_double2(0.0, 0.0);
-                }
-                double2* Ar = a.A + (size_t)i * n;
-                const double2 pvi = pv[i], pwi = pw[i];
-                double2 acc = make_double2(0.0, 0.0);
-#pragma unroll
-                for (int t = 0; t < CT; ++t) {
-                    const int j = k + 1 + lane + 64 * t;
-                    if (j < n) {
-                        const double2 x0 = cur[t];
-                        const double2 p = zmulc(pvi, pw[j]), q = zmulc(pwi, pv[j]);
-                        const double2 x = make_double2(x0.x - p.x - q.x, x0.y - p.y - q.y);
-                        Ar[j] = x;
-                        const double2 v = sv[j];
-                        acc.x += x.x * v.x - x.y * v.y;
-                        acc.y += x.x * v.y + x.y * v.x;
-                    }
-                    cur[t] = nxt[t];
-                }
-                for (int o = 32; o > 0; o >>= 1) {
-                    acc.x += __shfl_xor(acc.x, o);
-                    acc.y += __shfl_xor(acc.y, o);
-                }
-                if (lane == 0) sy[i] = acc;
-            }
-        }
-        __syncthreads();
-        // r = v^H y (real for Hermitian A22); w = tau y - |tau|^2 r v / 2 becomes the pending update
-        double pr = 0.0;
-        for (int i = k + 1 + tid; i < n; i += TRI_THREADS) pr += sv[i].x * sy[i].x + sv[i].y * sy[i].y;
-        const double r = block_sum<TRI_THREADS>(pr, red);
-        const double hw = 0.5 * (tau.x * tau.x + tau.y * tau.y) * r;
-        for (int i = k + 1 + tid; i < n; i += TRI_THREADS) {
-            const double2 ty = zmul(tau, sy[i]);
-            pv[i] = sv[i];
-            pw[i] = make_double2(ty.x - hw * sv[i].x, ty.y - hw * sv[i].y);
-        }
-        __syncthreads();
-    }
-    if (tid == 0) {
-        const int m = n - 1;
-        const double2 x0 = a.A[(size_t)m * n + m];
-        const double2 p = zmulc(pv[m], pw[m]);
-        a.d[m] = x0.x - 2.0 * p.x;
-        a.e[m] = 0.0;
-    }
-}
-
-// Register-resident form for n <= RT_N: the lower block triangle of A (the Hermitian
-// matrix) is held in the registers of one workgroup for the whole reduction, so a step
-// reads and writes no global memory.  It is cut into 16x16 blocks (I >= J; the diagonal
-// blocks are held whole, both triangles), listed by block column J descending and I
-// ascending and dealt to the 8 wavefronts in turn (a wavefront keeps blocks across the
-// whole matrix, so the shrinking trailing block stays spread over all of them); in a
-// block, lane l holds rows 4(l/16) .. 4(l/16)+3 of column l%16.  Step k:
-//   1. the owners of column k put A[k..n-1][k] in LDS;
-//   2. one wavefront forms the reflector (same formulas as the kernel above);
-//   3. p = A22 v: each stored A_ij adds A_ij v_j to p_i and, in the blocks below the
-//      diagonal, conj(A_ij) v_i to p_j: row sums are reduced over the block's 16 columns by
-//      a halving butterfly (each exchange halves the values a lane carries), column sums
-//      over its 4 row groups, both added into p with LDS atomics (each contribution rounded
-//      to a grid on which the FP64 sums are exact: the reduction is deterministic);
-//   4. every wavefront forms r = v^H p itself, and w = tau p - |tau|^2 r v / 2 on the fly;
-//   5. A22 -= v w^H + w v^H on every stored element, with w_j taken as 0 in the columns
-//      j <= k already reduced (v_j = 0 there too, so they are left as they are).
-// Rows and columns past n start at zero and stay zero without a test: v is zero there, so
-// their p and w are zero and the update adds nothing.
-// v and p alternate between two buffers by step parity, so a step's writes never meet
-// the previous step's reads (three barriers per step).
-constexpr int RT_N = 208;                  // 13 block rows: 91 blocks, at most 12 per wavefront
-constexpr int RT_THREADS = 512;            // 8 wavefronts, 2 per SIMD: 256 registers each
-constexpr int RT_WAVES = RT_THREADS / 64;
-constexpr int RT_BPW = 12;                 // blocks per wavefront
-constexpr int RT_REG = 8;                  // of them in registers; the rest in LDS (lane-private)
 
 __device__ __forceinline__ void rt_block(int b, int nbr, int& I, int& J) {
     I = J = -1;
@@ -334,212 +166,30 @@ __device__ __forceinline__ void rt_reduce(const double (&d)[8], double2 cs, int 
     }
 }
 
-// step 3 on one block (rows i0 .. i0+3 of column j in this lane); a diagonal block holds
-// both triangles and adds its row sums only
-template <bool DIAG>
-__device__ __forceinline__ void rt_matvec(const double2 (&x)[4], int i0, int j, int n, int c, int lane,
-                                          const double2* v, double2* p, double scale, double inv_scale) {
-    const double2 vj = v[j];
-    double d[8];
-    double2 cs = make_double2(0.0, 0.0);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const double2 r = zmul(x[q], vj);
-        d[2 * q] = r.x;
-        d[2 * q + 1] = r.y;
-        if (!DIAG) {
-            const double2 t = zmul(zconj(x[q]), v[i0 + q]);
-            cs.x += t.x;
-            cs.y += t.y;
-        }
-    }
-    rt_reduce(d, cs, i0, j, n, c, lane, DIAG, p, scale, inv_scale);
-}
-
-// step 5 on one block: A -= v w^H + w v^H, w = tau p - hw v, for this lane's stored elements
-// (w_j = 0 in a column j <= k: p_j there holds partial sums of reduced columns, not A22 v)
-__device__ __forceinline__ void rt_update(double2 (&x)[4], int i0, int j, int k, const double2* v, const double2* p,
-                                          double2 tau, double hw) {
-    const double2 vj = v[j], tpj = zmul(tau, p[j]);
-    const bool live = j > k;
-    const double2 wj = make_double2(live ? tpj.x - hw * vj.x : 0.0, live ? tpj.y - hw * vj.y : 0.0);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const double2 vi = v[i0 + q], tpi = zmul(tau, p[i0 + q]);
-        const double2 wi = make_double2(tpi.x - hw * vi.x, tpi.y - hw * vi.y);
-        const double2 u1 = zmulc(vi, wj), u2 = zmulc(wi, vj);
-        x[q].x -= u1.x + u2.x;
-        x[q].y -= u1.y + u2.y;
-    }
-}
-
-__global__ void __launch_bounds__(RT_THREADS) tridiag_reg_kernel(const TriArgs a) {
-    __shared__ double2 col[RT_N];
-    __shared__ double2 sv[2][RT_N], sp[2][RT_N];
-    __shared__ double2 s_tau;
-    __shared__ double fro2_w[RT_WAVES];
-    // blocks RT_REG .. RT_BPW-1 of each wavefront: [wave][block][q][lane]
-    __shared__ double2 AL[RT_WAVES * (RT_BPW - RT_REG) * 4 * 64];
-    const int n = a.n, tid = threadIdx.x, lane = tid & 63;
-    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: block bookkeeping in scalars
-    const int nbr = (n + 15) / 16;
-    const int c = lane & 15, rb = (lane >> 4) * 4;
-    for (int i = tid; i < RT_N; i += RT_THREADS) {
-        col[i] = sv[0][i] = sv[1][i] = sp[0][i] = sp[1][i] = make_double2(0.0, 0.0);
-    }
-    auto lds_blk = [&](int s, int q) -> double2& { return AL[((wv * (RT_BPW - RT_REG) + s - RT_REG) * 4 + q) * 64 + lane]; };
-    int bI[RT_BPW], bJ[RT_BPW];
-    double2 A[RT_REG][4];
-    double fro2 = 0.0;   // this lane's part of ||A||_F^2
-#pragma unroll
-    for (int s = 0; s < RT_BPW; ++s) {
-        rt_block(wv + RT_WAVES * s, nbr, bI[s], bJ[s]);
-        const int j = 16 * bJ[s] + c;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int i = 16 * bI[s] + rb + q;
-            double2 x = make_double2(0.0, 0.0);
-            if (bI[s] >= 0 && i < n && j < n) {
-                // Hermitian part of the input (the Gram is Hermitian up to its own rounding)
-                const double2 g = a.G[(size_t)i * n + j], gt = a.G[(size_t)j * n + i];
-                x = i == j ? make_double2(g.x, 0.0) : make_double2(0.5 * (g.x + gt.x), 0.5 * (g.y - gt.y));
-                fro2 += (bI[s] == bJ[s] ? 1.0 : 2.0) * (x.x * x.x + x.y * x.y);
-            }
-            if (s < RT_REG) A[s][q] = x;
-            else lds_blk(s, q) = x;
-        }
-    }
-    fro2 = wave_total(fro2);
-    if (lane == 0) fro2_w[wv] = fro2;
-    __syncthreads();
-    // scale 2^(51 - e) with ||A||_F < 2^(e+1): partial sums of p_i below sqrt(2) 2^(e+1) + 13 delta
-    // < 2^52.6 delta
-    double fro = 0.0;
-#pragma unroll
-    for (int w = 0; w < RT_WAVES; ++w) fro += fro2_w[w];
-    fro = sqrt(fro);
-    const int fe = __builtin_amdgcn_readfirstlane(fro > 0.0 ? max(ilogb(fro), -900) : 0);
-    const double scale = ldexp(1.0, 51 - fe), inv_scale = ldexp(1.0, fe - 51);
-    for (int k = 0; k < n - 1; ++k) {
-        double2* v = sv[k & 1];
-        double2* p = sp[k & 1];
-        // 1. column k, rows k .. n-1; clear p
-        const int kb = k >> 4, kc = k & 15;
-#pragma unroll
-        for (int s = 0; s < RT_BPW; ++s) {
-            if (bJ[s] == kb && c == kc) {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int i = 16 * bI[s] + rb + q;
-                    if (i >= k && i < n) col[i] = s < RT_REG ? A[s < RT_REG ? s : 0][q] : lds_blk(s, q);
-                }
-            }
-        }
-        for (int i = tid; i < n; i += RT_THREADS) p[i] = make_double2(0.0, 0.0);
-        __syncthreads();
-        // 2. the reflector of column k
-        if (wv == 0) {
-            double ps = 0.0;
-            for (int i = k + 2 + lane; i < n; i += 64) ps += col[i].x * col[i].x + col[i].y * col[i].y;
-            const double sigma = wave_total(ps);
-            const double2 alpha = col[k + 1];
-            double2 tau = make_double2(0.0, 0.0), scale = make_double2(0.0, 0.0);
-            double beta = alpha.x;
-            if (sigma > 0.0 || alpha.y != 0.0) {
-                const double nrm = sqrt(alpha.x * alpha.x + alpha.y * alpha.y + sigma);
-                beta = alpha.x >= 0.0 ? -nrm : nrm;
-                const double ib = 1.0 / beta;
-                tau = make_double2((beta - alpha.x) * ib, -alpha.y * ib);
-                const double2 den = make_double2(alpha.x - beta, alpha.y);   // 1 / (alpha - beta)
-                const double idd = 1.0 / (den.x * den.x + den.y * den.y);
-                scale = make_double2(den.x * idd, -den.y * idd);
-            }
-            if (lane == 0) {
-                a.tau[k] = tau;
-                a.e[k] = beta;
-                a.d[k] = col[k].x;
-                s_tau = tau;
-            }
-            for (int i = lane; i < n; i += 64) {
-                double2 vi = make_double2(0.0, 0.0);
-                if (i == k + 1) vi = make_double2(1.0, 0.0);
-                else if (i > k + 1) vi = zmul(col[i], scale);
-                v[i] = vi;
-                if (i > k) a.vh[(size_t)k * n + i] = vi;
-            }
-        }
-        __syncthreads();
-        const double2 tau = s_tau;
-        // 3. p = A22 v (blocks with a column beyond k)
-#pragma unroll
-        for (int s = 0; s < RT_BPW; ++s) {
-            if (bI[s] < 0 || 16 * bJ[s] + 15 <= k) continue;
-            const int j = 16 * bJ[s] + c, i0 = 16 * bI[s] + rb;
-            if (s < RT_REG) {
-                if (bI[s] == bJ[s]) rt_matvec<true>(A[s < RT_REG ? s : 0], i0, j, n, c, lane, v, p, scale, inv_scale);
-                else rt_matvec<false>(A[s < RT_REG ? s : 0], i0, j, n, c, lane, v, p, scale, inv_scale);
-            } else {
-                double2 x[4];
-#pragma unroll
-                for (int q = 0; q < 4; ++q) x[q] = lds_blk(s, q);
-                if (bI[s] == bJ[s]) rt_matvec<true>(x, i0, j, n, c, lane, v, p, scale, inv_scale);
-                else rt_matvec<false>(x, i0, j, n, c, lane, v, p, scale, inv_scale);
-            }
-        }
-        __syncthreads();
-        // 4. r = v^H p (real), in every wavefront
-        double pr = 0.0;
-        for (int i = k + 1 + lane; i < n; i += 64) pr += v[i].x * p[i].x + v[i].y * p[i].y;
-        pr = wave_total(pr);
-        const double hw = 0.5 * (tau.x * tau.x + tau.y * tau.y) * pr;
-        // 5. the rank-2 update on columns beyond k
-#pragma unroll
-        for (int s = 0; s < RT_BPW; ++s) {
-            if (bI[s] < 0 || 16 * bJ[s] + 15 <= k) continue;
-            const int j = 16 * bJ[s] + c, i0 = 16 * bI[s] + rb;
-            if (s < RT_REG) {
-                rt_update(A[s < RT_REG ? s : 0], i0, j, k, v, p, tau, hw);
-            } else {
-                double2 x[4];
-#pragma unroll
-                for (int q = 0; q < 4; ++q) x[q] = lds_blk(s, q);
-                rt_update(x, i0, j, k, v, p, tau, hw);
-#pragma unroll
-                for (int q = 0; q < 4; ++q) lds_blk(s, q) = x[q];
-            }
-        }
-    }
-    // the last diagonal element
-    const int m = n - 1;
-#pragma unroll
-    for (int s = 0; s < RT_BPW; ++s) {
-        if (bJ[s] == (m >> 4) && bI[s] == (m >> 4) && c == (m & 15)) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                if (16 * bI[s] + rb + q == m) {
-                    a.d[m] = s < RT_REG ? A[s < RT_REG ? s : 0][q].x : lds_blk(s, q).x;
-                    a.e[m] = 0.0;
-                }
-            }
-        }
-    }
-}
-
-// The same for n <= 128, where a wavefront has registers to spare, with one barrier a step:
+// Up to TRI_ONE frames the lower block triangle of A (the Hermitian matrix) is held in the
+// registers of one workgroup for the whole reduction, so a step reads and writes no global
+// memory.  It is cut into 16x16 blocks (I >= J; the diagonal blocks are held whole, both
+// triangles), listed by block column J descending and I ascending and dealt to the wavefronts in
+// turn (a wavefront keeps blocks across the whole matrix, so the shrinking trailing block stays
+// spread over all of them); in a block, lane l holds rows 4(l/16) .. 4(l/16)+3 of column l%16.
+// Step k, with one barrier:
 //   1. every wavefront forms w = tau p - |tau|^2 (v^H p) v / 2 of step k-1, takes its rank-2
 //      update off column k (held in LDS as step k-2 left it), and forms the reflector v, tau of
 //      column k, all redundantly: the vectors are one or two values a lane, and the chain (two
 //      wavefront sums, a square root, a division) would otherwise need a barrier at each end
 //      for the one wavefront that computes it;
-//   2. the update of step k-1 and p = A22 v in one pass over the blocks; the owners of column
-//      k+1 put it in LDS;
+//   2. the update of step k-1 and p = A22 v in one pass over the blocks: each stored A_ij adds
+//      A_ij v_j to p_i and, in the blocks below the diagonal, conj(A_ij) v_i to p_j; row sums are
+//      reduced over the block's 16 columns by a halving butterfly (each exchange halves the
+//      values a lane carries), column sums over its 4 row groups, both added into p with LDS
+//      atomics (each contribution rounded to a grid on which the FP64 sums are exact: the
+//      reduction is deterministic).  The owners of column k+1 put it in LDS;
 //   3. the barrier: p and column k+1 are complete.
 // v and w are zero on the rows already reduced and on rows past n, which so stay as they are.
 // All wavefronts write the same v and w to the same words (each reads back its own or an equal
 // value); v and the column alternate between two buffers, p between three, so that a wavefront
 // one step ahead writes nothing that another still reads.
-// 20 frames: 33 us, 64: 134, 128: 436 (54, 180, 521 with three barriers a step).  Beyond 128
-// frames its registers would spill: 1199 us at 129 frames, 621 in the form above.
+// 20 frames: 33 us, 64: 134, 128: 436 (54, 180, 521 with three barriers a step).
 // step 2 on one block (rows i0 .. i0+3 of column j in this lane): A -= v1 w^H + w v1^H, then its
 // part of A v; a diagonal block holds both triangles and adds its row sums only.  get and put
 // move the lane's element of row q.
@@ -742,6 +392,141 @@ __global__ void __launch_bounds__(64 * W) tridiag_step_kernel(const TriArgs a) {
         }
         pk = pn;
         __syncthreads();
+    }
+}
+
+// Beyond TRI_ONE frames one launch a step, the launch being the barrier, and one wavefront a row
+// of the trailing block (A is kept as a full Hermitian matrix in the workspace).  Step k: every
+// wavefront forms w of step k-1 and the reflector of column k itself (its lanes hold the vectors
+// in the columns they handle, so nothing goes through LDS), applies the update of step k-1 to
+// its row i, stores it and writes p_i = (A22 v)_i.  Row k, which gives column k, is only read in
+// step k; p alternates between two buffers; v_{k-1} is row k-1 of vh.  The wavefront of row
+// k+1 writes what leaves the step.  CT chunks of 64 columns from column k & ~63 on.
+// A step is latency: a launch, one round of loads, two wavefront sums, a square root and three
+// divisions; 3.3 us at 200 frames, 4.7 at 400, where one workgroup for the whole matrix takes 7
+// and 28 (registers and LDS hold 208 frames; beyond, every step streams the trailing block
+// through one compute unit).  Whole filter of 4096 voxels: 130 frames 886 -> 670 us, 200: 1775
+// -> 1015, 209: 3103 -> 1050, 400: 12131 -> 2220, 512: 21413 -> 3030.  At 1, 2, 4, 8 rows a
+// workgroup 400 frames take 2226, 2220, 2265, 2589 us and 200 frames 1014, 1041, 1055, 1175.
+// The line is at 128 frames: there the launches take 618 us and one workgroup 698, at 100 frames
+// 490 and 535, at 80 400 and 373, and 128 launches are 0.3 ms of the calling thread's time.
+constexpr int TRI_ONE = 128;
+template <int CT, bool FIRST>
+__global__ void __launch_bounds__(64) tridiag_row_kernel(const TriArgs a, int k) {
+    const int n = a.n, lane = threadIdx.x, gw = blockIdx.x;
+    const int i = k + 1 + gw, ir = min(i, n - 1);
+    const int base = k & ~63, ko = k - base;
+    const double2* p0 = a.p + (k & 1) * n;         // A22 v of step k-1
+    double2* p1 = a.p + ((k + 1) & 1) * n;
+    auto at = [&](int r, int c) {
+        if (!FIRST) return a.A[(size_t)r * n + c];
+        // Hermitian part of the input (the Gram is Hermitian up to its own rounding)
+        const double2 g = a.G[(size_t)r * n + c], gt = a.G[(size_t)c * n + r];
+        return r == c ? make_double2(g.x, 0.0) : make_double2(0.5 * (g.x + gt.x), 0.5 * (g.y - gt.y));
+    };
+    // every load ahead of the first use, without a branch (columns past n read column n - 1)
+    double2 x[CT], y[CT], v1[CT], w[CT];
+#pragma unroll
+    for (int t = 0; t < CT; ++t) {
+        const int j = min(base + lane + 64 * t, n - 1);
+        x[t] = at(k, j);
+        if (!FIRST) {
+            v1[t] = a.vh[(size_t)(k - 1) * n + j];
+            w[t] = p0[j];
+        }
+    }
+#pragma unroll
+    for (int t = 0; t < CT; ++t) y[t] = at(ir, min(base + lane + 64 * t, n - 1));
+    const double2 zero = make_double2(0.0, 0.0);
+    double2 v1i = zero, wi = zero;
+    if (!FIRST) {
+        v1i = a.vh[(size_t)(k - 1) * n + ir];
+        wi = p0[ir];
+        const double2 tau1 = a.tau[k - 1];
+        double pr = 0.0;
+#pragma unroll
+        for (int t = 0; t < CT; ++t) {
+            const int j = base + lane + 64 * t;
+            if (j < k || j >= n) v1[t] = w[t] = zero;
+            pr += v1[t].x * w[t].x + v1[t].y * w[t].y;
+        }
+        // r = v^H p (real for Hermitian A22); w = tau p - |tau|^2 r v / 2
+        const double hw = 0.5 * (tau1.x * tau1.x + tau1.y * tau1.y) * wave_total(pr);
+        auto to_w = [&](double2 p, double2 v) {
+            const double2 tp = zmul(tau1, p);
+            return make_double2(tp.x - hw * v.x, tp.y - hw * v.y);
+        };
+#pragma unroll
+        for (int t = 0; t < CT; ++t) w[t] = to_w(w[t], v1[t]);
+        wi = to_w(wi, v1i);
+    }
+    // column k = conj(row k), less the update of step k-1 (v_k of that step is 1)
+    const double2 wk = FIRST ? zero : make_double2(lane_f64(w[0].x, ko), lane_f64(w[0].y, ko));
+    double ps = 0.0;
+#pragma unroll
+    for (int t = 0; t < CT; ++t) {
+        const int j = base + lane + 64 * t;
+        x[t] = zconj(x[t]);
+        if (!FIRST) {
+            const double2 u = zmulc(v1[t], wk);
+            x[t].x -= u.x + w[t].x;
+            x[t].y -= u.y + w[t].y;
+        }
+        if (j >= k + 2 && j < n) ps += x[t].x * x[t].x + x[t].y * x[t].y;
+    }
+    const double dk = lane_f64(x[0].x, ko);
+    if (k == n - 1) {
+        if (gw == 0 && lane == 0) {
+            a.d[k] = dk;
+            a.e[k] = 0.0;
+        }
+        return;
+    }
+    const double sigma = wave_total(ps);
+    const bool over = CT > 1 && ko == 63;   // row k+1 starts the second chunk
+    const int al = (ko + 1) & 63;
+    const double2 xa = over ? x[CT > 1 ? 1 : 0] : x[0];
+    const double2 alpha = make_double2(lane_f64(xa.x, al), lane_f64(xa.y, al));
+    double2 tau = zero, scale = zero;
+    double beta = alpha.x;
+    if (sigma > 0.0 || alpha.y != 0.0) {
+        const double nrm = sqrt(alpha.x * alpha.x + alpha.y * alpha.y + sigma);
+        beta = alpha.x >= 0.0 ? -nrm : nrm;
+        const double ib = 1.0 / beta;
+        tau = make_double2((beta - alpha.x) * ib, -alpha.y * ib);
+        const double2 den = make_double2(alpha.x - beta, alpha.y);   // 1 / (alpha - beta)
+        const double idd = 1.0 / (den.x * den.x + den.y * den.y);
+        scale = make_double2(den.x * idd, -den.y * idd);
+    }
+    double2 acc = zero;
+#pragma unroll
+    for (int t = 0; t < CT; ++t) {
+        const int j = base + lane + 64 * t;
+        double2 v = zmul(x[t], scale);
+        if (j == k + 1) v = make_double2(1.0, 0.0);
+        if (j <= k || j >= n) v = zero;
+        double2 u = y[t];
+        if (!FIRST) {
+            const double2 u1 = zmulc(v1i, w[t]), u2 = zmulc(wi, v1[t]);
+            u.x -= u1.x + u2.x;
+            u.y -= u1.y + u2.y;
+        }
+        if (i < n && j > k && j < n) {
+            a.A[(size_t)i * n + j] = u;
+            acc.x += u.x * v.x - u.y * v.y;
+            acc.y += u.x * v.y + u.y * v.x;
+        }
+        if (gw == 0 && j > k && j < n) a.vh[(size_t)k * n + j] = v;
+    }
+    acc.x = wave_total(acc.x);
+    acc.y = wave_total(acc.y);
+    if (lane == 0 && i < n) {
+        p1[i] = acc;
+        if (gw == 0) {
+            a.tau[k] = tau;
+            a.e[k] = beta;
+            a.d[k] = dk;
+        }
     }
 }
 
@@ -1628,14 +1413,14 @@ __global__ void __launch_bounds__(256) pd_kernel(const float2* iq, int64_t nv, i
     pd[v] = acc * inv_nt;
 }
 
-using TriFn = void (*)(const TriArgs);
-int tri_threads(int n) { return n <= 64 ? 256 : n <= RT_N ? RT_THREADS : TRI_THREADS; }
-TriFn tri_fn(int n) {
-    if (n <= 64) return tridiag_step_kernel<64, 4>;
-    if (n <= 128) return tridiag_step_kernel<128, 8>;
-    if (n <= RT_N) return tridiag_reg_kernel;
-    if (n <= 256) return tridiag_kernel<4>;
-    return tridiag_kernel<FQ_MAX_NT / 64>;
+using TriRowFn = void (*)(const TriArgs, int);
+template <bool FIRST>
+TriRowFn tri_row_fn(int chunks) {
+    static const TriRowFn fn[FQ_MAX_NT / 64] = {
+        tridiag_row_kernel<1, FIRST>, tridiag_row_kernel<2, FIRST>, tridiag_row_kernel<3, FIRST>,
+        tridiag_row_kernel<4, FIRST>, tridiag_row_kernel<5, FIRST>, tridiag_row_kernel<6, FIRST>,
+        tridiag_row_kernel<7, FIRST>, tridiag_row_kernel<8, FIRST>};
+    return fn[chunks - 1];
 }
 
 struct SvdWs {
@@ -1677,6 +1462,27 @@ SvdWs svd_layout(int n) {
     return w;
 }
 
+// One workgroup up to TRI_ONE frames, one launch a step beyond.
+int launch_tridiag(const double* gram, int n, char* ws, const SvdWs& L, hipStream_t s) {
+    const TriArgs a{reinterpret_cast<const double2*>(gram), reinterpret_cast<double2*>(ws + L.off_A),
+                    reinterpret_cast<double2*>(ws + L.off_vh), reinterpret_cast<double2*>(ws + L.off_tau),
+                    reinterpret_cast<double*>(ws + L.off_d), reinterpret_cast<double*>(ws + L.off_e),
+                    reinterpret_cast<double2*>(ws + L.off_Zs), n};   // Zs is written by later kernels only
+    if (n <= TRI_ONE) {
+        if (n <= 64) hipLaunchKernelGGL((tridiag_step_kernel<64, 4>), dim3(1), dim3(256), 0, s, a);
+        else hipLaunchKernelGGL((tridiag_step_kernel<TRI_ONE, 8>), dim3(1), dim3(512), 0, s, a);
+        FQ_LAUNCH_CHECK();
+        return FQ_OK;
+    }
+    for (int k = 0; k < n; ++k) {
+        const int chunks = (n - (k & ~63) + 63) / 64;
+        const TriRowFn kern = k ? tri_row_fn<false>(chunks) : tri_row_fn<true>(chunks);
+        hipLaunchKernelGGL(kern, dim3(std::max(1, n - 1 - k)), dim3(64), 0, s, a, k);
+        FQ_LAUNCH_CHECK();
+    }
+    return FQ_OK;
+}
+
 // Every eigenpair by QL (hermitian_eig): eigenvalues (descending, clamped) into lam/sigma;
 // the leading ncols eigenvectors into vecs ([n][n] complex128, columns in rank order)
 // unless vecs is null.
@@ -1693,9 +1499,8 @@ int launch_eig(const double* gram, int n, char* ws, const SvdWs& L, double* lam,
     int* perm = reinterpret_cast<int*>(ws + L.off_perm);
     double* Zs = reinterpret_cast<double*>(ws + L.off_Zs);
 
-    TriArgs ta{reinterpret_cast<const double2*>(gram), reinterpret_cast<double2*>(ws + L.off_A), vh, tau, d, e, n};
-    hipLaunchKernelGGL(tri_fn(n), dim3(1), dim3(tri_threads(n)), 0, s, ta);
-    FQ_LAUNCH_CHECK();
+    const int st = launch_tridiag(gram, n, ws, L, s);
+    if (st != FQ_OK) return st;
     QlArgs qa{d, e, ri, rc, rs, rn, L.cap, lam, sigma, perm, status, n};
     hipLaunchKernelGGL(ql_kernel, dim3(1), dim3(64), 0, s, qa);
     FQ_LAUNCH_CHECK();
@@ -1714,11 +1519,8 @@ int launch_eig(const double* gram, int n, char* ws, const SvdWs& L, double* lam,
 // (lam, sigma, and the unit-scaled ev for the vectors).
 int launch_eigvals(const double* gram, int n, char* ws, const SvdWs& L, double* lam, double* sigma, int* status,
                    hipStream_t s) {
-    TriArgs ta{reinterpret_cast<const double2*>(gram), reinterpret_cast<double2*>(ws + L.off_A),
-               reinterpret_cast<double2*>(ws + L.off_vh), reinterpret_cast<double2*>(ws + L.off_tau),
-               reinterpret_cast<double*>(ws + L.off_d), reinterpret_cast<double*>(ws + L.off_e), n};
-    hipLaunchKernelGGL(tri_fn(n), dim3(1), dim3(tri_threads(n)), 0, s, ta);
-    FQ_LAUNCH_CHECK();
+    const int st = launch_tridiag(gram, n, ws, L, s);
+    if (st != FQ_OK) return st;
     EigvalArgs ea{reinterpret_cast<const double*>(ws + L.off_d), reinterpret_cast<const double*>(ws + L.off_e),
                   reinterpret_cast<double*>(ws + L.off_ev), reinterpret_cast<double*>(ws + L.off_sc), lam, sigma,
                   status, n};
