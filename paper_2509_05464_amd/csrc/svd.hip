@@ -86,8 +86,8 @@ __device__ __forceinline__ void rt_block(int b, int nbr, int& I, int& J) {
 template <int CTRL>
 __device__ __forceinline__ double dpp_f64(double x) {
     const long long u = __double_as_longlong(x);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)u, CTRL, 0xF, 0xF, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(u >> 32), CTRL, 0xF, 0xF, false);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)u, CTRL, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(u >> 32), CTRL, 0xF, 0xF, true);
     return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 constexpr int DPP_XOR1 = 0xB1;       // quad_perm [1, 0, 3, 2]
@@ -113,14 +113,34 @@ __device__ __forceinline__ double swap_sum(double x) {
     const double b = __longlong_as_double(((long long)h[1] << 32) | (unsigned int)l[1]);
     return a + b;
 }
-// sum over a full wavefront, the same value in every lane: each row of 16 lanes summed by
-// DPP (quad swaps, then rotations by 4 and 8), the four row totals read out in a fixed order
+// sums over a full wavefront, the same values in every lane: each row of 16 lanes summed by DPP
+// (quad swaps, then rotations by 4 and 8; every lane has its source, so the bound control only
+// saves clearing the destination), then the rows by the swaps.  Several at once hide each
+// other's latency.
+template <int N>
+__device__ __forceinline__ void wave_totals(double (&x)[N]) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) x[i] += dpp_f64<DPP_XOR1>(x[i]);
+#pragma unroll
+    for (int i = 0; i < N; ++i) x[i] += dpp_f64<DPP_XOR2>(x[i]);
+#pragma unroll
+    for (int i = 0; i < N; ++i) x[i] += dpp_f64<DPP_ROR4>(x[i]);
+#pragma unroll
+    for (int i = 0; i < N; ++i) x[i] += dpp_f64<DPP_ROR8>(x[i]);
+#pragma unroll
+    for (int i = 0; i < N; ++i) x[i] = swap_sum<false>(x[i]);
+#pragma unroll
+    for (int i = 0; i < N; ++i) x[i] = swap_sum<true>(x[i]);
+}
 __device__ __forceinline__ double wave_total(double x) {
-    x += dpp_f64<DPP_XOR1>(x);
-    x += dpp_f64<DPP_XOR2>(x);
-    x += dpp_f64<DPP_ROR4>(x);
-    x += dpp_f64<DPP_ROR8>(x);
-    return (lane_f64(x, 0) + lane_f64(x, 16)) + (lane_f64(x, 32) + lane_f64(x, 48));
+    double t[1] = {x};
+    wave_totals(t);
+    return t[0];
+}
+__device__ __forceinline__ double2 wave_total(double2 x) {
+    double t[2] = {x.x, x.y};
+    wave_totals(t);
+    return make_double2(t[0], t[1]);
 }
 
 // p = A22 v is summed in LDS by FP64 atomics from the blocks of every wavefront in the order
@@ -518,8 +538,7 @@ __global__ void __launch_bounds__(64) tridiag_row_kernel(const TriArgs a, int k)
         }
         if (gw == 0 && j > k && j < n) a.vh[(size_t)k * n + j] = v;
     }
-    acc.x = wave_total(acc.x);
-    acc.y = wave_total(acc.y);
+    acc = wave_total(acc);
     if (lane == 0 && i < n) {
         p1[i] = acc;
         if (gw == 0) {
@@ -678,12 +697,18 @@ struct EigvalArgs {
 // Number of eigenvalues of the scaled T below x: the negative pivots of the LDL^T
 // factorisation of T - x I.  A pivot smaller than pmin in magnitude is replaced by -pmin
 // (the count of a nearby matrix; no division by zero).
+// The division is the chain: e2 / q is e2 times the hardware's reciprocal of q (relative error
+// up to 2^-24.3 over 10^8 mantissas), corrected by one third-order step, y (1 + r + r^2) with r = 1 - q y, which leaves
+// r^3 < 2^-72 before rounding.  pmin <= |q| < 2^1022, so y and r stay finite.
+// 20 frames: 20 -> 13 us for the kernel, 200: 151 -> 81, 400: 286 -> 157 (before: the IEEE division).
 __device__ __forceinline__ int sturm_count(const double* d, const double* e2, int n, double x, double pmin) {
     double q = d[0] - x;
     if (fabs(q) < pmin) q = -pmin;
     int c = q < 0.0;
+#pragma unroll 8
     for (int i = 1; i < n; ++i) {
-        q = (d[i] - x) - e2[i - 1] / q;
+        const double y = __builtin_amdgcn_rcp(q), r = fma(-q, y, 1.0);
+        q = fma(-e2[i - 1], fma(y, fma(r, r, r), y), d[i] - x);
         if (fabs(q) < pmin) q = -pmin;
         c += q < 0.0;
     }
@@ -811,15 +836,17 @@ __device__ __forceinline__ double start_component(int i, int j) {
 // entry is the larger): U has a diagonal, a super-diagonal and a second super-diagonal
 // (created by exchanges); pivots below eps of the unit-scaled T are raised to +-eps, which
 // is what makes the nearly singular solve amplify the wanted eigenvector.  The serial
-// factorisation and solves run on lane 0 with the next row's operands loaded one step
-// ahead (the dependent chain is then arithmetic only); normalisation is wave-parallel.
+// factorisation and solves run on lane 0; the solves load the operands of IB rows at a time,
+// ahead of the chain (LDS would otherwise answer once a row); normalisation is wave-parallel.
+// 200 frames: 98 -> 87 us, of which the factorisation's divisions are the larger part.
 // Vectors of eigenvalues closer than CLUSTER_TOL are made orthogonal afterwards
 // (orth_kernel); farther apart, inverse iteration leaves them orthogonal to ~eps/gap.
+constexpr int IB = 8;
 __global__ void __launch_bounds__(64) invit_kernel(const InvitArgs a) {
     __shared__ double sd[FQ_MAX_NT], se[FQ_MAX_NT];
-    __shared__ double ua[FQ_MAX_NT], ub[FQ_MAX_NT], uc[FQ_MAX_NT], lf[FQ_MAX_NT];
-    __shared__ unsigned char sw[FQ_MAX_NT];
-    __shared__ double x[FQ_MAX_NT];
+    __shared__ double ua[FQ_MAX_NT], ub[FQ_MAX_NT], uc[FQ_MAX_NT], lf[FQ_MAX_NT + IB];
+    __shared__ unsigned char sw[FQ_MAX_NT + IB];
+    __shared__ double x[FQ_MAX_NT + IB + 1];
     const int n = a.n, lane = threadIdx.x, j = blockIdx.x;
     const int K = a.k_dev ? *a.k_dev : a.k_const;
     if (j >= K) return;
@@ -873,32 +900,73 @@ __global__ void __launch_bounds__(64) invit_kernel(const InvitArgs a) {
     for (int it = 0; it < INVIT_ITERS; ++it) {
         if (lane == 0) {
             // L y = P x: the carried value is x[i] as updated by step i-1
-            double c = x[0];
-            for (int i = 0; i + 1 < n; ++i) {
-                const double nx = x[i + 1];
-                const double l = lf[i];
-                if (sw[i]) {
-                    x[i] = nx;
-                    c = c - l * nx;
-                } else {
-                    x[i] = c;
-                    c = nx - l * c;
+            double c = x[0], f[IB], g[IB], h[IB], y[IB], fn[IB], gn[IB];
+            int m[IB], mn[IB];
+            const int nb = (n - 1) / IB * IB;   // rows in whole batches
+            auto get = [&](int i0) {            // reads at most x[nb + IB] and lf, sw[nb + IB - 1]
+#pragma unroll
+                for (int u = 0; u < IB; ++u) {
+                    fn[u] = x[i0 + u + 1];
+                    gn[u] = lf[i0 + u];
+                    mn[u] = sw[i0 + u];
                 }
+            };
+            get(0);
+            for (int i0 = 0; i0 < nb; i0 += IB) {
+#pragma unroll
+                for (int u = 0; u < IB; ++u) {
+                    f[u] = fn[u];
+                    g[u] = gn[u];
+                    m[u] = mn[u];
+                }
+                get(i0 + IB);
+#pragma unroll
+                for (int u = 0; u < IB; ++u) {
+                    y[u] = m[u] ? f[u] : c;
+                    c = m[u] ? fma(-g[u], f[u], c) : fma(-g[u], c, f[u]);
+                }
+#pragma unroll
+                for (int u = 0; u < IB; ++u) x[i0 + u] = y[u];
+            }
+            for (int i = nb; i + 1 < n; ++i) {
+                const double nx = x[i + 1], l = lf[i];
+                x[i] = sw[i] ? nx : c;
+                c = sw[i] ? fma(-l, nx, c) : fma(-l, c, nx);
             }
             x[n - 1] = c;
             // U z = y
             double z1 = 0.0, z2 = 0.0;   // z[i+1], z[i+2]
-            for (int i = n - 1; i >= 0; --i) {
-                const double zi = (x[i] - ub[i] * z1 - uc[i] * z2) * ua[i];
+            int i = n - 1;
+            for (; i + 1 > n / IB * IB; --i) {
+                const double zi = fma(-ub[i], z1, fma(-uc[i], z2, x[i])) * ua[i];
                 x[i] = zi;
                 z2 = z1;
                 z1 = zi;
+            }
+            for (; i >= 0; i -= IB) {
+                double a[IB];
+#pragma unroll
+                for (int u = 0; u < IB; ++u) {
+                    f[u] = x[i - u];
+                    g[u] = ub[i - u];
+                    h[u] = uc[i - u];
+                    a[u] = ua[i - u];
+                }
+#pragma unroll
+                for (int u = 0; u < IB; ++u) {
+                    const double zi = fma(-g[u], z1, fma(-h[u], z2, f[u])) * a[u];
+                    y[u] = zi;
+                    z2 = z1;
+                    z1 = zi;
+                }
+#pragma unroll
+                for (int u = 0; u < IB; ++u) x[i - u] = y[u];
             }
         }
         __syncthreads();
         double ss = 0.0;
         for (int i = lane; i < n; i += 64) ss += x[i] * x[i];
-        ss = wave_sum(ss);
+        ss = wave_total(ss);
         const bool ok = ss > 0.0 && ss < 1.0 / 0.0;
         bad |= !ok;
         const double inv = ok ? 1.0 / sqrt(ss) : 0.0;
@@ -1098,54 +1166,70 @@ struct BackArgs {
     int n;
 };
 
-constexpr int BT_PER_LANE = FQ_MAX_NT / 64;
+constexpr int BT_AHEAD = 4;   // reflectors in flight
+// One wavefront a column; its chain of n - 1 reflectors is bound by the latency of the loads
+// (covered by BT_AHEAD of them in flight) and of the sums: 200 frames 131 -> 71 us, 400: 255 -> 212
+// (before: one reflector ahead, its loads behind per-lane branches).  Two reflectors a round of
+// sums (with v1^H v0 added) took 83 and 262.
 
+template <int CT>
 __global__ void __launch_bounds__(64) back_kernel(const BackArgs a) {
+    __shared__ double2 st[FQ_MAX_NT];
     const int n = a.n, j = blockIdx.x, lane = threadIdx.x;
     if (j >= (a.k_dev ? *a.k_dev : a.k_const)) return;
-    double2 z[BT_PER_LANE];
+    double2 z[CT];
 #pragma unroll
-    for (int t = 0; t < BT_PER_LANE; ++t) {
+    for (int t = 0; t < CT; ++t) {
         const int i = lane + 64 * t;
         z[t] = make_double2(i < n ? a.Z[(size_t)i * a.zr + (size_t)j * a.zc] : 0.0, 0.0);
     }
-    // reflector k's tau and v (zero outside rows k+1 .. n-1), fetched one reflector ahead
-    double2 vn[BT_PER_LANE], taun = make_double2(0.0, 0.0);
-    auto fetch = [&](int k) {
-        taun = a.tau[k];
-        const double2* v = a.vh + (size_t)k * n;
+    // tau and v of the next BT_AHEAD reflectors; entries outside rows k+1 .. n-1 become zero at
+    // use, so that the loads need no branch
+    double2 vn[BT_AHEAD][CT], taun[BT_AHEAD];
+    for (int i = lane; i < n; i += 64) st[i] = a.tau[i];   // (scalar loads would be waited for all at once)
+    __syncthreads();
+    auto fetch = [&](double2 (&v)[CT], double2& tau, int k) {
+        k = max(k, 0);
+        tau = st[k];
 #pragma unroll
-        for (int t = 0; t < BT_PER_LANE; ++t) {
-            const int i = lane + 64 * t;
-            vn[t] = i > k && i < n ? v[i] : make_double2(0.0, 0.0);
-        }
+        for (int t = 0; t < CT; ++t) v[t] = a.vh[(size_t)k * n + min(lane + 64 * t, n - 1)];
     };
-    if (n >= 2) fetch(n - 2);
-    for (int k = n - 2; k >= 0; --k) {
-        double2 v[BT_PER_LANE];
+    if (n < 2) {
+        if (lane == 0) a.V[j] = z[0];
+        return;
+    }
 #pragma unroll
-        for (int t = 0; t < BT_PER_LANE; ++t) v[t] = vn[t];
-        const double2 tau = taun;
-        if (k > 0) fetch(k - 1);
-        if (tau.x == 0.0 && tau.y == 0.0) continue;
-        double2 dot = make_double2(0.0, 0.0);   // v^H z over rows k+1 .. n-1
+    for (int u = 0; u < BT_AHEAD; ++u) fetch(vn[u], taun[u], n - 2 - u);
+    for (int k0 = n - 2; k0 >= 0; k0 -= BT_AHEAD) {
 #pragma unroll
-        for (int t = 0; t < BT_PER_LANE; ++t) {
-            dot.x += v[t].x * z[t].x + v[t].y * z[t].y;
-            dot.y += v[t].x * z[t].y - v[t].y * z[t].x;
-        }
-        dot.x = wave_total(dot.x);
-        dot.y = wave_total(dot.y);
-        const double2 td = zmul(tau, dot);
+        for (int u = 0; u < BT_AHEAD; ++u) {
+            const int k = k0 - u;
+            double2 v[CT];
 #pragma unroll
-        for (int t = 0; t < BT_PER_LANE; ++t) {
-            const double2 u = zmul(v[t], td);
-            z[t].x -= u.x;
-            z[t].y -= u.y;
+            for (int t = 0; t < CT; ++t) {
+                const int i = lane + 64 * t;
+                v[t] = i > k && i < n ? vn[u][t] : make_double2(0.0, 0.0);
+            }
+            const double2 tau = k >= 0 ? taun[u] : make_double2(0.0, 0.0);
+            fetch(vn[u], taun[u], k - BT_AHEAD);
+            if (tau.x == 0.0 && tau.y == 0.0) continue;
+            double2 dot = make_double2(0.0, 0.0);   // v^H z over rows k+1 .. n-1
+#pragma unroll
+            for (int t = 0; t < CT; ++t) {
+                dot.x += v[t].x * z[t].x + v[t].y * z[t].y;
+                dot.y += v[t].x * z[t].y - v[t].y * z[t].x;
+            }
+            const double2 td = zmul(tau, wave_total(dot));
+#pragma unroll
+            for (int t = 0; t < CT; ++t) {
+                const double2 w = zmul(v[t], td);
+                z[t].x -= w.x;
+                z[t].y -= w.y;
+            }
         }
     }
 #pragma unroll
-    for (int t = 0; t < BT_PER_LANE; ++t) {
+    for (int t = 0; t < CT; ++t) {
         const int i = lane + 64 * t;
         if (i < n) a.V[(size_t)i * n + j] = z[t];
     }
@@ -1413,6 +1497,10 @@ __global__ void __launch_bounds__(256) pd_kernel(const float2* iq, int64_t nv, i
     pd[v] = acc * inv_nt;
 }
 
+using BackFn = void (*)(const BackArgs);
+BackFn back_fn(int n) {
+    return n <= 64 ? back_kernel<1> : n <= 128 ? back_kernel<2> : n <= 256 ? back_kernel<4> : back_kernel<FQ_MAX_NT / 64>;
+}
 using TriRowFn = void (*)(const TriArgs, int);
 template <bool FIRST>
 TriRowFn tri_row_fn(int chunks) {
@@ -1510,7 +1598,7 @@ int launch_eig(const double* gram, int n, char* ws, const SvdWs& L, double* lam,
     hipLaunchKernelGGL(replay_kernel, dim3((n + rows - 1) / rows), dim3(64), sizeof(double) * (size_t)rows * n, s, pa);
     FQ_LAUNCH_CHECK();
     BackArgs ba{Zs, n, 1, vh, tau, reinterpret_cast<double2*>(vecs), nullptr, std::min(ncols, n), n};
-    hipLaunchKernelGGL(back_kernel, dim3(std::min(ncols, n)), dim3(64), 0, s, ba);
+    hipLaunchKernelGGL(back_fn(n), dim3(std::min(ncols, n)), dim3(64), 0, s, ba);
     FQ_LAUNCH_CHECK();
     return FQ_OK;
 }
@@ -1546,7 +1634,7 @@ int launch_eigvecs(int n, char* ws, const SvdWs& L, const int* k_dev, int k_cons
     FQ_LAUNCH_CHECK();
     BackArgs ba{zt, 1, n, reinterpret_cast<const double2*>(ws + L.off_vh),
                 reinterpret_cast<const double2*>(ws + L.off_tau), reinterpret_cast<double2*>(vecs), k_dev, k_const, n};
-    hipLaunchKernelGGL(back_kernel, dim3(grid), dim3(64), 0, s, ba);
+    hipLaunchKernelGGL(back_fn(n), dim3(grid), dim3(64), 0, s, ba);
     FQ_LAUNCH_CHECK();
     return FQ_OK;
 }

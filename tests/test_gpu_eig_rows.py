@@ -37,3 +37,25 @@ def test_eigenvalues(gpu, n, kind):
     assert bool((sws[-4096:] == 0xff).all())
     got = sigma[0].cpu().numpy() ** 2
     assert np.abs(got - np.maximum(want, 0.0)).max() < 20 * n * 2.0 ** -53 * want[0]
+
+
+@pytest.mark.parametrize('n', [2, 3, 7, 8, 9, 10, 16, 17, 18, 63, 127, 255, 512])
+def test_leading_projector(gpu, n):
+    """Inverse iteration in batches of 8 rows and the back-transformation 4 reflectors ahead at
+    the ends of both.  Eigenvalues 2^-i: the leading projector is off by a few n 2^-53 / gap, and
+    the filter applied to the identity adds FP32 products of K <= 3 terms: 1e-5 covers both."""
+    import torch
+    rng = np.random.default_rng(n)
+    q, _ = np.linalg.qr(rng.standard_normal((n, n)) + 1j * rng.standard_normal((n, n)))
+    G = (q * 2.0 ** -np.minimum(np.arange(n), 40.0)) @ q.conj().T
+    G = 0.5 * (G + G.conj().T)
+    K = min(3, n - 1)
+    sws = torch.full((gpu.svd_workspace_size(n, n),), 0xff, dtype=torch.uint8, device='cuda')
+    sigma = torch.empty(n, dtype=torch.float64, device='cuda')
+    k = torch.zeros(1, dtype=torch.int32, device='cuda')
+    status = torch.full((1,), -1, dtype=torch.int32, device='cuda')
+    filt, pd = torch.empty(n, n, dtype=torch.complex64, device='cuda'), torch.empty(n, device='cuda')
+    gpu.svd_clutter_filter(dev(np.eye(n, dtype=np.complex64)), dev(G), sws, sigma, k, K, iq_filt=filt, pd=pd, status=status)
+    assert status.item() == 0 and k.item() == K
+    v = q[:, :K]
+    assert np.abs(filt.cpu().numpy() - (np.eye(n) - v.conj() @ v.T)).max() < 1e-5
