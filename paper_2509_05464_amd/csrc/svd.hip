@@ -143,6 +143,32 @@ __device__ __forceinline__ double2 wave_total(double2 x) {
     return make_double2(t[0], t[1]);
 }
 
+// Householder reflector of a column with first entry alpha and sum of squares sigma below it:
+// (alpha, x) -> beta, v = (1, scale x)
+__device__ __forceinline__ void reflector(double2 alpha, double sigma, double& beta, double2& tau, double2& scale) {
+    beta = alpha.x;
+    tau = scale = make_double2(0.0, 0.0);
+    if (sigma > 0.0 || alpha.y != 0.0) {
+        // square root and its reciprocal from one estimate, two Newton steps each (correct to
+        // the last place or two); the other reciprocal likewise
+        const double s2 = alpha.x * alpha.x + alpha.y * alpha.y + sigma;
+        double y = __builtin_amdgcn_rsq(s2);
+        y = fma(0.5 * y, fma(-s2 * y, y, 1.0), y);
+        y = fma(0.5 * y, fma(-s2 * y, y, 1.0), y);
+        double nrm = s2 * y;
+        nrm = fma(fma(-nrm, nrm, s2), 0.5 * y, nrm);
+        beta = alpha.x >= 0.0 ? -nrm : nrm;
+        const double ib = alpha.x >= 0.0 ? -y : y;
+        tau = make_double2((beta - alpha.x) * ib, -alpha.y * ib);
+        const double2 den = make_double2(alpha.x - beta, alpha.y);   // 1 / (alpha - beta)
+        const double d2 = den.x * den.x + den.y * den.y;
+        double idd = __builtin_amdgcn_rcp(d2);
+        idd = fma(idd, fma(-d2, idd, 1.0), idd);
+        idd = fma(idd, fma(-d2, idd, 1.0), idd);
+        scale = make_double2(den.x * idd, -den.y * idd);
+    }
+}
+
 // p = A22 v is summed in LDS by FP64 atomics from the blocks of every wavefront in the order
 // they arrive.  Each contribution is first rounded to a multiple of delta = 1/scale: the
 // contributions to p_i are the block pieces of one row of the Hermitian trailing matrix times v,
@@ -353,28 +379,9 @@ __global__ void __launch_bounds__(64 * W) tridiag_step_kernel(const TriArgs a) {
         }
         const double sigma = wave_total(ps);
         const double2 alpha = at(col, k + 1);
-        double2 scl = make_double2(0.0, 0.0);
-        double beta = alpha.x;
-        tau = make_double2(0.0, 0.0);
-        if (sigma > 0.0 || alpha.y != 0.0) {
-            // square root and its reciprocal from one estimate, two Newton steps each (correct to
-            // the last place or two); the other reciprocal likewise
-            const double s2 = alpha.x * alpha.x + alpha.y * alpha.y + sigma;
-            double y = __builtin_amdgcn_rsq(s2);
-            y = fma(0.5 * y, fma(-s2 * y, y, 1.0), y);
-            y = fma(0.5 * y, fma(-s2 * y, y, 1.0), y);
-            double nrm = s2 * y;
-            nrm = fma(fma(-nrm, nrm, s2), 0.5 * y, nrm);
-            beta = alpha.x >= 0.0 ? -nrm : nrm;
-            const double ib = alpha.x >= 0.0 ? -y : y;
-            tau = make_double2((beta - alpha.x) * ib, -alpha.y * ib);
-            const double2 den = make_double2(alpha.x - beta, alpha.y);   // 1 / (alpha - beta)
-            const double d2 = den.x * den.x + den.y * den.y;
-            double idd = __builtin_amdgcn_rcp(d2);
-            idd = fma(idd, fma(-d2, idd, 1.0), idd);
-            idd = fma(idd, fma(-d2, idd, 1.0), idd);
-            scl = make_double2(den.x * idd, -den.y * idd);
-        }
+        double2 scl;
+        double beta;
+        reflector(alpha, sigma, beta, tau, scl);
         if (tid == 0) {
             a.tau[k] = tau;
             a.e[k] = beta;
@@ -507,17 +514,9 @@ __global__ void __launch_bounds__(64) tridiag_row_kernel(const TriArgs a, int k)
     const int al = (ko + 1) & 63;
     const double2 xa = over ? x[CT > 1 ? 1 : 0] : x[0];
     const double2 alpha = make_double2(lane_f64(xa.x, al), lane_f64(xa.y, al));
-    double2 tau = zero, scale = zero;
-    double beta = alpha.x;
-    if (sigma > 0.0 || alpha.y != 0.0) {
-        const double nrm = sqrt(alpha.x * alpha.x + alpha.y * alpha.y + sigma);
-        beta = alpha.x >= 0.0 ? -nrm : nrm;
-        const double ib = 1.0 / beta;
-        tau = make_double2((beta - alpha.x) * ib, -alpha.y * ib);
-        const double2 den = make_double2(alpha.x - beta, alpha.y);   // 1 / (alpha - beta)
-        const double idd = 1.0 / (den.x * den.x + den.y * den.y);
-        scale = make_double2(den.x * idd, -den.y * idd);
-    }
+    double2 tau, scale;
+    double beta;
+    reflector(alpha, sigma, beta, tau, scale);
     double2 acc = zero;
 #pragma unroll
     for (int t = 0; t < CT; ++t) {
