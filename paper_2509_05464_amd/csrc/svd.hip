@@ -1390,6 +1390,7 @@ struct PdArgs {
     int nt;
     int k_lo;             // this instantiation serves k_lo < K <= KM (device-side dispatch)
     float inv_nt;
+    bool stream;          // store out past the caches
 };
 
 // Projection and power Doppler on the matrix cores.  A workgroup of four wavefronts
@@ -1404,6 +1405,15 @@ struct PdArgs {
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 constexpr int PV = 16;             // voxels per wavefront
 constexpr int PW = 4;              // wavefronts per workgroup
+// At most four workgroups a compute unit, V_K staged once for all of a workgroup's voxels.  A
+// filtered ensemble larger than the 256 MB last-level cache is stored past it, so that S's second
+// read still hits there, if every wavefront's 16 voxels are a whole 128-byte line (partial lines
+// written past the caches cost more than they save).  200 frames x 2097152 voxels, filtered
+// ensemble and power Doppler: K = 5 3506 -> 2450 us (2826 with cached stores), K = 24 4875 -> 2670,
+// K = 50 9166 -> 4560; power Doppler alone: K = 24 4050 -> 2116, K = 50 8041 -> 4220; x 65536, K = 5:
+// 99 -> 84 (91 stored past the caches); 400 x 1000001, K = 12: 3864 -> 2620 (4068).
+constexpr int PGRID = 1024;
+constexpr int64_t PSTREAM = (int64_t)256 << 20;
 
 __host__ __device__ inline int vk_stride(int km) { return km + 2; }   // LDS row stride of V_K (float2)
 
@@ -1430,93 +1440,136 @@ __global__ void __launch_bounds__(64 * PW) project_mfma_kernel(const PdArgs a) {
     const float2* V = VL ? sm2 : a.vk;   // [ntp or n_t][VS]
     __syncthreads();
     const int li = lane & 15, lk = lane >> 4;
-    const int64_t v0 = ((int64_t)blockIdx.x * PW + wv) * PV;
-    if (v0 >= a.nv) return;
-    const bool full = v0 + PV <= a.nv;
-    const float2* S = a.iq;
-    // P = S V_K: A[i][k] = S[voxel i][frame f0 + k], B[k][j] = V[frame f0 + k][column 16t + j]
-    floatx4 rr[NKT], ii[NKT], ri[NKT], ir[NKT];
+    const int64_t step = (int64_t)gridDim.x * PW * PV;
+    for (int64_t v0 = ((int64_t)blockIdx.x * PW + wv) * PV; v0 < a.nv; v0 += step) {
+        const bool full = v0 + PV <= a.nv;
+        const float2* S = a.iq;
+        // P = S V_K: A[i][k] = S[voxel i][frame f0 + k], B[k][j] = V[frame f0 + k][column 16t + j]
+        floatx4 rr[NKT], ii[NKT], ri[NKT], ir[NKT];
 #pragma unroll
-    for (int t = 0; t < NKT; ++t)
-        for (int r = 0; r < 4; ++r) rr[t][r] = ii[t][r] = ri[t][r] = ir[t][r] = 0.f;
-    const bool vin = full || v0 + li < a.nv;
-#pragma unroll 4
-    for (int f0 = 0; f0 < ntp; f0 += 4) {
-        const int f = f0 + lk;
-        const float2 x = (f < nt && vin) ? S[(int64_t)f * a.nv + v0 + li] : make_float2(0.f, 0.f);
+        for (int t = 0; t < NKT; ++t)
+            for (int r = 0; r < 4; ++r) rr[t][r] = ii[t][r] = ri[t][r] = ir[t][r] = 0.f;
+        // loads run 16 frames ahead, without a branch (past the last frame and voxel they repeat it)
+        const int64_t vi = v0 + li < a.nv ? v0 + li : a.nv - 1;
+        auto get1 = [&](float2 (&x)[4], int f0) {
 #pragma unroll
-        for (int t = 0; t < NKT; ++t) {
-            const float2 w = (VL || f < nt) ? V[f * VS + 16 * t + li] : make_float2(0.f, 0.f);
-            rr[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(x.x, w.x, rr[t], 0, 0, 0);
-            ii[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(x.y, w.y, ii[t], 0, 0, 0);
-            ri[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(x.x, w.y, ri[t], 0, 0, 0);
-            ir[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(x.y, w.x, ir[t], 0, 0, 0);
+            for (int u = 0; u < 4; ++u) x[u] = S[(int64_t)min(f0 + 4 * u + lk, nt - 1) * a.nv + vi];
+        };
+        float2 xn[4];
+        get1(xn, 0);
+        for (int f0 = 0; f0 < ntp; f0 += 16) {
+            float2 xc[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const bool in = f0 + 4 * u + lk < nt;
+                xc[u] = make_float2(in ? xn[u].x : 0.f, in ? xn[u].y : 0.f);
+            }
+            if (f0 + 16 < ntp) get1(xn, f0 + 16);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int f = f0 + 4 * u + lk;
+                const float2 x = xc[u];
+#pragma unroll
+                for (int t = 0; t < NKT; ++t) {
+                    const float2 w = (VL || f < nt) ? V[f * VS + 16 * t + li] : make_float2(0.f, 0.f);
+                    rr[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(x.x, w.x, rr[t], 0, 0, 0);
+                    ii[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(x.y, w.y, ii[t], 0, 0, 0);
+                    ri[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(x.x, w.y, ri[t], 0, 0, 0);
+                    ir[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(x.y, w.x, ir[t], 0, 0, 0);
+                }
+            }
         }
-    }
-    // P[voxel 4 lk + r][column 16 t + li]
+        float2 sn[4];
+        auto get2 = [&](int f0) {
+            const float2* row = S + (int64_t)min(f0 + li, nt - 1) * a.nv;
+            if (full) {
+                const float4* sp = reinterpret_cast<const float4*>(row + v0 + 4 * lk);
+                const float4 s0 = sp[0], s1 = sp[1];
+                sn[0] = make_float2(s0.x, s0.y);
+                sn[1] = make_float2(s0.z, s0.w);
+                sn[2] = make_float2(s1.x, s1.y);
+                sn[3] = make_float2(s1.z, s1.w);
+            } else {
 #pragma unroll
-    for (int t = 0; t < NKT; ++t)
+                for (int r = 0; r < 4; ++r) sn[r] = row[min(v0 + 4 * lk + r, a.nv - 1)];
+            }
+        };
+        get2(0);
+        // P[voxel 4 lk + r][column 16 t + li]
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            Pr[(4 * lk + r) * PS + 16 * t + li] = rr[t][r] - ii[t][r];
-            Pi[(4 * lk + r) * PS + 16 * t + li] = ri[t][r] + ir[t][r];
-        }
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-    // R = S - P V_K^H, 16 frames at a time: A[i][k] = P[voxel i][k0 + k],
-    // B[k][j] = conj(V[frame f0 + j][k0 + k]); lane holds R[voxel 4 lk + r][frame f0 + li]
-    float pacc[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int f0 = 0; f0 < ntp; f0 += 16) {
-        const int f = f0 + li;
-        floatx4 qa, qb, qc, qd;
-        for (int r = 0; r < 4; ++r) qa[r] = qb[r] = qc[r] = qd[r] = 0.f;
-#pragma unroll
-        for (int k0 = 0; k0 < KM; k0 += 4) {
-            const float pr = Pr[li * PS + k0 + lk], pi = Pi[li * PS + k0 + lk];
-            const float2 w = (VL || f < nt) ? V[f * VS + k0 + lk] : make_float2(0.f, 0.f);
-            qa = __builtin_amdgcn_mfma_f32_16x16x4f32(pr, w.x, qa, 0, 0, 0);
-            qb = __builtin_amdgcn_mfma_f32_16x16x4f32(pi, w.y, qb, 0, 0, 0);
-            qc = __builtin_amdgcn_mfma_f32_16x16x4f32(pi, w.x, qc, 0, 0, 0);
-            qd = __builtin_amdgcn_mfma_f32_16x16x4f32(pr, w.y, qd, 0, 0, 0);
-        }
-        float2 sv[4];
-        if (f < nt && full) {
-            const float4* sp = reinterpret_cast<const float4*>(S + (int64_t)f * a.nv + v0 + 4 * lk);
-            const float4 s0 = sp[0], s1 = sp[1];
-            sv[0] = make_float2(s0.x, s0.y);
-            sv[1] = make_float2(s0.z, s0.w);
-            sv[2] = make_float2(s1.x, s1.y);
-            sv[3] = make_float2(s1.z, s1.w);
-        } else {
+        for (int t = 0; t < NKT; ++t)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const int64_t v = v0 + 4 * lk + r;
-                sv[r] = (f < nt && v < a.nv) ? S[(int64_t)f * a.nv + v] : make_float2(0.f, 0.f);
+                Pr[(4 * lk + r) * PS + 16 * t + li] = rr[t][r] - ii[t][r];
+                Pi[(4 * lk + r) * PS + 16 * t + li] = ri[t][r] + ir[t][r];
+            }
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+        // R = S - P V_K^H, 16 frames at a time: A[i][k] = P[voxel i][k0 + k],
+        // B[k][j] = conj(V[frame f0 + j][k0 + k]); lane holds R[voxel 4 lk + r][frame f0 + li]
+        float pacc[4] = {0.f, 0.f, 0.f, 0.f};
+        for (int f0 = 0; f0 < ntp; f0 += 16) {
+            const int f = f0 + li;
+            float2 sv[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) sv[r] = make_float2(f < nt ? sn[r].x : 0.f, f < nt ? sn[r].y : 0.f);
+            if (f0 + 16 < ntp) get2(f0 + 16);
+            floatx4 qa, qb, qc, qd;
+            for (int r = 0; r < 4; ++r) qa[r] = qb[r] = qc[r] = qd[r] = 0.f;
+#pragma unroll
+            for (int k0 = 0; k0 < KM; k0 += 4) {
+                const float pr = Pr[li * PS + k0 + lk], pi = Pi[li * PS + k0 + lk];
+                const float2 w = (VL || f < nt) ? V[f * VS + k0 + lk] : make_float2(0.f, 0.f);
+                qa = __builtin_amdgcn_mfma_f32_16x16x4f32(pr, w.x, qa, 0, 0, 0);
+                qb = __builtin_amdgcn_mfma_f32_16x16x4f32(pi, w.y, qb, 0, 0, 0);
+                qc = __builtin_amdgcn_mfma_f32_16x16x4f32(pi, w.x, qc, 0, 0, 0);
+                qd = __builtin_amdgcn_mfma_f32_16x16x4f32(pr, w.y, qd, 0, 0, 0);
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                // P conj(V) = (Pr Vr + Pi Vi) + i (Pi Vr - Pr Vi)
+                const float xr = sv[r].x - (qa[r] + qb[r]);
+                const float xi = sv[r].y - (qc[r] - qd[r]);
+                pacc[r] = fmaf(xr, xr, fmaf(xi, xi, pacc[r]));
+                sv[r] = make_float2(xr, xi);
+            }
+            if (a.out && f < nt) {
+                float2* op = a.out + (int64_t)f * a.nv + v0 + 4 * lk;
+                if (full) {
+                    const floatx4 o0{sv[0].x, sv[0].y, sv[1].x, sv[1].y}, o1{sv[2].x, sv[2].y, sv[3].x, sv[3].y};
+                    floatx4* o = reinterpret_cast<floatx4*>(op);
+                    if (a.stream) {
+                        __builtin_nontemporal_store(o0, o);
+                        __builtin_nontemporal_store(o1, o + 1);
+                    } else {
+                        o[0] = o0;
+                        o[1] = o1;
+                    }
+                } else {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        if (v0 + 4 * lk + r < a.nv) op[r] = sv[r];
+                }
             }
         }
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            // P conj(V) = (Pr Vr + Pi Vi) + i (Pi Vr - Pr Vi)
-            const float xr = sv[r].x - (qa[r] + qb[r]);
-            const float xi = sv[r].y - (qc[r] - qd[r]);
-            pacc[r] = fmaf(xr, xr, fmaf(xi, xi, pacc[r]));
-            const int64_t v = v0 + 4 * lk + r;
-            if (a.out && f < nt && v < a.nv) a.out[(int64_t)f * a.nv + v] = make_float2(xr, xi);
+            float x = pacc[r];
+            for (int o = 1; o < 16; o <<= 1) x += __shfl_xor(x, o);
+            pacc[r] = x;
         }
-    }
+        if (li == 0 && a.pd) {
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        float x = pacc[r];
-        for (int o = 1; o < 16; o <<= 1) x += __shfl_xor(x, o);
-        pacc[r] = x;
-    }
-    if (li == 0 && a.pd) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int64_t v = v0 + 4 * lk + r;
-            if (v < a.nv) a.pd[v] = pacc[r] * a.inv_nt;
+            for (int r = 0; r < 4; ++r) {
+                const int64_t v = v0 + 4 * lk + r;
+                if (v < a.nv) a.pd[v] = pacc[r] * a.inv_nt;
+            }
         }
+        // (the next voxels' P overwrites this one's: the wavefront's own LDS, in order)
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
     }
 }
 
@@ -1723,7 +1776,9 @@ static int launch_apply(const float* iq, int64_t n_vox, int n_t, char* w, const 
     pa.nv = n_vox;
     pa.nt = n_t;
     pa.inv_nt = 1.0f / (float)n_t;
-    const unsigned blocks = (unsigned)((n_vox + PV * PW - 1) / (PV * PW));
+    pa.stream = iq_filt && n_vox % 16 == 0 && (uintptr_t)iq_filt % 128 == 0 &&
+                (int64_t)sizeof(float2) * n_vox * n_t > PSTREAM;
+    const unsigned blocks = (unsigned)std::min<int64_t>((n_vox + PV * PW - 1) / (PV * PW), PGRID);
     if (!iq_filt) {
         // power Doppler alone: the FP64 norm difference up to K = 16, the explicit
         // projection above; all but the class holding K return at once
