@@ -711,7 +711,7 @@ def workload_run(cfg, steps, warmup, args, fq, torch, dev, filt, train, full=Tru
     }
 
     # a stream of ensembles: the same SVD path on two streams, volumes alternating, so one
-    # volume's single-workgroup eigensolver runs beside the next volume's Gram
+    # volume's eigensolver (small, latency-bound launches) runs beside the next volume's Gram
     def two_in_flight(mode, reps=8):
         sets = [(G, gws, sws, sigma, k1, st1, pd_svd), (G2, gws2, sws2, sigma2, k2, st2, pd_split)]
         strs = (torch.cuda.Stream(), torch.cuda.Stream())
@@ -735,8 +735,8 @@ def workload_run(cfg, steps, warmup, args, fq, torch, dev, filt, train, full=Tru
 
     # a stream of ensembles, pipelined: the eigendecomposition and cutoff of volume v on a
     # stream held to 8 CUs (one per XCD) while the other 248 form volume v+1's Gram and then
-    # volume v's projection and PD (svd_filter_apply); the eigensolver's single workgroup needs
-    # a whole CU, which a full-GPU Gram otherwise keeps taken
+    # volume v's projection and PD (svd_filter_apply); a full-GPU Gram otherwise keeps the CUs
+    # taken that the eigensolver's small launches need
     def pipelined(mode, streams, reps=8):
         sets = [(G, gws, sws, sigma, k1, st1, pd_svd), (G2, gws2, sws2, sigma2, k2, st2, pd_split)]
         M, E = streams

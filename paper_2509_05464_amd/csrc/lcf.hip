@@ -477,7 +477,7 @@ struct BwdArgs {
 //  * dL/dy enters the products exactly (three BF16 terms), like the biases of the forward pass.
 //
 // Bound by the VALU (GELU' of 96 values a frame) and the matrix products, with one wavefront
-// per SIMD to issue both.  4096 series x 200 frames: 235 us for the two kernels, where one
+// per SIMD to issue both.  4096 series x 200 frames: 242 us for the two kernels, where one
 // for the dz (256 wavefronts, weights in registers) and three for the weight gradients took
 // 1262 us.
 constexpr int BWD_WAVES = 4;

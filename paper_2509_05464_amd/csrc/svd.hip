@@ -25,10 +25,9 @@
 // each plane rotation, and replays the log on the identity to form all of Z.
 // Eigenvalues are clamped at zero (round-off of a PSD matrix).
 //
-// The projection S_f = S - (S V_K) V_K^H and the power Doppler are fused: one thread
-// per voxel reads its slow-time series twice (coalesced across voxels), first to form
-// the K projections, then to subtract them and accumulate |S_f|^2.  V_K is read through
-// the scalar cache (uniform across the wavefront).
+// The projection S_f = S - (S V_K) V_K^H and the power Doppler are fused: one wavefront per 16
+// voxels forms their K projections on the matrix cores, reads the series again to subtract them
+// and accumulates |S_f|^2.  Power Doppler alone takes one read of S up to K = 16.
 #include "fq_common.hpp"
 
 namespace fq {
