@@ -99,7 +99,7 @@ __device__ __forceinline__ void elem_resp(const FdArgs& a, double dxc, double dy
 #pragma unroll
     for (int q = 0; q < KC; ++q) h[q] = make_float2(0.f, 0.f);
     float h0 = 0.0f;   // the response at f = 0
-    const float jm = (float)(j0 + M);
+    const float jm = (float)(j0 + M), tmin = 1e-12f * __builtin_amdgcn_rcpf((float)(j0 + KC));
     for (int mx = 0; mx < a.vx; ++mx) {
         const double dx = dxc - ((mx + 0.5) / a.vx - 0.5) * a.wx;
         const double dx2 = fma(dx, dx, sz2);
@@ -136,8 +136,12 @@ __device__ __forceinline__ void elem_resp(const FdArgs& a, double dxc, double dy
             }
             // sinc(2 pi j t) = sin(2 pi j t) / (2 pi j t), t = b df u / c turns per frequency step, the
             // sine straight from the hardware (argument reduced to a turn); 1 / j^2 of both axes
-            // comes last.  In a direction of exactly zero j stands for the sine.
+            // comes last.  Where |j t| stays below 1e-12 (an offset of about 1e-14 m: the rounding
+            // error of an element's position, seen from a scatterer on its axis) j stands for the
+            // sine: the product of two such t, in the one reciprocal of both axes, is below FP32's
+            // range and its reciprocal infinite.
             const float tx = (float)(a.bx_df_c * dx) * rinv, ty = (float)(a.by_df_c * dy) * rinv;
+            const bool axis_x = fabsf(tx) < tmin, axis_y = fabsf(ty) < tmin;
             float d[KC];
             {
                 float s[KC];
@@ -151,18 +155,18 @@ __device__ __forceinline__ void elem_resp(const FdArgs& a, double dxc, double dy
                     const float c = ty * (float)(j0 + q);
                     s[q] = __builtin_amdgcn_sinf(c - floorf(c));
                 }
-                if (tx == 0.0f) {
+                if (axis_x) {
 #pragma unroll
                     for (int q = 0; q < KC; ++q) d[q] = (float)(j0 + q);
                 }
-                if (ty == 0.0f) {
+                if (axis_y) {
 #pragma unroll
                     for (int q = 0; q < KC; ++q) s[q] = (float)(j0 + q);
                 }
 #pragma unroll
                 for (int q = 0; q < KC; ++q) d[q] *= s[q];
             }
-            g *= __builtin_amdgcn_rcpf((tx != 0.0f ? (float)TWO_PI * tx : 1.0f) * (ty != 0.0f ? (float)TWO_PI * ty : 1.0f));
+            g *= __builtin_amdgcn_rcpf((axis_x ? 1.0f : (float)TWO_PI * tx) * (axis_y ? 1.0f : (float)TWO_PI * ty));
             float2 z = make_float2(zm.x * g, zm.y * g);
             const float2 z0 = z;
 #pragma unroll
