@@ -91,6 +91,30 @@ __device__ __forceinline__ void elem_xy(const FdArgs& a, int e, double& ex, doub
     ey = (e / a.nx_el) * a.pitch_y - a.hy;
 }
 
+// h[q] += g z_q 2^(-ar (j0 + q)) d[q] (d: null for 1), z_q unit phases stepped outwards from the
+// middle's zm by st, every amplitude by its own exponential: for a scatterer whose amplitude
+// at the middle, or its growth from there down, is past FP32's range.
+__device__ __forceinline__ void faint_resp(float2 zm, float2 st, float g, float ar, int j0, const float* d, float2* h) {
+    constexpr int M = KC / 2;
+    auto put = [&](int q, float2 z) {
+        const float s = g * __builtin_amdgcn_exp2f(-ar * (float)(j0 + q)) * (d ? d[q] : 1.0f);
+        h[q].x = fmaf(z.x, s, h[q].x);
+        h[q].y = fmaf(z.y, s, h[q].y);
+    };
+    float2 z = zm;
+#pragma unroll
+    for (int q = M; q < KC; ++q) {
+        put(q, z);
+        z = cmul(z, st);
+    }
+    z = zm;
+#pragma unroll
+    for (int q = M - 1; q >= 0; --q) {
+        z = cmul(z, make_float2(st.x, -st.y));
+        put(q, z);
+    }
+}
+
 // h[q] = sum_mu (r_ref/r) e^{(i k - alpha) r} D for f = (j0 + q) df, q < KC, of an element whose
 // centre is (dxc, dyc) off the scatterer; D = sinc sinc of the sub-element's direction.
 __device__ __forceinline__ void elem_resp(const FdArgs& a, double dxc, double dyc, double sz2, int j0,
@@ -115,8 +139,14 @@ __device__ __forceinline__ void elem_resp(const FdArgs& a, double dxc, double dy
             const float2 up = make_float2(st.x * at, st.y * at), dn = make_float2(st.x * ai, -st.y * ai);
             float g = a.r_ref * rinv;
             h0 += g;
-            g *= __builtin_amdgcn_exp2f(-ar * jm);
+            // 2^-100 at the middle: a step down then grows by 2^25 at most (j0 >= 0), four by 2^100
+            const bool faint = ar * jm > 100.0f;
             if (!a.dir) {
+                if (faint) {
+                    faint_resp(zm, st, g, ar, j0, nullptr, h);
+                    continue;
+                }
+                g *= __builtin_amdgcn_exp2f(-ar * jm);
                 float2 z = make_float2(zm.x * g, zm.y * g);
                 const float2 z0 = z;
 #pragma unroll
@@ -167,6 +197,11 @@ __device__ __forceinline__ void elem_resp(const FdArgs& a, double dxc, double dy
                 for (int q = 0; q < KC; ++q) d[q] *= s[q];
             }
             g *= __builtin_amdgcn_rcpf((axis_x ? 1.0f : (float)TWO_PI * tx) * (axis_y ? 1.0f : (float)TWO_PI * ty));
+            if (faint) {
+                faint_resp(zm, st, g, ar, j0, d, h);
+                continue;
+            }
+            g *= __builtin_amdgcn_exp2f(-ar * jm);
             float2 z = make_float2(zm.x * g, zm.y * g);
             const float2 z0 = z;
 #pragma unroll

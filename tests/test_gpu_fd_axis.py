@@ -42,3 +42,23 @@ def test_scatterers_on_the_axis_of_an_odd_array(gpu, n, pitch, n_sub, n_tx):
     """The centre element's position is the rounding error of its coordinate (1e-20 m), so the
     direction cosines on the axis are about 1e-20 and not zero."""
     check((n, n), pitch, n_tx, [[0.0, 0.0, 5e-3], [0.0, 0.0, 8e-3], [0.0, 0.3e-3, 6e-3]], 360, n_sub)
+
+
+@pytest.mark.parametrize('n_tx', [1, 4])
+@pytest.mark.parametrize('far', [12.0, 30.0, 1e4, 1e8])
+def test_attenuation_of_a_far_scatterer(gpu, n_tx, far):
+    """A scatterer whose amplitude falls by 8 powers of two a frequency step and metre: from 16 m
+    on one step passes FP32's range.  Nothing is left of its echo, and nothing of the others' is
+    lost."""
+    pos = [[0.1e-3, -0.2e-3, 5e-3], [0.0, 0.0, far], [-0.3e-3, 0.1e-3, 6e-3]]
+    check((4, 3), 0.3e-3, n_tx, pos, 270, atten=5.0)
+    check((4, 3), 0.3e-3, n_tx, pos, 270, width=0.0, atten=5.0)
+
+
+@pytest.mark.parametrize('n_tx', [1, 4])
+@pytest.mark.parametrize('width', [0.0, 0.9])
+@pytest.mark.parametrize('z', [10e-3, 20e-3, 40e-3])
+def test_band_from_zero_under_strong_attenuation(gpu, n_tx, width, z):
+    """A record of one sample has a band of 22 frequencies from 0 on, 0.7 MHz apart: the amplitude
+    falls by 12, 24 or 48 powers of two a step, and the lowest frequencies are all that is left."""
+    check((3, 4), 0.3e-3, n_tx, [[0.2e-3, -0.1e-3, z]], 1, width=width, atten=99.0)
