@@ -295,11 +295,16 @@ int das_prepare(const fq_probe* probe, const fq_tx* tx, const fq_grid* grid, int
     ia.T = P.T;
     ia.TR = TR;
     ia.FB = P.fb;
-    ia.stride = (TR + IQ_RUN - 1) / IQ_RUN * IQ_RUN + 2 * FIR_HALF + 1;   // odd: frames fall in different banks
+    // Room for the inputs of every sample, odd (frames fall in different banks).  The samples of a
+    // last run past the record read up to IQ_RUN - 1 values into the next trace, or behind the
+    // last one, and are not stored: with rows of whole runs 8 frames of 5085 to 5087 samples
+    // would not fit.
+    ia.stride = (TR + 2 * FIR_HALF) | 1;
     ia.fc_fs = probe->fc_hz / probe->fs_hz;
     make_taps(probe->fc_hz, probe->fs_hz, ia.taps);
-    P.iq_lds = sizeof(float) * P.fb * (size_t)ia.stride;
-    FQ_REQUIRE(sizeof(float) * DAS_MAX_FB * (size_t)(P.T + 2 * FIR_HALF + 1) <= 160 * 1024,
+    P.iq_lds = sizeof(float) * (P.fb * (size_t)ia.stride + IQ_RUN - 1);
+    // (one limit for every number of frames: that of a block of 8)
+    FQ_REQUIRE(P.iq_lds <= 160 * 1024 && sizeof(float) * DAS_MAX_FB * (size_t)(P.T + 2 * FIR_HALF + 1) <= 160 * 1024,
                "n_samples too large for on-chip demodulation");
 
     DasArgs& da = P.da;
