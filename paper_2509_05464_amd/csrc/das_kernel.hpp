@@ -151,6 +151,7 @@ __global__ void __launch_bounds__(G == 1 ? DAS_THREADS : DAS_SPLIT_THREADS, WIDE
     float2 ptx[AT];
     const uint32_t smax = ((uint32_t)(a.W - NT) << SH) | MASK;
     constexpr double ONE = (double)(1u << SH);
+    double tlo = 1e300;
 #pragma unroll
     for (int j = 0; j < AT; ++j) {
         const double lo = (a.ux[j] * (a.ux[j] > 0 ? bx0 : bx1) + a.uy[j] * (a.uy[j] > 0 ? by0 : by1) + a.uz[j] * bz0) *
@@ -158,6 +159,7 @@ __global__ void __launch_bounds__(G == 1 ? DAS_THREADS : DAS_SPLIT_THREADS, WIDE
         const double hi = (a.ux[j] * (a.ux[j] > 0 ? bx1 : bx0) + a.uy[j] * (a.uy[j] > 0 ? by1 : by0) + a.uz[j] * bz1) *
                               a.fs_c - a.t0s[j];
         const double fl = floor(lo) - 1.0;
+        tlo = fmin(tlo, fl);
         if (lane == j) {
             l_tlo = (int)fl;
             l_dtx = (int)ceil((hi - fl) * 16.0);
@@ -178,6 +180,12 @@ __global__ void __launch_bounds__(G == 1 ? DAS_THREADS : DAS_SPLIT_THREADS, WIDE
             for (int q = 0; q < FB; ++q) acc[j][k][q] = make_float2(0.0f, 0.0f);
 
     const int ny_el = a.E / a.nx_el;
+    // A tile whose nearest delay lies past the record sums nothing.  (Its rows' byte offsets could
+    // also wrap at 2^32; a tile that reaches back into the record is too near for that.)
+    const double hx = fabs(0.5 * (a.nx_el - 1) * a.pitch_x), hy = fabs(0.5 * (ny_el - 1) * a.pitch_y);
+    const double nx = fmax(fmax(bx0 - hx, -hx - bx1), 0.0), ny = fmax(fmax(by0 - hy, -hy - by1), 0.0);
+    const bool past = __builtin_amdgcn_readfirstlane(
+        tlo + floor(sqrt(nx * nx + ny * ny + bz0 * bz0) * a.fs_c) - 2.0 > (double)a.TR);
     const int64_t trace_bytes = (int64_t)a.TR * ROWG;
     const char* bb = a.bb + ((int64_t)fbl * a.A + a.a0) * a.E * trace_bytes;
 
@@ -188,7 +196,7 @@ __global__ void __launch_bounds__(G == 1 ? DAS_THREADS : DAS_SPLIT_THREADS, WIDE
     double pex_n = 0.0, pey_n = 0.0;   // of the element whose rows are requested next
     int rlo_n = 0, drx_n = 0;
     // n counts the elements of this group
-    const int n_el = G == 1 ? a.E : (a.E - grp + G - 1) / G;
+    const int n_el = past ? 0 : G == 1 ? a.E : (a.E - grp + G - 1) / G;
     auto element = [&](int n) {
         if ((n & 63) == 0) {
             const int el = min((n + lane) * G + grp, a.E - 1);
@@ -337,9 +345,9 @@ __global__ void __launch_bounds__(G == 1 ? DAS_THREADS : DAS_SPLIT_THREADS, WIDE
     using IH = std::integral_constant<int, H1>;
     using IA = std::integral_constant<int, AT>;
     // (a group that is out of elements keeps the barriers of the others)
-    const int n_max = G == 1 ? a.E : (a.E + G - 1) / G;
+    const int n_max = past ? 0 : G == 1 ? a.E : (a.E + G - 1) / G;
     element(0);
-    if (G == 1 || n_el > 0) request(winA, I0{}, IH{}, 0, rlo_n, drx_n);
+    if (n_el > 0) request(winA, I0{}, IH{}, 0, rlo_n, drx_n);
     if (AT > 1) {
         for (int n = 0; n < n_max; ++n) {
             const bool live = G == 1 || n < n_el;
