@@ -114,29 +114,33 @@ __global__ void __launch_bounds__(DISP_THREADS) db_kernel(const float* in, int64
 // keeps 1024 waves of independent reads in flight where one thread per pixel kept 64
 // waves in a chain of 64 reads (13.6 us).
 constexpr int MIP_SEG = 16;
+constexpr int64_t MIP_MAX_BLOCKS = 1 << 20;   // (a launch holds 2^32 threads) larger planes loop
 
 __global__ void __launch_bounds__(64 * MIP_SEG) mip_strided_kernel(const float* vol, int nx, int ny, int nz,
                                                                   int over_z, float* out) {
     __shared__ float s[MIP_SEG][64];
     const int l = threadIdx.x & 63, seg = threadIdx.x >> 6;
-    const int64_t idx = (int64_t)blockIdx.x * 64 + l;
     const int64_t n_out = over_z ? (int64_t)nx * ny : (int64_t)nx * nz;
-    float m = -INFINITY;
-    if (idx < n_out) {
-        // over z: pixel (ix, iy) is voxel idx of every plane; over y: pixel (ix, iz) starts at row iz * ny
-        const int64_t o = idx / nx, plane = (int64_t)nx * ny;
-        const float* src = vol + (over_z ? idx : idx + o * (plane - nx));
-        const int64_t stride = over_z ? plane : nx;
-        const int len = over_z ? nz : ny;
+    for (int64_t i0 = (int64_t)blockIdx.x * 64; i0 < n_out; i0 += (int64_t)gridDim.x * 64) {
+        const int64_t idx = i0 + l;
+        float m = -INFINITY;
+        if (idx < n_out) {
+            // over z: pixel (ix, iy) is voxel idx of every plane; over y: pixel (ix, iz) starts at row iz * ny
+            const int64_t o = idx / nx, plane = (int64_t)nx * ny;
+            const float* src = vol + (over_z ? idx : idx + o * (plane - nx));
+            const int64_t stride = over_z ? plane : nx;
+            const int len = over_z ? nz : ny;
 #pragma unroll 4
-        for (int k = seg; k < len; k += MIP_SEG) m = fmaxf(m, src[k * stride]);
-    }
-    s[seg][l] = m;
-    __syncthreads();
-    if (seg == 0 && idx < n_out) {
+            for (int k = seg; k < len; k += MIP_SEG) m = fmaxf(m, src[k * stride]);
+        }
+        s[seg][l] = m;
+        __syncthreads();
+        if (seg == 0 && idx < n_out) {
 #pragma unroll
-        for (int k = 1; k < MIP_SEG; ++k) m = fmaxf(m, s[k][l]);
-        out[idx] = m;
+            for (int k = 1; k < MIP_SEG; ++k) m = fmaxf(m, s[k][l]);
+            out[idx] = m;
+        }
+        __syncthreads();
     }
 }
 
@@ -210,7 +214,7 @@ extern "C" int mip(const float* vol, int32_t nx, int32_t ny, int32_t nz, int32_t
     } else {
         const int over_z = plane == FQ_MIP_XY ? 1 : 0;
         const int64_t n_out = over_z ? (int64_t)nx * ny : (int64_t)nx * nz;
-        const unsigned nb = (unsigned)((n_out + 63) / 64);
+        const unsigned nb = (unsigned)std::min<int64_t>((n_out + 63) / 64, MIP_MAX_BLOCKS);
         hipLaunchKernelGGL(mip_strided_kernel, dim3(nb), dim3(64 * MIP_SEG), 0, s, vol, nx, ny, nz, over_z, out);
     }
     FQ_LAUNCH_CHECK();
