@@ -929,7 +929,9 @@ __global__ void fb_partial_kernel(const float* pl, const float* ps, int64_t n, d
 }
 
 // Every block reduces the partials itself, in the same order (12 KB out of L2), and block
-// 0 stores the judgement: one thread adding them alone took 60 us.
+// 0 stores the judgement: one thread adding them alone took 60 us.  Eight blocks a compute unit at
+// most share the values: a block for every 256 of 20 million took 214 us, mostly reductions, as
+// against 148 before the partials were reduced here.
 __global__ void __launch_bounds__(256) fb_select_kernel(const float* pl, const float* ps, int64_t n, const double* part,
                                                         int nblk, float tau_db, int* flag, float* d_db, float* out) {
     __shared__ double s[3][4];
@@ -952,11 +954,12 @@ __global__ void __launch_bounds__(256) fb_select_kernel(const float* pl, const f
         *flag = f;
         *d_db = a[2] > 0.0 ? __builtin_nanf("") : (float)d;
     }
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i < n) out[i] = f ? ps[i] : pl[i];
+    const float* src = f ? ps : pl;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) out[i] = src[i];
 }
 
 constexpr int FB_BLOCKS = 512;
+constexpr int64_t FB_SELECT_BLOCKS = 2048;
 
 size_t fwd_lds(int T) {   // the launch below takes the streamed kernel above 256 frames
     const int TP = 32 * ((T + 31) / 32) + 8;
@@ -1056,7 +1059,7 @@ extern "C" int lcf_fallback(const float* pd_l, const float* pd_s, int64_t n, flo
     double* part = reinterpret_cast<double*>(ws);
     hipLaunchKernelGGL(fb_partial_kernel, dim3(FB_BLOCKS), dim3(256), 0, s, pd_l, pd_s, n, part);
     FQ_LAUNCH_CHECK();
-    hipLaunchKernelGGL(fb_select_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, pd_l, pd_s, n, part,
+    hipLaunchKernelGGL(fb_select_kernel, dim3((unsigned)std::min<int64_t>((n + 255) / 256, FB_SELECT_BLOCKS)), dim3(256), 0, s, pd_l, pd_s, n, part,
                        FB_BLOCKS, tau_db, flag, d_db, out);
     FQ_LAUNCH_CHECK();
     return FQ_OK;
