@@ -50,8 +50,9 @@ constexpr int EB = 16;        // elements per LDS block (transmit field) and wav
 constexpr int SB = 32;        // scatterers per LDS block (echo)
 constexpr int FD_MAX_K = 4096;
 constexpr int FD_MIN_BLOCK = 256;
-constexpr int MC = 8;         // elements of an inverse-transform workgroup
+constexpr int MC = 8;         // elements of an inverse-transform workgroup, at most
 constexpr int MC_MAX_K = 1024;   // band that MC elements' spectra fit in LDS for; two beyond
+constexpr int64_t IDFT_WG = 1024;   // inverse-transform workgroups that fill the chip
 constexpr double TWO_PI = 6.283185307179586;
 
 struct FdArgs {
@@ -565,6 +566,7 @@ __global__ void __launch_bounds__(FD_THREADS) fd_idft_kernel(const FdArgs a) {
             const int64_t ph = ((int64_t)(a.j_lo + k0) * t) % a.N;
             float2 z = cis_cycles(-(double)ph / a.N);
             const int k1 = min(a.K, k0 + 64);
+#pragma unroll 4
             for (int kk = k0; kk < k1; ++kk) {
 #pragma unroll
                 for (int c = 0; c < NM; ++c) {
@@ -594,6 +596,18 @@ FdFn fd_fn(bool tx, int na) {
         if (na == NA) return tx ? fd_tx_kernel<NA> : fd_rx_kernel<NA>;
         return fd_fn<NA + 1>(tx, na);
     }
+}
+
+// Elements of an inverse-transform workgroup: they share the stepped exponential, so as many as
+// leave IDFT_WG workgroups (a launch, 1500 samples: 32 elements, 6 transmits at 8 483 us, at 1
+// 124; 16 x 16 elements, 9 transmits at 8 564, at 2 375).
+int idft_elements(int E, int K, int64_t transmits) {
+    int nm = K <= MC_MAX_K ? MC : 2;
+    while (nm > 1 && (E + nm - 1) / nm * transmits < IDFT_WG) nm /= 2;
+    return nm;
+}
+FdFn idft_fn(int nm) {
+    return nm == 8 ? fd_idft_kernel<8> : nm == 4 ? fd_idft_kernel<4> : nm == 2 ? fd_idft_kernel<2> : fd_idft_kernel<1>;
 }
 
 __global__ void fd_weights_kernel(float* w, int K, int j_lo, int N, double df, double fc, double sig) {
@@ -794,9 +808,9 @@ extern "C" int fd_synth(const fq_probe* probe, const fq_tx* tx, const fq_pulse* 
             }
             a.frame0 = f;
             a.n_frames_out = pos_static ? n_frames : 1;
-            const int nm = pl.K <= MC_MAX_K ? MC : 2;
-            hipLaunchKernelGGL(nm == MC ? fd_idft_kernel<MC> : fd_idft_kernel<2>, dim3((E + nm - 1) / nm, a.na, nb),
-                               dim3(FD_THREADS), sizeof(float2) * (size_t)pl.K * nm, s, a);
+            const int nm = idft_elements(E, pl.K, (int64_t)a.na * nb);
+            hipLaunchKernelGGL(idft_fn(nm), dim3((E + nm - 1) / nm, a.na, nb), dim3(FD_THREADS),
+                               sizeof(float2) * (size_t)pl.K * nm, s, a);
             FQ_LAUNCH_CHECK();
         }
     }
