@@ -109,19 +109,17 @@ __global__ void __launch_bounds__(DISP_THREADS) db_kernel(const float* in, int64
     }
 }
 
-// MIP onto x-y (max over z) or x-z (max over y): a workgroup takes 64 consecutive output
-// pixels, its 16 waves share the planes (or rows) of the reduction, so that a 64^3 volume
-// keeps 1024 waves of independent reads in flight where one thread per pixel kept 64
-// waves in a chain of 64 reads (13.6 us).
-constexpr int MIP_SEG = 16;
+// MIP onto x-y (max over z) or x-z (max over y): SEG wavefronts share the planes (or rows) of 64
+// consecutive output pixels (mip_segments).
 constexpr int64_t MIP_MAX_BLOCKS = 1 << 20;   // (a launch holds 2^32 threads) larger planes loop
-
-__global__ void __launch_bounds__(64 * MIP_SEG) mip_strided_kernel(const float* vol, int nx, int ny, int nz,
-                                                                  int over_z, float* out) {
-    __shared__ float s[MIP_SEG][64];
-    const int l = threadIdx.x & 63, seg = threadIdx.x >> 6;
+template <int SEG>
+__global__ void __launch_bounds__(SEG > 4 ? 64 * SEG : 256) mip_strided_kernel(const float* vol, int nx, int ny, int nz,
+                                                                              int over_z, float* out) {
+    constexpr int PIX = SEG >= 4 ? 64 : 256 / SEG;   // pixels of a workgroup
+    __shared__ float s[SEG > 1 ? SEG : 1][SEG > 1 ? PIX : 1];
+    const int l = threadIdx.x % PIX, seg = threadIdx.x / PIX;
     const int64_t n_out = over_z ? (int64_t)nx * ny : (int64_t)nx * nz;
-    for (int64_t i0 = (int64_t)blockIdx.x * 64; i0 < n_out; i0 += (int64_t)gridDim.x * 64) {
+    for (int64_t i0 = (int64_t)blockIdx.x * PIX; i0 < n_out; i0 += (int64_t)gridDim.x * PIX) {
         const int64_t idx = i0 + l;
         float m = -INFINITY;
         if (idx < n_out) {
@@ -131,13 +129,17 @@ __global__ void __launch_bounds__(64 * MIP_SEG) mip_strided_kernel(const float* 
             const int64_t stride = over_z ? plane : nx;
             const int len = over_z ? nz : ny;
 #pragma unroll 4
-            for (int k = seg; k < len; k += MIP_SEG) m = fmaxf(m, src[k * stride]);
+            for (int k = seg; k < len; k += SEG) m = fmaxf(m, src[k * stride]);
+        }
+        if (SEG == 1) {
+            if (idx < n_out) out[idx] = m;
+            continue;
         }
         s[seg][l] = m;
         __syncthreads();
         if (seg == 0 && idx < n_out) {
 #pragma unroll
-            for (int k = 1; k < MIP_SEG; ++k) m = fmaxf(m, s[k][l]);
+            for (int k = 1; k < SEG; ++k) m = fmaxf(m, s[k][l]);
             out[idx] = m;
         }
         __syncthreads();
@@ -162,6 +164,12 @@ int blocks_for(int64_t n, int per_thread) {
     const int64_t per = (int64_t)DISP_THREADS * per_thread;
     return (int)std::max<int64_t>(1, std::min<int64_t>(DISP_MAX_BLOCKS, (n + per - 1) / per));
 }
+
+// Wavefronts that share 64 pixels' reduction: few pixels leave the chip idle in chains of dependent
+// reads, many are a stream of their own and only pay for the exchange.  1, 4 and 16 wavefronts:
+// 128 x 128 pixels of 1024 planes 68, 20, 11 us; 256 x 256 of 256 planes 20, 11, 11; 1024 x 1024 of 8
+// planes 10, 10, 28 and of 64 planes 42, 39, 47; 4096 x 4096 of 4 planes 62, 135, 503.
+int mip_segments(int64_t pixels) { return pixels <= 32768 ? 16 : pixels <= 524288 ? 4 : 1; }
 
 template <bool IQ>
 int launch_display(const float* in, int64_t n, float* part, float* peak, float neg_dr, int unit, float* out,
@@ -214,8 +222,11 @@ extern "C" int mip(const float* vol, int32_t nx, int32_t ny, int32_t nz, int32_t
     } else {
         const int over_z = plane == FQ_MIP_XY ? 1 : 0;
         const int64_t n_out = over_z ? (int64_t)nx * ny : (int64_t)nx * nz;
-        const unsigned nb = (unsigned)std::min<int64_t>((n_out + 63) / 64, MIP_MAX_BLOCKS);
-        hipLaunchKernelGGL(mip_strided_kernel, dim3(nb), dim3(64 * MIP_SEG), 0, s, vol, nx, ny, nz, over_z, out);
+        const int seg = mip_segments(n_out);
+        const int pix = seg >= 4 ? 64 : 256 / seg;
+        const unsigned nb = (unsigned)std::min<int64_t>((n_out + pix - 1) / pix, MIP_MAX_BLOCKS);
+        auto kern = seg == 16 ? mip_strided_kernel<16> : seg == 4 ? mip_strided_kernel<4> : mip_strided_kernel<1>;
+        hipLaunchKernelGGL(kern, dim3(nb), dim3(seg * pix), 0, s, vol, nx, ny, nz, over_z, out);
     }
     FQ_LAUNCH_CHECK();
     return FQ_OK;
