@@ -194,6 +194,12 @@ int das_delay_sum(const fq_probe* probe, const fq_tx* tx, const fq_grid* grid, i
  * the error text) for invalid arguments. */
 int das_window_rows(const fq_probe* probe, const fq_tx* tx, const fq_grid* grid);
 
+/* Host-only query (no device work): how das_beamform and das_delay_sum split a call.
+ *  shape  int64 [5] (host): frames of a block, transmits of a pass over the elements, element
+ *         groups of a workgroup (1, 4 or 16), 1 if the delay windows pass 248 rows, voxel tiles. */
+int das_launch_shape(const fq_probe* probe, const fq_tx* tx, const fq_grid* grid, int32_t n_frames,
+                     int32_t n_samples, int32_t interp, int64_t* shape);
+
 /* ---------------------------------------------------------------------------------
  * casorati_gram -- G = S^H S for the Casorati matrix S[v][f] = iq[f][v] (Section 2.4.2:
  * the SVD clutter filter works on S; its right singular vectors and squared singular

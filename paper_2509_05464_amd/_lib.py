@@ -112,6 +112,7 @@ _SIGS = {
     'das_demodulate': (ctypes.c_int, [_P(Probe), _P(Tx), _i32, _i32, _vp, _vp, _sz, _vp]),
     'das_delay_sum': (ctypes.c_int, [_P(Probe), _P(Tx), _P(Grid), _i32, _i32, _i32, _vp, _sz, _vp, _vp]),
     'das_window_rows': (ctypes.c_int, [_P(Probe), _P(Tx), _P(Grid)]),
+    'das_launch_shape': (ctypes.c_int, [_P(Probe), _P(Tx), _P(Grid), _i32, _i32, _i32, _P(_i64)]),
     'gram_workspace_size': (_sz, [_i64, _i32, _i32]),
     'casorati_gram': (ctypes.c_int, [_vp, _i64, _i32, _i32, _vp, _sz, _vp, _vp]),
     'casorati_gram_noalloc': (ctypes.c_int, [_vp, _i64, _i32, _i32, _vp, _vp]),
@@ -217,6 +218,15 @@ def das_window_rows(probe: Probe, tx: Tx, grid: Grid) -> int:
     if w < 0:
         _check("das_window_rows", FQ_E_INVALID)
     return int(w)
+
+
+def das_launch_shape(probe: Probe, tx: Tx, grid: Grid, n_frames: int, n_samples: int,
+                     interp: int = INTERP_LINEAR) -> Tuple[int, ...]:
+    """(frames of a block, transmits of a pass, element groups, wide windows, voxel tiles) of a call (host query)."""
+    shape = (_i64 * 5)()
+    _check('das_launch_shape', lib().das_launch_shape(ctypes.byref(probe), ctypes.byref(tx), ctypes.byref(grid), n_frames,
+                                                      n_samples, interp, shape))
+    return tuple(shape)
 
 
 def das_beamform(probe: Probe, tx: Tx, grid: Grid, rf: torch.Tensor, iq: torch.Tensor, ws: torch.Tensor,

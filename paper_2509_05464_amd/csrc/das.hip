@@ -199,6 +199,8 @@ bool choose_launch(const fq_grid& g, const TxHost& th, double fs_c, int A, int f
     for (int groups : {1, 4, 16}) {
         DasTile t{};
         if (!choose_tile(g, th, fs_c, A, fb, groups, t)) continue;
+        // (a launch holds 2^32 threads: beyond, one group's 256 a tile are the fewest)
+        if (groups > 1 && t.ntx * t.nty * t.ntz * nfb * DAS_SPLIT_THREADS >= (1LL << 32)) continue;
         const double per_cu = (double)(t.ntx * t.nty * t.ntz) * nfb / 256.0;
         double time;
         if (groups == 1) {
@@ -238,6 +240,27 @@ extern "C" int das_window_rows(const fq_probe* probe, const fq_tx* tx, const fq_
         return -1;
     }
     return window_rows(*grid, make_tx(*probe, *tx), probe->fs_hz / probe->c_mps, TILE_X, TILE_Y, TILE_Z);
+}
+
+extern "C" int das_launch_shape(const fq_probe* probe, const fq_tx* tx, const fq_grid* grid, int32_t n_frames,
+                                int32_t n_samples, int32_t interp, int64_t* shape) {
+    const int st = check_probe_tx(probe, tx);
+    if (st != FQ_OK) return st;
+    FQ_REQUIRE(grid && grid->nx > 0 && grid->ny > 0 && grid->nz > 0 && grid->dx > 0 && grid->dy > 0 && grid->dz > 0,
+               "bad grid");
+    FQ_REQUIRE(n_frames >= 1 && n_samples >= 2 && shape, "bad n_frames / n_samples / shape");
+    const TxHost th = make_tx(*probe, *tx);
+    int nfb, fb, TR;
+    frame_blocks(n_frames, n_samples, nfb, fb, TR);
+    DasTile t{};
+    FQ_REQUIRE(choose_launch(*grid, th, probe->fs_hz / probe->c_mps, th.n, fb, nfb, interp, t),
+               "voxel spacing too coarse for the on-chip delay window");
+    shape[0] = fb;
+    shape[1] = t.at;
+    shape[2] = t.groups;
+    shape[3] = t.wide ? 1 : 0;
+    shape[4] = t.ntx * t.nty * t.ntz;
+    return FQ_OK;
 }
 
 namespace fq {
