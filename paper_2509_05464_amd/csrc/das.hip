@@ -379,7 +379,6 @@ int launch_das(DasPlan& P, int fb0, int nb, int interp, const fq_grid* grid, dou
     da.nwork = (int64_t)da.ntiles * nb;
     const int threads = P.tile.groups == 1 ? DAS_THREADS : DAS_SPLIT_THREADS;
     FQ_REQUIRE(da.nwork * threads < (1LL << 32), "grid too large");
-    const double one = P.tile.wide ? (double)(1 << 22) : (double)(1 << 24);
     for (int a0 = 0; a0 < P.A; a0 += P.tile.at) {
         const int na = std::min(P.tile.at, P.A - a0);
         da.a0 = a0;
@@ -391,8 +390,11 @@ int launch_das(DasPlan& P, int fb0, int nb, int interp, const fq_grid* grid, dou
             da.uz[j] = P.th.uz[an];
             da.t0s[j] = P.th.t0[an] * fs_hz;
             const double step = P.th.uz[an] * grid->dz * P.fs_c;     // samples per z step
-            // (a window that fits has a step below 2^32 / one; a single plane or voxel takes none)
-            da.dzs[j] = grid->nz > 1 && P.tile.groups == 1 ? (uint32_t)std::floor(step * one + 0.5) : 0u;
+            // (a narrow window holds a step below 2^8 rows; a single plane or voxel takes none)
+            const double rows = P.tile.wide ? std::floor(step) : 0.0;
+            const bool steps = grid->nz > 1 && P.tile.groups == 1;
+            da.dzr[j] = steps ? (int)rows : 0;
+            da.dzs[j] = steps ? (uint32_t)std::floor((step - rows) * (1 << 24) + 0.5) : 0u;
             const double cyc = step * da.fc_fs;
             const double fr = cyc - std::floor(cyc);
             da.zeta[j] = make_float2((float)std::cos(2 * M_PI * fr), (float)std::sin(2 * M_PI * fr));

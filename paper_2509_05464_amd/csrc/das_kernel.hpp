@@ -16,11 +16,11 @@
 //    half being summed, into two LDS arrays that take turns: one barrier per half.  Rows
 //    outside the record read as zero through the buffer descriptor's bounds.  Only the
 //    rows between the tile's nearest and farthest delay are fetched.
-//  * Delays are 32-bit fixed point with SH fraction bits: a transmit part per (voxel,
+//  * Delays are 32-bit fixed point with 24 fraction bits: a transmit part per (voxel,
 //    transmit) and a receive part per (voxel, element), both relative to integer row
 //    bases of the tile and rounded once from FP64.  One integer add gives row and
-//    fraction (the fraction, below 2^24, converts to FP32 exactly; its scale 2^-SH is
-//    folded into the phase factor).
+//    fraction (the fraction, below 2^24, converts to FP32 exactly; its scale 2^-24 is
+//    folded into the phase factor).  Windows beyond 248 rows keep whole rows beside it.
 //  * The phase exp(i 2 pi fc tau) is a per-(voxel, transmit) factor times a
 //    per-(voxel, element) factor, each from an FP64 cycle count.  With few frames
 //    (AT * FB <= 16) every transmit keeps its own sums and its factor is applied once at
@@ -78,6 +78,7 @@ struct DasArgs {
     float inv_A;
     double ux[DAS_MAX_AT], uy[DAS_MAX_AT], uz[DAS_MAX_AT], t0s[DAS_MAX_AT];   // t0s = t0 * fs
     uint32_t dzs[DAS_MAX_AT];                                // transmit delay of one z step, fixed point
+    int dzr[DAS_MAX_AT];                                     // its whole rows (wide windows)
     float2 zeta[DAS_MAX_AT];                                 // exp(i 2 pi fc uz dz / c)
 };
 
@@ -95,7 +96,7 @@ __global__ void __launch_bounds__(G == 1 ? DAS_THREADS : DAS_SPLIT_THREADS, WIDE
     constexpr int TPG = das_group_threads(G), WPG = TPG / 64;   // threads and wavefronts of a group
     constexpr int NT = INTERP ? 4 : 2;         // taps per delay
     constexpr int J0 = INTERP ? -1 : 0;        // first tap offset
-    constexpr int SH = WIDE ? 22 : 24;         // fraction bits of a delay
+    constexpr int SH = 24;                     // fraction bits of a delay
     constexpr uint32_t MASK = (1u << SH) - 1u;
     constexpr int ROWG = 8 * FB;               // row bytes in the baseband
     constexpr int ROWL = das_row_lds(FB);      // row bytes in LDS
@@ -148,6 +149,7 @@ __global__ void __launch_bounds__(G == 1 ? DAS_THREADS : DAS_SPLIT_THREADS, WIDE
     // l_dtx the spread above it in 1/16 rows.
     int l_tlo = 0, l_dtx = 0;
     uint32_t ftx[AT];
+    int itx[AT];                               // wide windows: whole rows, ftx the fraction
     float2 ptx[AT];
     const uint32_t smax = ((uint32_t)(a.W - NT) << SH) | MASK;
     constexpr double ONE = (double)(1u << SH);
@@ -165,7 +167,9 @@ __global__ void __launch_bounds__(G == 1 ? DAS_THREADS : DAS_SPLIT_THREADS, WIDE
             l_dtx = (int)ceil((hi - fl) * 16.0);
         }
         const double x = (a.ux[j] * xv + a.uy[j] * yv + a.uz[j] * zv[0]) * a.fs_c - a.t0s[j];
-        ftx[j] = (uint32_t)fma(x - fl, ONE, 0.5);
+        const double xf = WIDE ? floor(x) : fl;
+        itx[j] = WIDE ? (int)(xf - fl) : 0;
+        ftx[j] = (uint32_t)fma(x - xf, ONE, 0.5);
         float2 p = cis_cycles(x * a.fc_fs);
         if (!INTERP) p = make_float2(p.x * (1.0f / ONE), p.y * (1.0f / ONE));   // the weights' scale
         ptx[j] = p;
@@ -247,6 +251,7 @@ __global__ void __launch_bounds__(G == 1 ? DAS_THREADS : DAS_SPLIT_THREADS, WIDE
     };
 
     uint32_t frx[VZ];
+    int irx[VZ];
     float2 prx[VZ];
     // receive geometry of the thread's voxels (FP64 distance, shared by all transmits)
     auto receive = [&](double pex, double pey, int rlo) {
@@ -256,7 +261,13 @@ __global__ void __launch_bounds__(G == 1 ? DAS_THREADS : DAS_SPLIT_THREADS, WIDE
 #pragma unroll
         for (int k = 0; k < VZ; ++k) {
             const double xr = sqrt_nr(fma(zv[k], zv[k], dxy2)) * a.fs_c;
-            frx[k] = (uint32_t)fma(xr, ONE, off);
+            if (WIDE) {
+                const double xf = floor(xr);
+                irx[k] = (int)xf - rlo;
+                frx[k] = (uint32_t)fma(xr - xf, ONE, 0.5);
+            } else {
+                frx[k] = (uint32_t)fma(xr, ONE, off);
+            }
             prx[k] = cis_cycles(xr * a.fc_fs);
         }
     };
@@ -272,8 +283,11 @@ __global__ void __launch_bounds__(G == 1 ? DAS_THREADS : DAS_SPLIT_THREADS, WIDE
             for (int k = 0; k < VZ; ++k) {
                 // The window holds every tap of the tile; the bound keeps the LDS reads in it
                 // whatever the input.
-                const uint32_t x = min(ftx[j] + frx[k] + (k ? a.dzs[j] : 0u), smax);
-                const char* rp = wj + (x >> SH) * (uint32_t)ROWL;
+                uint32_t x = ftx[j] + frx[k] + (k ? a.dzs[j] : 0u);
+                if (!WIDE) x = min(x, smax);
+                uint32_t row = x >> SH;
+                if (WIDE) row = (uint32_t)min(max(itx[j] + irx[k] + (int)row + (k ? a.dzr[j] : 0), 0), a.W - NT);
+                const char* rp = wj + row * (uint32_t)ROWL;
                 const float fr = (float)(x & MASK);
                 float w[NT];
                 if (INTERP == 0) {
