@@ -131,11 +131,13 @@ __device__ __forceinline__ void elem_resp(const FdArgs& a, double dxc, double dy
         const double dx2 = fma(dx, dx, sz2);
         for (int my = 0; my < a.vy; ++my) {
             const double dy = dyc - ((my + 0.5) / a.vy - 0.5) * a.wy;
-            const double r = sqrt_nr(fma(dy, dy, dx2));
+            // r and 1/r (to about 1e-14, rounded to FP32 once) from one estimate
+            const double d2 = fma(dy, dy, dx2), y = __builtin_amdgcn_rsq(d2), r0 = d2 * y;
+            const double r = fma(fma(-r0, r0, d2), 0.5 * y, r0);
+            const float rinv = (float)fma(fma(-r, y, 1.0), y, y);
             const double cyc = a.df_c * r;                        // phase cycles per frequency step
             const float2 zm = cis_cycles((double)(j0 + M) * cyc);
             const float2 st = cis_cycles(cyc);
-            const float rinv = __builtin_amdgcn_rcpf((float)r);
             const float ar = (float)(a.alpha2_df * r);
             const float at = __builtin_amdgcn_exp2f(-ar), ai = __builtin_amdgcn_exp2f(ar);
             const float2 up = make_float2(st.x * at, st.y * at), dn = make_float2(st.x * ai, -st.y * ai);
