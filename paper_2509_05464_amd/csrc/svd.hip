@@ -1402,6 +1402,8 @@ struct PdArgs {
 // MFMA 16x16x4 (FP32) lane layout: lane l supplies A[l%16][l/16] and B[l/16][l%16] and
 // holds D[4(l/16) + r][l%16], r = 0..3.
 typedef float floatx4 __attribute__((ext_vector_type(4)));
+// two samples of a row of the ensemble: rows of an odd number of voxels start on 8 bytes
+typedef float samples2 __attribute__((ext_vector_type(4), aligned(8)));
 constexpr int PV = 16;             // voxels per wavefront
 constexpr int PW = 4;              // wavefronts per workgroup
 // At most four workgroups a compute unit, V_K staged once for all of a workgroup's voxels.  A
@@ -1482,8 +1484,8 @@ __global__ void __launch_bounds__(64 * PW) project_mfma_kernel(const PdArgs a) {
         auto get2 = [&](int f0) {
             const float2* row = S + (int64_t)min(f0 + li, nt - 1) * a.nv;
             if (full) {
-                const float4* sp = reinterpret_cast<const float4*>(row + v0 + 4 * lk);
-                const float4 s0 = sp[0], s1 = sp[1];
+                const samples2* sp = reinterpret_cast<const samples2*>(row + v0 + 4 * lk);
+                const samples2 s0 = sp[0], s1 = sp[1];
                 sn[0] = make_float2(s0.x, s0.y);
                 sn[1] = make_float2(s0.z, s0.w);
                 sn[2] = make_float2(s1.x, s1.y);
@@ -1536,8 +1538,8 @@ __global__ void __launch_bounds__(64 * PW) project_mfma_kernel(const PdArgs a) {
             if (a.out && f < nt) {
                 float2* op = a.out + (int64_t)f * a.nv + v0 + 4 * lk;
                 if (full) {
-                    const floatx4 o0{sv[0].x, sv[0].y, sv[1].x, sv[1].y}, o1{sv[2].x, sv[2].y, sv[3].x, sv[3].y};
-                    floatx4* o = reinterpret_cast<floatx4*>(op);
+                    const samples2 o0{sv[0].x, sv[0].y, sv[1].x, sv[1].y}, o1{sv[2].x, sv[2].y, sv[3].x, sv[3].y};
+                    samples2* o = reinterpret_cast<samples2*>(op);
                     if (a.stream) {
                         __builtin_nontemporal_store(o0, o);
                         __builtin_nontemporal_store(o1, o + 1);
