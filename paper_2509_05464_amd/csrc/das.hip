@@ -190,10 +190,14 @@ bool choose_tile(const fq_grid& g, const TxHost& th, double fs_c, int A, int fb,
 // within 4% of the best of the three on average.  34 x 16 x 14 voxels, 4 frames, 576
 // elements, 5 transmits: 1125 us unsplit, 379 with 4 groups, 122 with 16; 35 x 33 x 61, 20
 // frames, cubic: 1209, 881, 997; 107 x 72 x 91, 2 frames: 247, 422, 896.
-bool choose_launch(const fq_grid& g, const TxHost& th, double fs_c, int A, int fb, int nfb, int interp, DasTile& best) {
+// Below 64 elements the 6 us that a split workgroup takes to set up and to add its sums count, 44
+// elements' worth with one transmit: 64 x 48 x 7 voxels, 33 frames, 16 elements, 1 transmit: 31
+// us unsplit, 33 with 4 groups, 61 with 16.
+bool choose_launch(const fq_grid& g, const TxHost& th, double fs_c, int A, int E, int fb, int nfb, int interp, DasTile& best) {
     static const double unsplit[4] = {0.0, 5.7, 6.7, 7.5};
     // (little work per row of a window: the staging shows)
     const double split4 = interp ? 1.5 : fb * A <= 9 ? 2.1 : 1.75, split16 = 0.6;
+    const double fixed = E < 64 ? 44.0 / (E * A) : 0.0;
     bool found = false;
     double best_time = 0.0;
     for (int groups : {1, 4, 16}) {
@@ -207,7 +211,7 @@ bool choose_launch(const fq_grid& g, const TxHost& th, double fs_c, int A, int f
             const int n = (int)std::min(1e6, std::ceil(per_cu));
             time = n > 6 ? per_cu * unsplit[3] / 3.0 : n / 3 * unsplit[3] + unsplit[n % 3];
         } else {
-            time = std::ceil(per_cu) * (groups == 4 ? split4 : split16);
+            time = std::ceil(per_cu) * ((groups == 4 ? split4 : split16) + fixed);
         }
         time *= t.cost;
         if (!found || time < best_time) {
@@ -253,7 +257,7 @@ extern "C" int das_launch_shape(const fq_probe* probe, const fq_tx* tx, const fq
     int nfb, fb, TR;
     frame_blocks(n_frames, n_samples, nfb, fb, TR);
     DasTile t{};
-    FQ_REQUIRE(choose_launch(*grid, th, probe->fs_hz / probe->c_mps, th.n, fb, nfb, interp, t),
+    FQ_REQUIRE(choose_launch(*grid, th, probe->fs_hz / probe->c_mps, th.n, probe->nx_el * probe->ny_el, fb, nfb, interp, t),
                "voxel spacing too coarse for the on-chip delay window");
     shape[0] = fb;
     shape[1] = t.at;
@@ -305,7 +309,7 @@ int das_prepare(const fq_probe* probe, const fq_tx* tx, const fq_grid* grid, int
     P.bblk = block_bytes(P.A, P.E, TR, P.fb);
     P.full = bmax * P.nfb;
     FQ_REQUIRE((size_t)W0 * das_row_lds(DAS_MAX_FB) <= DAS_LDS_BUDGET &&
-                   choose_launch(*grid, P.th, P.fs_c, P.A, P.fb, P.nfb, interp, P.tile),
+                   choose_launch(*grid, P.th, P.fs_c, P.A, P.E, P.fb, P.nfb, interp, P.tile),
                "voxel spacing too coarse for the on-chip delay window (%d rows)", W0);
 
     IqArgs& ia = P.ia;

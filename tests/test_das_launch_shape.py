@@ -4,7 +4,7 @@ import pytest
 import paper_2509_05464_amd as fq
 
 
-def shape(nx, ny, nz, frames, nx_el=2, spacing=1e-4):
+def shape(nx, ny, nz, frames, nx_el=32, spacing=1e-4):
     probe = fq.make_probe(nx_el, 2, 3e-4, 3e-4, 7.8e6, 31.25e6, 1540.0)
     grid = fq.make_grid(nx, ny, nz, 0.0, 0.0, 5e-3, spacing, spacing, spacing)
     return fq.das_launch_shape(probe, fq.make_tx([(0.0, 0.0)]), grid, frames, 512)
@@ -25,3 +25,9 @@ def test_frames_and_wide_windows():
     assert shape(40, 40, 24, 2, spacing=1.5e-3)[2:4] == (1, 1)
     with pytest.raises(fq.FqError):
         shape(40, 40, 24, 2, spacing=5e-3)
+
+
+@pytest.mark.parametrize('nx_el,groups', [(1, 1), (8, 1), (32, 16)])
+def test_few_elements_are_not_split(nx_el, groups):
+    """Too few elements to pay for a split workgroup's setting up; 64 do."""
+    assert shape(64, 48, 7, 33, nx_el=nx_el)[2] == groups

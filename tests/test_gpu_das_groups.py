@@ -27,7 +27,9 @@ def check(gpu, acq, interp, frames, groups):
 @pytest.mark.parametrize('groups,grid', [(16, (7, 5, 3)), (4, (48, 40, 20)), (1, (64, 64, 70))])
 def test_block_lengths(gpu, frames, interp, groups, grid):
     nx, ny, nz = grid
-    acq = C1.with_(nx=nx, ny=ny, nz=nz, n_frames=frames, nx_el=3, ny_el=3, z0=6e-3, tilts_deg=TILTS[:5], n_samples=767)
+    el = (11, 6) if groups == 4 else (3, 3)   # 4 does not divide 66; fewer elements than 16 groups
+    acq = C1.with_(nx=nx, ny=ny, nz=nz, n_frames=frames, nx_el=el[0], ny_el=el[1], z0=6e-3, tilts_deg=TILTS[:5],
+                   n_samples=767)
     check(gpu, acq, interp, frames, groups)
 
 
@@ -35,5 +37,6 @@ def test_block_lengths(gpu, frames, interp, groups, grid):
 @pytest.mark.parametrize('interp', [0, 1])
 @pytest.mark.parametrize('frames', [1, 8])
 def test_transmits_over_four_groups(gpu, angles, interp, frames):
-    acq = C1.with_(nx=40, ny=40, nz=40, n_frames=frames, nx_el=2, ny_el=3, z0=6e-3, tilts_deg=TILTS[:angles], n_samples=766)
+    acq = C1.with_(nx=40, ny=40, nz=40, n_frames=frames, nx_el=11, ny_el=6, z0=6e-3, tilts_deg=TILTS[:angles],
+                   n_samples=766)
     check(gpu, acq, interp, frames, 4)
