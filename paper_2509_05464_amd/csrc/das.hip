@@ -404,7 +404,7 @@ int launch_das(DasPlan& P, int fb0, int nb, int interp, const fq_grid* grid, dou
             da.zeta[j] = make_float2((float)std::cos(2 * M_PI * fr), (float)std::sin(2 * M_PI * fr));
         }
         hipLaunchKernelGGL(das_fn(P.fb, na, interp, P.tile.wide, P.tile.groups), dim3((unsigned)da.nwork),
-                           dim3(threads), 0, s, da);
+                           dim3(threads), P.tile.wide ? 2 * (size_t)da.WB : 0, s, da);
         FQ_LAUNCH_CHECK();
     }
     return FQ_OK;

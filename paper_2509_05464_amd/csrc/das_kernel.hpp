@@ -42,7 +42,7 @@ constexpr int DAS_THREADS = 256;      // one group
 constexpr int DAS_SPLIT_THREADS = 1024;
 constexpr int DAS_MAX_AT = 9;         // transmits per pass
 constexpr int DAS_ROWS = 320;         // rows of one LDS array (half the transmits of a pass)
-constexpr int DAS_ROWS_WIDE = 832;    // the same, for windows beyond 248 rows (AT <= 2)
+constexpr int DAS_ROWS_WIDE = 832;    // the same at most, for windows beyond 248 rows (AT <= 2: one window an array)
 __host__ __device__ constexpr int das_group_threads(int G) { return G == 1 ? DAS_THREADS : DAS_SPLIT_THREADS / G; }
 __host__ __device__ constexpr int das_vz(int G) { return G == 1 ? 2 : 1; }   // voxels per thread, consecutive in z
 constexpr int DAS_W_NARROW = 248;     // fixed point with 24 fraction bits holds 256 rows
@@ -91,7 +91,7 @@ __device__ __forceinline__ double das_lane(double x, int l) {
 }
 
 template <int AT, int INTERP, int FB, bool WIDE, int G>
-__global__ void __launch_bounds__(G == 1 ? DAS_THREADS : DAS_SPLIT_THREADS, WIDE || G > 1 ? 1 : 3) das_kernel(const DasArgs a) {
+__global__ void __launch_bounds__(G == 1 ? DAS_THREADS : DAS_SPLIT_THREADS, G > 1 ? 1 : 3) das_kernel(const DasArgs a) {
     constexpr int VZ = das_vz(G);
     constexpr int TPG = das_group_threads(G), WPG = TPG / 64;   // threads and wavefronts of a group
     constexpr int NT = INTERP ? 4 : 2;         // taps per delay
@@ -106,12 +106,13 @@ __global__ void __launch_bounds__(G == 1 ? DAS_THREADS : DAS_SPLIT_THREADS, WIDE
     constexpr int H1 = (AT + 1) / 2;           // transmits of the first half
     constexpr bool OWN = AT * FB <= 16;        // every transmit keeps its own sums
     constexpr int NS = OWN ? AT : 1;
-    constexpr int LDS_BYTES = das_rows(G, WIDE, FB) * ROWL;   // of a group
+    constexpr int LDS_BYTES = WIDE ? 16 : das_rows(G, WIDE, FB) * ROWL;   // of a group
     __shared__ __attribute__((aligned(16))) char ldsA[G * LDS_BYTES];
     __shared__ __attribute__((aligned(16))) char ldsB[G * LDS_BYTES];
+    extern __shared__ __attribute__((aligned(16))) char wide_lds[];   // wide: two windows
     const int grp = G == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / TPG);
-    char* const winA = ldsA + grp * LDS_BYTES;
-    char* const winB = ldsB + grp * LDS_BYTES;
+    char* const winA = WIDE ? wide_lds : ldsA + grp * LDS_BYTES;
+    char* const winB = WIDE ? wide_lds + a.WB : ldsB + grp * LDS_BYTES;
 
     // Workgroup id -> (tile, frame block), tiles fastest.  (Handing each XCD a contiguous
     // run of tiles cut the HBM traffic ~3x but ran 5.6% slower: the neighbouring tiles of one
