@@ -176,7 +176,9 @@ int das_beamform(const fq_probe* probe, const fq_tx* tx, const fq_grid* grid, in
  * (ws_bytes >= das_workspace_size(..., minimum=0)):
  *  das_demodulate -- rf2iq of every trace into ws (Algorithm 3, "convert to IQ");
  *  das_delay_sum  -- delay-and-sum with coherent compounding from ws into iq
- *                    (Algorithm 3, "apply delays" and "average over transmits").
+ *                    (Algorithm 3, "apply delays" and "average over transmits"), with the
+ *                    probe, tx, n_frames and n_samples that das_demodulate had: together
+ *                    they set the layout of ws.
  * das_beamform(...) == das_demodulate(...) followed by das_delay_sum(...), bit for bit.
  * Errors as das_beamform; FQ_E_WORKSPACE if ws cannot hold all frames. */
 int das_demodulate(const fq_probe* probe, const fq_tx* tx, int32_t n_frames, int32_t n_samples,

@@ -475,6 +475,11 @@ struct BwdArgs {
 //    input rows overlap, so the read needs no copy per tap), 18..20 db1..db3 (ones), 21..26
 //    dW4 (rows = channels; dL/dy as three BF16 terms per output).
 //  * dL/dy enters the products exactly (three BF16 terms), like the biases of the forward pass.
+//  * The accumulators truncate; over 1024 wavefronts the sums still lose no more than FP32 FMAs in
+//    256 did.  Gradient of 64 series repeated to 4096, against the 64 themselves (200 frames,
+//    relative L2, FMAs / here): db1 2.9e-7 / 7.6e-8, db2 2.2e-7 / 8.2e-8, db3 3.8e-7 / 6.9e-8, dW4
+//    2.8e-7 / 8.2e-8; the whole gradient against 64 bits with the same BF16 roundings, 8 sizes:
+//    5.15e-6 / 5.14e-6 (the quotient of GELU' by IEEE division / by the hardware reciprocal).
 //
 // Bound by the VALU (GELU' of 96 values a frame) and the matrix products, with one wavefront
 // per SIMD to issue both.  4096 series x 200 frames: 242 us for the two kernels, where one

@@ -434,8 +434,10 @@ __global__ void __launch_bounds__(64 * W) tridiag_step_kernel(const TriArgs a) {
 // through one compute unit).  Whole filter of 4096 voxels: 130 frames 886 -> 670 us, 200: 1775
 // -> 1015, 209: 3103 -> 1050, 400: 12131 -> 2220, 512: 21413 -> 3030.  At 1, 2, 4, 8 rows a
 // workgroup 400 frames take 2226, 2220, 2265, 2589 us and 200 frames 1014, 1041, 1055, 1175.
-// The line is at 128 frames: there the launches take 618 us and one workgroup 698, at 100 frames
-// 490 and 535, at 80 400 and 373, and 128 launches are 0.3 ms of the calling thread's time.
+// The line stands where the launches' cost to the calling thread does: on the GPU they win from
+// about 90 frames on (80 frames 400 us, one workgroup 373; 100: 490, 535; 128: 618, 698), but 128
+// launches hold the caller for 0.3 ms, half the filter's time, and one hardly at all; from
+// 129 frames on the GPU's gain (886 -> 670 us at 130) outgrows what the caller pays.
 constexpr int TRI_ONE = 128;
 template <int CT, bool FIRST>
 __global__ void __launch_bounds__(64) tridiag_row_kernel(const TriArgs a, int k) {
