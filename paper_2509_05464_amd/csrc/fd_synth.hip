@@ -173,7 +173,8 @@ __device__ __forceinline__ void elem_resp(const FdArgs& a, double dxc, double dy
             // comes last.  Where |j t| stays below 1e-12 (an offset of about 1e-14 m: the rounding
             // error of an element's position, seen from a scatterer on its axis) j stands for the
             // sine: the product of two such t, in the one reciprocal of both axes, is below FP32's
-            // range and its reciprocal infinite.
+            // range and its reciprocal infinite.  (The fraction c - floor(c) of a small negative c keeps
+            // FP32's grid just below 1: the sinc is off by up to 3e-8 / |c|, and lost below 3e-8 turns.)
             const float tx = (float)(a.bx_df_c * dx) * rinv, ty = (float)(a.by_df_c * dy) * rinv;
             const bool axis_x = fabsf(tx) < tmin, axis_y = fabsf(ty) < tmin;
             float d[KC];
