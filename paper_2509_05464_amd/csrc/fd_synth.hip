@@ -93,30 +93,6 @@ __device__ __forceinline__ void elem_xy(const FdArgs& a, int e, double& ex, doub
     ey = (e / a.nx_el) * a.pitch_y - a.hy;
 }
 
-// h[q] += g z_q 2^(-ar (j0 + q)) d[q] (d: null for 1), z_q unit phases stepped outwards from the
-// middle's zm by st, every amplitude by its own exponential: for a scatterer whose amplitude
-// at the middle, or its growth from there down, is past FP32's range.
-__device__ __forceinline__ void faint_resp(float2 zm, float2 st, float g, float ar, int j0, const float* d, float2* h) {
-    constexpr int M = KC / 2;
-    auto put = [&](int q, float2 z) {
-        const float s = g * __builtin_amdgcn_exp2f(-ar * (float)(j0 + q)) * (d ? d[q] : 1.0f);
-        h[q].x = fmaf(z.x, s, h[q].x);
-        h[q].y = fmaf(z.y, s, h[q].y);
-    };
-    float2 z = zm;
-#pragma unroll
-    for (int q = M; q < KC; ++q) {
-        put(q, z);
-        z = cmul(z, st);
-    }
-    z = zm;
-#pragma unroll
-    for (int q = M - 1; q >= 0; --q) {
-        z = cmul(z, make_float2(st.x, -st.y));
-        put(q, z);
-    }
-}
-
 // h[q] = sum_mu (r_ref/r) e^{(i k - alpha) r} D for f = (j0 + q) df, q < KC, of an element whose
 // centre is (dxc, dyc) off the scatterer; D = sinc sinc of the sub-element's direction.
 __device__ __forceinline__ void elem_resp(const FdArgs& a, double dxc, double dyc, double sz2, int j0,
@@ -125,7 +101,7 @@ __device__ __forceinline__ void elem_resp(const FdArgs& a, double dxc, double dy
 #pragma unroll
     for (int q = 0; q < KC; ++q) h[q] = make_float2(0.f, 0.f);
     float h0 = 0.0f;   // the response at f = 0
-    const float jm = (float)(j0 + M), tmin = 1e-12f * __builtin_amdgcn_rcpf((float)(j0 + KC));
+    const float tmin = 1e-12f * __builtin_amdgcn_rcpf((float)(j0 + KC));
     for (int mx = 0; mx < a.vx; ++mx) {
         const double dx = dxc - ((mx + 0.5) / a.vx - 0.5) * a.wx;
         const double dx2 = fma(dx, dx, sz2);
@@ -139,20 +115,20 @@ __device__ __forceinline__ void elem_resp(const FdArgs& a, double dxc, double dy
             const float2 zm = cis_cycles((double)(j0 + M) * cyc);
             const float2 st = cis_cycles(cyc);
             const float ar = (float)(a.alpha2_df * r);
-            const float at = __builtin_amdgcn_exp2f(-ar), ai = __builtin_amdgcn_exp2f(ar);
-            const float2 up = make_float2(st.x * at, st.y * at), dn = make_float2(st.x * ai, -st.y * ai);
+            // Amplitudes of the lower half, from j0 up, and of the middle: a scatterer whose
+            // attenuation over a step passes FP32's range decays to zero (steps down from the middle
+            // would grow past it, from nothing).
+            const float at = __builtin_amdgcn_exp2f(-ar);
+            float am[M + 1];
+            am[0] = __builtin_amdgcn_exp2f(-ar * (float)j0);
+#pragma unroll
+            for (int q = 0; q < M; ++q) am[q + 1] = am[q] * at;
+            const float2 up = make_float2(st.x * at, st.y * at), dn = make_float2(st.x, -st.y);
             float g = a.r_ref * rinv;
             h0 += g;
-            // 2^-100 at the middle: a step down then grows by 2^25 at most (j0 >= 0), four by 2^100
-            const bool faint = ar * jm > 100.0f;
             if (!a.dir) {
-                if (faint) {
-                    faint_resp(zm, st, g, ar, j0, nullptr, h);
-                    continue;
-                }
-                g *= __builtin_amdgcn_exp2f(-ar * jm);
-                float2 z = make_float2(zm.x * g, zm.y * g);
-                const float2 z0 = z;
+                const float2 z0 = make_float2(zm.x * g, zm.y * g);
+                float2 z = make_float2(z0.x * am[M], z0.y * am[M]);
 #pragma unroll
                 for (int q = M; q < KC; ++q) {
                     h[q].x += z.x;
@@ -163,8 +139,8 @@ __device__ __forceinline__ void elem_resp(const FdArgs& a, double dxc, double dy
 #pragma unroll
                 for (int q = M - 1; q >= 0; --q) {
                     z = cmul(z, dn);
-                    h[q].x += z.x;
-                    h[q].y += z.y;
+                    h[q].x = fmaf(z.x, am[q], h[q].x);
+                    h[q].y = fmaf(z.y, am[q], h[q].y);
                 }
                 continue;
             }
@@ -202,13 +178,8 @@ __device__ __forceinline__ void elem_resp(const FdArgs& a, double dxc, double dy
                 for (int q = 0; q < KC; ++q) d[q] *= s[q];
             }
             g *= __builtin_amdgcn_rcpf((axis_x ? 1.0f : (float)TWO_PI * tx) * (axis_y ? 1.0f : (float)TWO_PI * ty));
-            if (faint) {
-                faint_resp(zm, st, g, ar, j0, d, h);
-                continue;
-            }
-            g *= __builtin_amdgcn_exp2f(-ar * jm);
-            float2 z = make_float2(zm.x * g, zm.y * g);
-            const float2 z0 = z;
+            const float2 z0 = make_float2(zm.x * g, zm.y * g);
+            float2 z = make_float2(z0.x * am[M], z0.y * am[M]);
 #pragma unroll
             for (int q = M; q < KC; ++q) {
                 h[q].x = fmaf(z.x, d[q], h[q].x);
@@ -219,6 +190,7 @@ __device__ __forceinline__ void elem_resp(const FdArgs& a, double dxc, double dy
 #pragma unroll
             for (int q = M - 1; q >= 0; --q) {
                 z = cmul(z, dn);
+                d[q] *= am[q];
                 h[q].x = fmaf(z.x, d[q], h[q].x);
                 h[q].y = fmaf(z.y, d[q], h[q].y);
             }
@@ -268,11 +240,11 @@ __global__ void __launch_bounds__(FD_THREADS) fd_tx_kernel(const FdArgs a) {
 #pragma unroll
         for (int g = 0; g < NA; ++g) acc[q][g] = make_float2(0.f, 0.f);
 
-    float2* tab = lds + w * TAB;   // [eb][KC][NA] of this wavefront
+    float2* tab = lds + w * TAB;   // [EB][KC][NA] of this wavefront
     const int eb = min(EB, (a.n_elem + W - 1) / W);   // (up to 64 elements: shared evenly)
     for (int e0 = w * eb; e0 < a.n_elem; e0 += W * eb) {
         __builtin_amdgcn_wave_barrier();
-        for (int i = l; i < eb * KC * NA; i += 64) {
+        for (int i = l; i < TAB; i += 64) {
             const int el = i / (KC * NA), q = (i / NA) % KC, g = i % NA;
             const int e = e0 + el;
             float2 v = make_float2(0.f, 0.f);
